@@ -48,7 +48,7 @@ def kernel_source_hash():
     """Hash of the kernel sources with comments and blank lines removed (a comment edit does
     not change the kernels the counters were taken on)."""
     h = hashlib.sha256()
-    for f in ("ccr_kernels.hip", "ccr_internal.h"):
+    for f in ("ccr_kernels.hip", "ccr_lag.hip", "ccr_device.h", "ccr_internal.h"):
         text = open(os.path.join(ROOT, "paper_1712_06515_amd", "csrc", f)).read()
         text = re.sub(r"/\*.*?\*/", "", text, flags=re.S)
         for line in text.splitlines():
@@ -113,7 +113,9 @@ def roofline(name, avg_ms, tb, info, workload, streams=1):
     `streams` spectra per segment (2 with per-sample antenna functions)."""
     import numpy as np
     n_active = info["n_active"]
-    ns, P = int(info["n_s"]), int(info["P"])
+    # transforms per segment: on the lag-resolved grid its classes, else N_FFT = P n_s
+    grid = info.get("grid_ns", 0) > 0
+    ns, P = (info["grid_ns"], info["grid_classes"]) if grid else (int(info["n_s"]), int(info["P"]))
     if name == "resample" and info.get("farrow_used"):
         # Farrow form: one complex64 sample written per resampled sample, plus the band's
         # table (kFarDeg + 1 complex64 planes per input sample and detector) read once
@@ -141,16 +143,18 @@ def roofline(name, avg_ms, tb, info, workload, streams=1):
     per_unit = f"P (5 n_s log2 n_s + 6 n_s) FP32 flop per (template, detector, segment), n_s={ns}, P={P}"
     if streams != 1:
         per_unit += f", x{streams} spectra per segment"
-    if name in ("spectra_pairs", "fused"):
+    if name in ("spectra_pairs", "fused") and not grid:
         # the direct pair sum runs in the same kernel: 8 flop per (template, pair, bin) over the
         # pairs whose two spectra are present
         flops += 8.0 * info["n_pairs_present"] * info["n_f"] * tb
         per_unit += " + 8 flop per (template, pair with both spectra present, bin)"
-    if name == "spectra_wide":
-        per_unit += " (segment FFTs only: the pair sums, done as window sums, are not counted)"
+    if name == "spectra_wide" or grid:
+        per_unit += " (segment FFTs only: the pair sums are not counted)"
     ach = flops / (avg_ms * 1e-3) / 1e12
     kern = {"spectra": "k_spectra16_m" if ns == 256 else "k_spectra_m", "spectra_pairs": "k_spectra_pairs_m",
             "fused": "k_fused", "spectra_wide": "k_spectra_wide_m"}[name]
+    if grid and name in ("spectra_pairs", "spectra_wide"):
+        kern = "k_lag"
     return {"kernel": kern, "bound": "alu", "achieved": ach, "peak": FP32_PEAK_TFLOPS, "unit": "TFLOP/s",
             "frac": ach / FP32_PEAK_TFLOPS, "traffic": read_traffic(name, workload),
             "avg_launch_ms": avg_ms, "algorithmic_flops_per_launch": flops, "per_unit": per_unit}
@@ -338,6 +342,7 @@ def main():
         step()
     kt = ctx.kernel_times(reset=True)
     ctx.set_option("timing", 0)
+    info["grid_ns"], info["grid_classes"] = ctx.get_option("grid_ns"), ctx.get_option("grid_classes")
 
     # plain FP64 path: one template per launch sequence, no graph, on a bounded subset
     nsub = min(args.fp64_templates, n_t)
@@ -433,6 +438,7 @@ def form_lines(args, ds, info0):
             ctx.kernel_times(reset=True)
             step()
             kt = ctx.kernel_times(reset=True)
+            inf["grid_ns"], inf["grid_classes"] = ctx.get_option("grid_ns"), ctx.get_option("grid_classes")
         dom = max((k for k in kt if kt[k][1]), key=lambda k: kt[k][0])
         line = {"value": len(tm) * inf["n_f"] / sec, "unit": "rho-evals/s", "ms_per_step": 1e3 * sec,
                 "templates": len(tm), "kernels_ms_per_step": {k: v[0] for k, v in kt.items() if v[1]},

@@ -144,9 +144,10 @@ typedef struct {
      * sum_n |fitted - exact tap weight| (relative to the input amplitude). */
     int64_t farrow_degree;
     double farrow_err;
-    /* The segment FFT as the kernels take it: N_FFT = P n_s, P transforms of n_s points per
-     * (template, detector, segment), one per residue class of the output bins (n_s the power of
-     * two holding N_K, at least 256 where N_FFT allows). */
+    /* N_FFT = P n_s, n_s the power of two holding N_K (at least 256 where N_FFT allows): the
+     * kernels that transform at the output bins take P transforms of n_s points per (template,
+     * detector, segment), one per residue class of the bins.  Bands that run on the lag-resolved
+     * grid take fewer (options "grid_ns" and "grid_classes"). */
     int64_t n_s, P;
 } ccr_band_info;
 
@@ -179,9 +180,10 @@ const char *ccr_last_error(const ccr_ctx *ctx);
  *                     applies to device outputs only;
  *   "round_templates" at most this many templates in one launch round (0, the default: as
  *                     many as the workspace budget holds);
- *   "spectra_kernel"  1: run the 256- to 1024-point spectra + pair-sum kernel on every band
- *                     it takes, also where the 256-point one applies; 0 (default): the
- *                     256-point kernel first;
+ *   "spectra_kernel"  0 (default): bands of same-time pairs on 256-point segments run the
+ *                     256-point spectra + pair-sum kernel; 1: they run the kernel of the other
+ *                     bands.  (With lags up to 4 both values run the lag-resolved grid; the value
+ *                     then only says which slot of ccr_kernel_time, 6 or 7, counts it.);
  *   "autotune"        1: on the first call for a given band list and precision, time the
  *                     first launch round of each candidate launch shape and keep the fastest
  *                     per template: the spectra kernel (where a band can take either) and
@@ -205,7 +207,9 @@ ccr_status ccr_set_option(ccr_ctx *ctx, const char *name, int64_t value);
  * (0, or -1 for the kernel, before any tuning), or "resample_templates": the
  * templates one resampling workgroup handles from one staged input window (a constant of the
  * build), "farrow_templates" / "farrow_degree": the same for the Farrow-form kernel and its
- * polynomial degree.  CCR_EUNSUP for an unknown name. */
+ * polynomial degree, or "grid_ns" / "grid_classes": transform length and transforms per segment
+ * of the lag-resolved grid, for the first band of the last call (0: not on the grid).
+ * CCR_EUNSUP for an unknown name. */
 ccr_status ccr_get_option(ccr_ctx *ctx, const char *name, int64_t *value);
 
 /* Add a band; returns its id and the part of the plan known before data (n_k, dt, f_het,
@@ -325,8 +329,9 @@ ccr_status ccr_sync(ccr_ctx *ctx);
  * since the last ccr_reset_kernel_times (HIP events recorded on the launch stream around each
  * launch).  kernel: 0 resampling, 1 segment spectra, 2 pair sum, 3 final scaling,
  * 4 fused resampling + spectra + pair sum, 5 FP64 time base (per-segment interpolating polynomial),
- * 6 spectra + pair sum in one kernel (split precision, 256-point segments), 7 the same for
- * 1024-point segments, 8 the SFT front end (ccr_sft_series).
+ * 6 spectra + pair sum in one kernel (split precision, 256-point segments with per-segment
+ * Gamma^ave weights), 7 the same for every other band that has such a kernel, 8 the SFT front end
+ * (ccr_sft_series).
  * Waits for the recorded launches to finish. */
 ccr_status ccr_kernel_time(ccr_ctx *ctx, int kernel, double *ms, int64_t *launches);
 ccr_status ccr_reset_kernel_times(ccr_ctx *ctx);

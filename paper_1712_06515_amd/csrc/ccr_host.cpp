@@ -23,6 +23,8 @@ namespace {
 
 constexpr double kPi = 3.14159265358979323846;
 constexpr int kRawStride = 5;
+constexpr size_t kMaxLds = 65536;
+constexpr size_t kLagMaxLds = 160 * 1024;  // the whole LDS of a CU
 constexpr long double kPiL = 3.141592653589793238462643383279502884L;
 
 // ------------------------------------------------------------------ device buffers
@@ -65,6 +67,12 @@ struct DetData {
     std::vector<double> ar, br;  // per-sample antenna functions on the source lattice, or empty
 };
 
+// Lag-resolved grid of a band for one precision (see LagDev) and its device tables.
+struct LagGrid {
+    LagDev d{};
+    size_t fin_lds = 0;  // LDS of the finishing kernel
+};
+
 struct Plan {
     int64_t n_k = 0, n_seg = 0, n_fft = 0, n_f = 0, k_lo = 0, n_s = 0, P = 0, n_pairs = 0;
     double dt = 0, f_het = 0, df_load = 0, t_coh = 0, dlf = 0, t_fft = 0, nu_r = 0, norm = 0;
@@ -85,7 +93,9 @@ struct Band {
     // device tables
     DevBuf d_x, d_mask, d_anchor, d_earth, d_win64, d_win32, d_cheb_x, d_mono, d_tw64, d_tw32, d_bin_m, d_bin_p,
         d_bin_kb, d_bin_pos, d_segw, d_segwf, d_active, d_work, d_seg_work, d_tmpl, d_lagph, d_seg_any, d_col_bin, d_bin_col, d_zero256,
-        d_class_start, d_farrow, d_farrow_A, d_cls_m0, d_pw, d_pwf;
+        d_class_start, d_farrow, d_farrow_A, d_cls_m0, d_pw, d_pwf, d_lag;
+    LagGrid lag[2];  // split precision, FP64; their tables, with segwd and seg_bits, lie in d_lag
+    size_t off_segwd = 0, off_seg_bits = 0;
     bool per_sample = false;  // every detector has per-sample antenna functions (two spectra streams)
     int wide_jmax = 0, wide_ncol = 0;  // 1024-point spectra + pair-sum kernel (see BandDev)
     int64_t far_len = 0;  // plane length of the Farrow table, 0 when the band has none
@@ -138,6 +148,7 @@ struct ccr_ctx {
     };
     std::vector<Tuned> tuned;
     int64_t last_tuned_k_chunk = 0, last_tuned_template_batch = 0, last_tuned_spectra = -1, last_tuned_round_templates = 0;
+    int64_t last_grid_ns = 0, last_grid_classes = 0;  // first band of the last planned call
     struct Timed {
         int kind;
         hipEvent_t a, b;
@@ -267,6 +278,179 @@ ccr_status make_plan(ccr_ctx *c, const Band &B, Plan &pl) {
 }
 
 int64_t bin_index(const Plan &pl, int64_t i) { return pl.k_lo + (int64_t)std::floor(pl.nu_r * (double)i); }
+
+// ------------------------------------------------------------------ lag-resolved grid
+
+// Interpolation from a grid with N_G points per cycle to a function whose Fourier coefficients
+// (sample lags) lie within +-(N_K - 1): taps sinc(x) I0(beta sqrt(1 - (2x / W)^2)) / I0(beta) at
+// grid distance |x| < W / 2, a Kaiser-windowed sinc whose transition band is the grid's spare
+// 1 - (2 N_K - 1) / N_G.  W taps give beta = pi sqrt((W (1 - 1/sigma) / 2)^2 - 1), sigma = N_G /
+// (2 N_K - 1), and a relative error of about e^(-beta): 180 dB (2e-9) below the split path's
+// FP32 rounding (4e-7), 300 dB (8e-15, measured) at FP64 rounding.
+constexpr double kLagSigmaMin = 1.05;
+
+int lag_taps(int64_t n_k, int64_t ng, bool fp64, double *beta) {
+    const double spare = 1.0 - (double)(2 * n_k - 1) / (double)ng;
+    const double b = 0.1102 * ((fp64 ? 300.0 : 180.0) - 8.7);
+    const int w = 2 * (int)std::ceil(std::sqrt(b * b / (kPi * kPi) + 1.0) / spare);
+    const double h = 0.5 * w * spare;
+    *beta = kPi * std::sqrt(std::max(0.0, h * h - 1.0));
+    return w;
+}
+
+int64_t floor_div(int64_t a, int64_t b) { return a / b - ((a % b != 0 && (a < 0) != (b < 0)) ? 1 : 0); }
+
+// Detectors that one workgroup of the grid's kernel sums over (see LagDev::n_sub).
+int lag_dets(int Q, int R, int pairs) {
+    if (R == 0 || (pairs & 3) == 3) return Q;
+    return pairs == CCR_PAIRS_SAME ? 1 : 2;
+}
+
+// Host tables of a band's grid.
+struct LagTables {
+    std::vector<float2> tw32, step32;
+    std::vector<double2> tw64, step64;
+    std::vector<int> g0, frac;
+    std::vector<double> wt;
+};
+
+// The grid of a band, if it runs on one: pairs at lags up to kLagMaxR (not every ordered pair) of
+// segments of 256 points and more.  ns is a transform of the kernels (256, 512, in split
+// precision 1024), P the number of classes; of the choices with N_G >= 1.05 (2 N_K - 1), or
+// whose points hold the output bins themselves (N_G a multiple of N_FFT, one tap), the one with
+// the fewest vector instructions per segment is taken: the transforms (570, 255, 115 a wavefront
+// for 1024, 512, 256 points as counted in the kernels, 4 per extra row folded) and the pair sums
+// (8 per lag and 4 per detector + 12 for 64 columns).
+// Choices whose transforms of one step do not fit in a CU's LDS are left out.
+bool lag_plan(const Plan &pl, const ccr_band &b, int Q, bool streams, bool fp64, LagDev &d) {
+    d = LagDev{};
+    const int R = b.max_lag;
+    const bool cross = b.pairs & CCR_PAIRS_CROSS, same = b.pairs & CCR_PAIRS_SAME;
+    const int n_sub = R == 0 || (cross && same) ? 1 : (same ? Q : std::max(1, Q * (Q - 1) / 2));
+    const int cs = fp64 ? 16 : 8;
+    if (b.pairs == CCR_PAIRS_ALL || R > kLagMaxR || pl.n_s < 256) return false;
+    const int64_t k0 = bin_index(pl, 0), k1 = bin_index(pl, pl.n_f - 1);
+    double best = HUGE_VAL;
+    for (int ns = 256; ns <= (fp64 ? 512 : 1024); ns *= 2) {
+        const int nf = (int)((pl.n_k + ns - 1) / ns);
+        if (nf > 4) continue;
+        const int64_t pmin = std::max<int64_t>(1, (int64_t)std::ceil(kLagSigmaMin * (double)(2 * pl.n_k - 1) / ns));
+        std::vector<int64_t> cand{pmin, pmin + 1, pmin + 2};
+        if (pl.n_fft % ns == 0) cand.push_back(pl.n_fft / ns);
+        for (int64_t P : cand) {
+            const int64_t ng = P * ns;
+            const bool direct = ng % pl.n_fft == 0;
+            if ((!direct && ng < kLagSigmaMin * (double)(2 * pl.n_k - 1)) || ng > (1 << 22) || P > 4096) continue;
+            double beta = 0.0;
+            const int w = direct ? 1 : lag_taps(pl.n_k, ng, fp64, &beta);
+            const int64_t gmin = floor_div(k0 * ng, pl.n_fft) - (direct ? 0 : w / 2 - 1);
+            const int64_t gmax = floor_div(k1 * ng, pl.n_fft) + (direct ? 0 : w / 2);
+            const int v = ns / 64;
+            int64_t m0 = floor_div(floor_div(gmin, P), v) * v;
+            int64_t span = floor_div(gmax, P) - m0 + 1;
+            const bool wrap = span >= ns;
+            if (wrap) {
+                m0 = 0;
+                span = ns;
+            }
+            const int exch = (ns + 64) * cs / 2;  // ns + ns / V = ns + 64 values of one component
+            const int slot = (int)std::max<int64_t>(exch, (span + 63) / 64 * 64 * cs);
+            if ((size_t)kLagSegs * lag_dets(Q, R, b.pairs) * (streams ? 2 : 1) * slot > kLagMaxLds) continue;
+            const double fft = ns == 1024 ? 570.0 : (ns == 512 ? 255.0 : 115.0);
+            const double cost = (double)P * (Q * (fft + 4.0 * (nf - 1) * v) +
+                                             (double)((span + 63) / 64) * (8.0 * R + 4.0 * Q + 12.0));
+            if (cost >= best) continue;
+            best = cost;
+            d.on = 1;
+            d.ns = ns;
+            d.P = (int)P;
+            d.ng = (int)ng;
+            d.nfold = nf;
+            d.m0 = (int)(((m0 % ns) + ns) % ns);
+            d.span = (int)span;
+            d.wrap = wrap ? 1 : 0;
+            d.taps = w;
+            d.n_sub = n_sub;
+            d.slot_bytes = slot;
+        }
+    }
+    return d.on != 0;
+}
+
+// Tables of a planned grid (g0 holds the taps' first grid index less P m0, unwrapped where every
+// grid point is kept) and the finishing kernel's shape.
+void lag_tables(const Plan &pl, bool fp64, LagGrid &L, LagTables &t) {
+    LagDev &d = L.d;
+    const int64_t ng = d.ng, nfft = pl.n_fft;
+    auto root = [&](int64_t j) {
+        const long double a = -2.0L * kPiL * (long double)(j % ng) / (long double)ng;
+        return make_double2((double)cosl(a), (double)sinl(a));
+    };
+    t.tw64.resize((size_t)ng);
+    for (int64_t j = 0; j < ng; ++j) t.tw64[(size_t)j] = root(j);
+    const int v = d.ns / 64;
+    t.step64.resize((size_t)d.P * v * d.nfold);
+    for (int64_t p = 0; p < d.P; ++p)
+        for (int64_t r = 0; r < (int64_t)v * d.nfold; ++r)
+            t.step64[(size_t)(p * v * d.nfold + r)] = t.tw64[(size_t)(((p + (int64_t)d.P * d.m0) * 64 * r) % ng)];
+    auto narrow = [](const std::vector<double2> &a, std::vector<float2> &o) {
+        o.resize(a.size());
+        for (size_t i = 0; i < a.size(); ++i) o[i] = make_float2((float)a[i].x, (float)a[i].y);
+    };
+    if (!fp64) {
+        narrow(t.tw64, t.tw32);
+        narrow(t.step64, t.step32);
+    }
+    // taps: the bin kbar lies at grid coordinate kbar N_G / N_FFT; its fraction is a multiple of
+    // gcd(N_G, N_FFT) / N_FFT
+    const int64_t gc = [](int64_t a, int64_t b) {
+        while (b) {
+            const int64_t r = a % b;
+            a = b;
+            b = r;
+        }
+        return a;
+    }(ng, nfft);
+    const int64_t nfrac = nfft / gc;
+    double beta = 0.0;
+    const int w = d.taps;
+    if (w > 1) (void)lag_taps(pl.n_k, ng, fp64, &beta);
+    t.wt.assign((size_t)nfrac * w, 1.0);
+    if (w > 1) {
+        const double i0b = std::cyl_bessel_i(0.0, beta);
+        for (int64_t f = 0; f < nfrac; ++f)
+            for (int j = 0; j < w; ++j) {
+                const double x = (double)f / (double)nfrac - (double)(j - (w / 2 - 1));
+                const double z = 1.0 - (2.0 * x / w) * (2.0 * x / w);
+                const double sc = x == 0.0 ? 1.0 : std::sin(kPi * ((double)f / (double)nfrac)) / (kPi * x);
+                // sin(pi x) = +-sin(pi f / nfrac): the sign alternates with the tap
+                const double sg = ((j - (w / 2 - 1)) & 1) ? -1.0 : 1.0;
+                t.wt[(size_t)f * w + j] =
+                    z < 0.0 ? 0.0 : (x == 0.0 ? 1.0 : sg * sc) * std::cyl_bessel_i(0.0, beta * std::sqrt(z)) / i0b;
+            }
+    }
+    t.g0.resize((size_t)pl.n_f);
+    t.frac.resize((size_t)pl.n_f);
+    // absolute grid index of the first column: P m0 with m0 in (-ns, ns) as planned
+    const int64_t first = floor_div(bin_index(pl, 0) * ng, nfft) - (w > 1 ? w / 2 - 1 : 0);
+    const int64_t off = ((first % ng) + ng) % ng;  // mod N_G
+    const int64_t rel0 = d.wrap ? off : ((off - (int64_t)d.P * d.m0) % ng + ng) % ng;
+    for (int64_t i = 0; i < pl.n_f; ++i) {
+        const int64_t num = bin_index(pl, i) * ng;
+        const int64_t g = floor_div(num, nfft);
+        t.g0[(size_t)i] = (int)(rel0 + (g - (w > 1 ? w / 2 - 1 : 0) - first));
+        t.frac[(size_t)i] = (int)((num - g * nfft) / gc);
+    }
+    // bins per thread: all of kLagFinBins where that leaves a template several workgroups
+    d.fin_bpt = pl.n_f > 4 * kLagFinThreads ? kLagFinBins : 1;
+    int64_t cols = 0;
+    const int64_t nb = (int64_t)kLagFinThreads * d.fin_bpt;
+    for (int64_t b0 = 0; b0 < pl.n_f; b0 += nb) {
+        const int64_t b1 = std::min<int64_t>(pl.n_f, b0 + nb);
+        cols = std::max<int64_t>(cols, t.g0[(size_t)b1 - 1] + w - t.g0[(size_t)b0]);
+    }
+    L.fin_lds = (size_t)cols * sizeof(double2);
+}
 
 // ------------------------------------------------------------------ Earth model
 
@@ -753,6 +937,59 @@ ccr_status prepare(ccr_ctx *c, Band &B) {
                                                      (float)(segw[e].bhat * segw[e].scale));
         if ((st = upload(c, B.d_segwf, segwf))) return st;
     }
+    // the grid's tables of both precisions, the FP64 pair weights and the activity bits share one
+    // allocation and one copy
+    {
+        std::vector<char> pack;
+        auto put = [&](const auto &v) {
+            const size_t off = (pack.size() + 255) & ~(size_t)255, n = v.size() * sizeof(v[0]);
+            pack.resize(off + n);
+            if (n) std::memcpy(pack.data() + off, v.data(), n);
+            return off;
+        };
+        std::vector<double2> segwd(segw.size());
+        for (size_t e = 0; e < segw.size(); ++e)
+            segwd[e] = seg_work[e] < 0 ? make_double2(0.0, 0.0)
+                                       : make_double2(segw[e].ahat * segw[e].scale, segw[e].bhat * segw[e].scale);
+        std::vector<uint32_t> bits((size_t)M, 0);
+        for (int X = 0; X < Q; ++X)
+            for (int64_t K = 0; K < M; ++K)
+                if (seg_work[(size_t)X * M + K] >= 0) bits[(size_t)K] |= 1u << X;
+        B.off_segwd = put(segwd);
+        B.off_seg_bits = put(bits);
+        size_t off[2][5] = {};
+        for (int f = 0; f < 2; ++f) {
+            LagGrid &L = B.lag[f];
+            if (!lag_plan(pl, B.p, Q, per_sample, f == 1, L.d)) continue;
+            LagTables t;
+            lag_tables(pl, f == 1, L, t);
+            if (L.fin_lds > kMaxLds) {
+                L.d.on = 0;
+                continue;
+            }
+            off[f][0] = f == 1 ? put(t.tw64) : put(t.tw32);
+            off[f][1] = f == 1 ? put(t.step64) : put(t.step32);
+            off[f][2] = put(t.g0);
+            off[f][3] = put(t.frac);
+            off[f][4] = put(t.wt);
+        }
+        if ((st = upload(c, B.d_lag, pack))) return st;
+        const char *base = B.d_lag.as<char>();
+        for (int f = 0; f < 2; ++f) {
+            LagDev &d = B.lag[f].d;
+            if (!d.on) continue;
+            if (f == 1) {
+                d.tw64 = reinterpret_cast<const double2 *>(base + off[f][0]);
+                d.step64 = reinterpret_cast<const double2 *>(base + off[f][1]);
+            } else {
+                d.tw32 = reinterpret_cast<const float2 *>(base + off[f][0]);
+                d.step32 = reinterpret_cast<const float2 *>(base + off[f][1]);
+            }
+            d.g0 = reinterpret_cast<const int *>(base + off[f][2]);
+            d.frac = reinterpret_cast<const int *>(base + off[f][3]);
+            d.wt = reinterpret_cast<const double *>(base + off[f][4]);
+        }
+    }
     // per-sample stream weights (a_r, b_r) / (sigma_XK^2 sqrt(N_K)): hat a_r times the spectra's
     // 1 / (sigma sqrt N_K)
     B.per_sample = per_sample;
@@ -990,9 +1227,11 @@ ccr_status prepare_templates(ccr_ctx *c, Band &B) {
     return upload(c, B.d_tmpl, B.tmpl);
 }
 
-BandDev band_dev(const Band &B) {
+// The band's device descriptor, with the grid of the given precision.
+BandDev band_dev(const Band &B, bool fp64) {
     const Plan &pl = B.plan;
     BandDev d;
+    d.lag = B.lag[fp64 ? 1 : 0].d;
     d.Q = B.Q;
     d.n = B.det[0].n;
     d.n_k = (int)pl.n_k;
@@ -1026,6 +1265,8 @@ BandDev band_dev(const Band &B) {
     d.bins_unique = B.bins_unique;
     d.segw = B.d_segw.as<SegWeight>();
     d.segwf = B.d_segwf.as<float2>();
+    d.segwd = reinterpret_cast<const double2 *>(B.d_lag.as<char>() + B.off_segwd);
+    d.seg_bits = reinterpret_cast<const uint32_t *>(B.d_lag.as<char>() + B.off_seg_bits);
     d.active = B.d_active.as<uint8_t>();
     d.work = B.d_work.as<int>();
     d.seg_work = B.d_seg_work.as<int>();
@@ -1106,8 +1347,6 @@ void collect_times(ccr_ctx *c) {
     c->timed.clear();
 }
 
-
-constexpr size_t kMaxLds = 65536;
 // host staging (and scratch region) of the no-allocation entry point's tables
 constexpr size_t kNoAllocTableBytes = (size_t)1 << 20;
 
@@ -1182,13 +1421,17 @@ struct Variant {
     bool wallp = false;  // wide: every ordered pair (stream-sum partials)
     bool wps = false;    // wide: two spectra streams per segment (per-sample antenna functions)
     int wns = 0;         // wide: segment FFT length (256, 512 or 1024)
+    bool lag = false;    // spectra + pair sum on the lag-resolved grid
+    LagKey lk;
+    int timer = 0;       // kernel-time slot of the spectra stage (not part of the kernel choice)
     int DT = 0, window = 0, n_s = 0, nr = 0, n_cheb = kCheb;
     int wcols = 0, wqm = 0, wts = 0, wwv = 0;  // wide: bins of a class per lane, detector count,
                                                // segments a step, wavefronts a workgroup
     bool operator==(const Variant &o) const {
         return sp == o.sp && reg16 == o.reg16 && z4 == o.z4 && ss == o.ss && far == o.far && wide == o.wide &&
                DT == o.DT && window == o.window && n_s == o.n_s && nr == o.nr && n_cheb == o.n_cheb &&
-               wcols == o.wcols && wqm == o.wqm && wts == o.wts && wwv == o.wwv && wallp == o.wallp && wns == o.wns && wps == o.wps;
+               wcols == o.wcols && wqm == o.wqm && wts == o.wts && wwv == o.wwv && wallp == o.wallp && wns == o.wns && wps == o.wps &&
+               lag == o.lag && lk == o.lk;
     }
 };
 
@@ -1207,6 +1450,7 @@ struct Round {
     int64_t n_tmpl = 0;  // templates of those items
     Variant v;
     size_t lds = 0;     // dynamic LDS of the spectra + pair-sum kernel
+    size_t fin_lds = 0;  // and of the grid's finishing kernel
     int64_t blocks[kStages] = {0, 0, 0, 0, 0};
     size_t y_bytes = 0, F_bytes = 0, part_bytes = 0, coef_bytes = 0;
     size_t arena() const { return arena_bytes_of(coef_bytes, y_bytes, F_bytes, part_bytes); }
@@ -1230,6 +1474,25 @@ struct BatchParams {
     int spectra = 0;  // 1: the wide spectra + pair-sum kernel wherever it applies, 0: the 256-point one first
 };
 
+// LDS of a workgroup of the grid's kernel: a step's transforms.
+size_t lag_lds(const BandDev &bd) {
+    return (size_t)kLagSegs * lag_dets(bd.Q, bd.R, bd.pairs) * (bd.pw ? 2 : 1) * bd.lag.slot_bytes;
+}
+
+// Whether a band runs on the lag-resolved grid, and the kernel variant that takes it.
+bool lag_fits(const BandDev &bd, LagKey &k) {
+    if (!bd.lag.on) return false;
+    if (bd.pairs == CCR_PAIRS_CROSS && bd.Q < 2) return false;
+    k.ns = bd.lag.ns;
+    k.cross = bd.pairs == CCR_PAIRS_CROSS && bd.R > 0;
+    k.ps = bd.pw != nullptr;
+    k.rm = bd.R == 0 ? 0 : (k.cross || k.ps || bd.R > 2 ? 4 : bd.R);
+    const int per = lag_cols(k.ns);
+    k.waves = 2;
+    while (k.waves * per < bd.lag.span) k.waves *= 2;
+    return k.waves <= 8;
+}
+
 Variant variant_of(const BandDev &bd, bool fp64, bool short_series, bool farrow, bool prefer_wide,
                    bool streams = true) {
     Variant v;
@@ -1246,13 +1509,23 @@ Variant variant_of(const BandDev &bd, bool fp64, bool short_series, bool farrow,
     bw.ps2 = bd.pw != nullptr ? 1 : 0;
     const bool wide_ok = (bd.pw == nullptr || (streams && v.far && bd.pwf != nullptr)) && spectra_wide_ok(bw, fp64, kMaxLds);
     v.sp = plain && spectra_pairs_ok(bd, fp64, kMaxLds) && !(prefer_wide && wide_ok);
-    v.wide = !v.sp && wide_ok;
+    v.timer = v.sp ? 6 : 7;
+    // same-time pairs on 256-point segments stay on their own kernel: N_FFT is then 2 to 4
+    // transforms too, and only the decimated bins are summed (120-day band, 512 templates: 7.4 ms
+    // there, 10 ms on the grid)
+    if (!(v.sp && bd.R == 0) && lag_fits(bd, v.lk)) {
+        v.lag = true;
+        v.sp = false;
+    }
+    v.wide = !v.sp && !v.lag && wide_ok;
     v.wallp = v.wide && bd.allp;
     v.wps = v.wide && bd.pw != nullptr;
     v.DT = bd.D == 8 ? 8 : 0;
     v.window = bd.window;
     v.n_cheb = fp64 ? kCheb : bd.cheb_split;
-    if (v.wide) {
+    if (v.lag) {
+        // one kernel per key; the rest of the variant is the time base's and the resampler's
+    } else if (v.wide) {
         v.wns = bd.n_s;
         v.wcols = spectra_wide_cols(bd);
         v.wqm = bd.Q;
@@ -1275,7 +1548,7 @@ int64_t stage_max_blocks(const Variant &v, int st) {
     int threads = 64;
     if (st == kStTimebase) threads = tb_entries(v.n_cheb) * v.n_cheb;
     else if (st == kStResample) threads = v.far ? 256 : 64;
-    else if (st == kStSpectra) threads = v.sp ? 64 : (v.wide ? 64 * v.wwv : (v.reg16 ? 128 : spectra_threads(v.n_s)));
+    else if (st == kStSpectra) threads = v.lag ? 64 * v.lk.waves : v.sp ? 64 : (v.wide ? 64 * v.wwv : (v.reg16 ? 128 : spectra_threads(v.n_s)));
     else if (st == kStPairs) threads = kPairsThreads;
     else if (st == kStFinish) threads = kFinishThreads;
     return std::min<int64_t>(kMaxBlocks, (((int64_t)1 << 32) - 1) / threads);
@@ -1320,7 +1593,7 @@ ccr_status build_plan(ccr_ctx *c, bool fp64, int n_bands, const int *band_ids, v
     struct Pending {
         WorkItem it;
         Variant v;
-        size_t y, F, part, coef, lds;
+        size_t y, F, part, coef, lds, fin_lds;
         int64_t blk[kStages];
     };
     std::vector<Pending> pend;
@@ -1328,22 +1601,32 @@ ccr_status build_plan(ccr_ctx *c, bool fp64, int n_bands, const int *band_ids, v
     for (int bi = 0; bi < n_bands; ++bi) {
         const Band &B = *get_band(c, band_ids[bi]);
         const Plan &pl = B.plan;
-        BandDev bd = band_dev(B);
+        BandDev bd = band_dev(B, fp64);
         bd.far_stage = (int)c->opt_farrow_stage;
         cp.bands.push_back(bd);
         const Variant v = variant_of(bd, fp64, B.short_series, c->opt_farrow != 0, bp.spectra != 0, !bp.no_streams);
         if (v.wps) cp.bands.back().ps2 = 1;
+        if (bi == 0) {
+            c->last_grid_ns = v.lag ? bd.lag.ns : 0;
+            c->last_grid_classes = v.lag ? bd.lag.P : 0;
+        }
         const int res_t = v.far ? kFarTemplates : kResTemplates;  // templates per resampler workgroup
         if (std::find(variants.begin(), variants.end(), v) == variants.end()) variants.push_back(v);
         int64_t kc = bp.k_chunk > 0 ? bp.k_chunk : std::min<int64_t>(pl.n_seg, 256);
         kc = std::max<int64_t>(1, std::min<int64_t>(kc, pl.n_seg));
-        const int nch = (int)((pl.n_seg + kc - 1) / kc);
         const size_t y1 = (size_t)B.Q * pl.n_seg * pl.n_k * cs * (v.wps ? 2 : 1);
         // two spectra streams per segment with per-sample weights; four partials per bin (the
         // stream sums) for every ordered pair
-        const size_t F1 = (v.sp || v.wide) ? 0 : (size_t)B.Q * pl.n_seg * pl.n_f * cs * (bd.pw ? 2 : 1);
-        const size_t part1 = (size_t)nch * pl.n_f * sizeof(double) * (bd.allp ? 4 : 1);
+        const size_t F1 = (v.sp || v.wide || v.lag) ? 0 : (size_t)B.Q * pl.n_seg * pl.n_f * cs * (bd.pw ? 2 : 1);
         const size_t coef1 = (size_t)std::max(B.n_work, 1) * kCheb * sizeof(double);
+        const size_t lag1 = (size_t)bd.lag.n_sub * (2 * bd.R + 1) * bd.lag.P * bd.lag.span * sizeof(double);
+        // a fixed workspace that one template's chunk partials would overflow: longer chunks
+        while (v.lag && budget_override > 0 && kc < pl.n_seg &&
+               arena_bytes_of(coef1, y1, F1, (size_t)((pl.n_seg + kc - 1) / kc) * lag1) > budget)
+            kc = std::min<int64_t>(2 * kc, pl.n_seg);
+        const int nch = (int)((pl.n_seg + kc - 1) / kc);
+        const size_t part1 = v.lag ? (size_t)nch * lag1
+                                   : (size_t)nch * pl.n_f * sizeof(double) * (bd.allp ? 4 : 1);
         WorkItem proto;
         std::memset(&proto, 0, sizeof proto);
         proto.band = bi;
@@ -1353,11 +1636,13 @@ ccr_status build_plan(ccr_ctx *c, bool fp64, int n_bands, const int *band_ids, v
         proto.out_fp64 = out_fp64 ? 1 : 0;
         proto.gx[kStTimebase] = (B.n_work + tb_entries(v.n_cheb) - 1) / tb_entries(v.n_cheb);
         proto.gx[kStResample] = B.n_work;
-        proto.gx[kStSpectra] = v.wide ? nch * (int)pl.P
+        proto.gx[kStSpectra] = v.lag ? nch * bd.lag.n_sub * bd.lag.P
+                               : v.wide ? nch * (int)pl.P
                                : v.sp ? nch
                                       : (v.reg16 ? (B.n_work + kSpec16Groups - 1) / kSpec16Groups : B.n_work);
-        proto.gx[kStPairs] = (v.sp || v.wide) ? 0 : (int)((pl.n_f + kPairsThreads - 1) / kPairsThreads);
-        proto.gx[kStFinish] = (int)((pl.n_f + kFinishThreads - 1) / kFinishThreads);
+        proto.gx[kStPairs] = (v.sp || v.wide || v.lag) ? 0 : (int)((pl.n_f + kPairsThreads - 1) / kPairsThreads);
+        const int fin = v.lag ? kLagFinThreads * bd.lag.fin_bpt : kFinishThreads;
+        proto.gx[kStFinish] = (int)((pl.n_f + fin - 1) / fin);
         const int64_t per_t[kStages] = {proto.gx[0], proto.gx[1], proto.gx[2], (int64_t)proto.gx[3] * nch, proto.gx[4]};
         int64_t tb = bp.template_batch > 0 ? bp.template_batch : c->opt_template_batch;
         if (tb <= 0) tb = (int64_t)std::max<size_t>(1, budget / std::max<size_t>(y1 + F1 + part1 + coef1, 1));
@@ -1380,7 +1665,8 @@ ccr_status build_plan(ccr_ctx *c, bool fp64, int n_bands, const int *band_ids, v
             q.F = F1 * nb;
             q.part = part1 * nb;
             q.coef = coef1 * nb;
-            q.lds = v.sp ? spectra_pairs_lds(cp.bands.back()) : (v.wide ? spectra_wide_lds(cp.bands.back()) : 0);
+            q.fin_lds = v.lag ? B.lag[fp64 ? 1 : 0].fin_lds : 0;
+            q.lds = v.lag ? lag_lds(bd) : v.sp ? spectra_pairs_lds(cp.bands.back()) : (v.wide ? spectra_wide_lds(cp.bands.back()) : 0);
             for (int st = 0; st < kStages; ++st) q.blk[st] = per_t[st] * nb;
             q.blk[kStResample] = per_t[kStResample] * ((nb + res_t - 1) / res_t);
             pend.push_back(q);
@@ -1422,6 +1708,7 @@ ccr_status build_plan(ccr_ctx *c, bool fp64, int n_bands, const int *band_ids, v
             r.part_bytes += q.part;
             r.coef_bytes += q.coef;
             r.lds = std::max(r.lds, q.lds);
+            r.fin_lds = std::max(r.fin_lds, q.fin_lds);
             r.n_tmpl += q.it.n_tmpl;
             r.n++;
             cp.items.push_back(it);
@@ -1502,7 +1789,10 @@ ccr_status run_rounds(ccr_ctx *c, const CallPlan &cp, size_t r0, size_t r1, bool
             HIP_OK(c, launch_resample_m(db, di, r.n, (int)r.blocks[kStResample], fp64, r.v.DT, r.v.window,
                                         r.v.n_cheb, r.v.far, coef, ws.y, s));
         }
-        if (r.v.sp) {
+        if (r.v.lag) {
+            LaunchTimer lt(c, r.v.timer, s, timing);
+            HIP_OK(c, launch_lag_m(r.v.lk, db, di, r.n, (int)r.blocks[kStSpectra], fp64, r.lds, ws.y, part, s));
+        } else if (r.v.sp) {
             LaunchTimer lt(c, 6, s, timing);
             HIP_OK(c, launch_spectra_pairs_m(db, di, r.n, (int)r.blocks[kStSpectra], r.v.nr, r.v.z4, r.lds, ws.y, part, s));
         } else if (r.v.wide) {
@@ -1522,7 +1812,10 @@ ccr_status run_rounds(ccr_ctx *c, const CallPlan &cp, size_t r0, size_t r1, bool
         }
         {
             LaunchTimer lt(c, 3, s, timing);
-            HIP_OK(c, launch_finish_m(db, di, r.n, (int)r.blocks[kStFinish], part, s));
+            if (r.v.lag)
+                HIP_OK(c, launch_lag_finish_m(db, di, r.n, (int)r.blocks[kStFinish], r.fin_lds, part, s));
+            else
+                HIP_OK(c, launch_finish_m(db, di, r.n, (int)r.blocks[kStFinish], part, s));
         }
     }
     return CCR_OK;
@@ -1580,7 +1873,7 @@ ccr_status choose_params(ccr_ctx *c, ccr_precision prec, int n_bands, const int 
     for (int bi = 0; bi < n_bands; ++bi) {
         const Band &B = *get_band(c, band_ids[bi]);
         max_seg = std::max<int64_t>(max_seg, B.plan.n_seg);
-        const BandDev bd = band_dev(B);
+        const BandDev bd = band_dev(B, fp64);
         const Variant v0 = variant_of(bd, fp64, B.short_series, c->opt_farrow != 0, false);
         const Variant v1 = variant_of(bd, fp64, B.short_series, c->opt_farrow != 0, true);
         both = both || !(v0 == v1);
@@ -1909,6 +2202,8 @@ ccr_status ccr_get_option(ccr_ctx *c, const char *name, int64_t *value) {
     else if (k == "spectra_kernel") *value = c->opt_spectra_kernel;
     else if (k == "round_templates") *value = c->opt_round_templates;
     else if (k == "tuned_round_templates") *value = c->last_tuned_round_templates;
+    else if (k == "grid_ns") *value = c->last_grid_ns;
+    else if (k == "grid_classes") *value = c->last_grid_classes;
     else if (k == "resample_templates") *value = kResTemplates;
     else if (k == "farrow") *value = c->opt_farrow;
     else if (k == "farrow_stage") *value = c->opt_farrow_stage;
@@ -2181,7 +2476,7 @@ ccr_status ccr_compute_rho(ccr_ctx *c, ccr_precision prec, int n_bands, const in
         std::vector<void *> rest_out;
         for (int bi = 0; bi < n_bands; ++bi) {
             Band &B = *get_band(c, band_ids[bi]);
-            const BandDev bd = band_dev(B);
+            const BandDev bd = band_dev(B, fp64);
             const bool plain = bd.weight == CCR_WEIGHT_AVE && !bd.allp && bd.pw == nullptr;
             const int S = plain ? fused_steps(bd, fp64, kMaxLds) : 0;
             if (S > 0) {
@@ -2367,7 +2662,7 @@ ccr_status ccr_resample_series(ccr_ctx *c, ccr_precision prec, int band_id, int6
     HIP_OK(c, y.ensure(bytes));
     HIP_OK(c, cf.ensure((size_t)std::max(B->n_work, 1) * kCheb * sizeof(double)));
     HIP_OK(c, launch_zero(y.p, bytes, s));
-    BandDev bd = band_dev(*B);
+    BandDev bd = band_dev(*B, fp64);
     if (!c->opt_farrow) bd.farrow = nullptr;
     bd.far_stage = (int)c->opt_farrow_stage;
     HIP_OK(c, launch_timebase(bd, B->d_tmpl.as<double>() + (size_t)template_index * kTmplStride, 1, cf.as<double>(), s));
@@ -2399,7 +2694,7 @@ ccr_status ccr_time_base(ccr_ctx *c, int band_id, int64_t template_index, int de
     hipStream_t s = c->stream;
     HIP_OK(c, hipMemcpyAsync(de.p, eta_out, ns * sizeof(double), hipMemcpyHostToDevice, s));
     if (psi_out) HIP_OK(c, hipMemcpyAsync(dp.p, psi_out, ns * sizeof(double), hipMemcpyHostToDevice, s));
-    const BandDev bd = band_dev(*B);
+    const BandDev bd = band_dev(*B, true);
     HIP_OK(c, launch_timebase(bd, B->d_tmpl.as<double>() + (size_t)template_index * kTmplStride, 1, cf.as<double>(), s));
     HIP_OK(c, launch_time_samples(bd, cf.as<double>(), det, (int)k0, (int)n_seg_out, de.as<double>(), dp.as<double>(), s));
     HIP_OK(c, hipMemcpyAsync(eta_out, de.p, ns * sizeof(double), hipMemcpyDeviceToHost, s));
@@ -2435,7 +2730,7 @@ ccr_status ccr_segment_spectra(ccr_ctx *c, ccr_precision prec, int band_id, int6
     HIP_OK(c, F.ensure(fbytes));
     hipStream_t s = c->stream;
     HIP_OK(c, launch_zero(F.p, fbytes, s));
-    BandDev bd = band_dev(*B);
+    BandDev bd = band_dev(*B, fp64);
     if (!c->opt_farrow) bd.farrow = nullptr;
     bd.far_stage = (int)c->opt_farrow_stage;
     const void *ysrc = nullptr;

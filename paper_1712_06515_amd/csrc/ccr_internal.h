@@ -53,6 +53,28 @@ constexpr int cheb_x_off(int nn) {
 constexpr int kChebNodesAll = kCheb + kChebSplit + kChebSplitMin + kChebSplitLow;
 #define CCR_MAX_DET_K 8
 
+// Lag-resolved frequency grid of a band for one precision (ccr_lag.hip): N_G = P ns grid points
+// per cycle/sample, residue class p holding the grid indices p + P (m0 + i), i < span.
+struct LagDev {
+    int on;          // 1 when the band runs on the grid
+    int ns, P, ng;   // transform length, classes, N_G = P ns
+    int nfold;       // rows of ns samples that a segment's N_K samples fold onto
+    int m0, span;    // first transform output kept (mod ns, a multiple of ns / 64), outputs kept per class
+    int wrap;        // 1: every grid point is kept (span = ns), indices taken mod N_G
+    int n_sub;       // problems per chunk: 1, or one per detector (pairs within a detector only) or
+                     // per pair of detectors (pairs across detectors only, with lags)
+    int slot_bytes;  // LDS slot of one transform
+    int taps;        // interpolation taps from the grid to an output bin (1: the bins are grid points)
+    int fin_bpt;     // finishing kernel: bins per thread
+    const float2 *tw32;    // [ng] exp(-2 pi i j / ng)
+    const double2 *tw64;
+    const float2 *step32;  // [P][nfold ns / 64] class input twiddle W^(64 (p + P m0) r)
+    const double2 *step64;
+    const int *g0;         // [n_f] first tap of a bin, relative to grid index P m0
+    const int *frac;       // [n_f] row of wt
+    const double *wt;      // [fractions][taps]
+};
+
 // Everything a kernel needs about a band (device pointers + scalars).
 struct BandDev {
     int Q;              // detectors
@@ -82,6 +104,8 @@ struct BandDev {
     int bins_unique;          // 1 when every output bin has its own FFT index
     const SegWeight *segw;    // [Q][n_seg]
     const float2 *segwf;      // [Q][n_seg] (hat a scale, hat b scale) rounded to FP32
+    const double2 *segwd;     // [Q][n_seg] the same in FP64
+    const uint32_t *seg_bits; // [n_seg] bit X: segment K of detector X takes part in a pair
     const uint8_t *active;    // [Q][n_seg] 1 when the segment takes part in a pair
     const int *work;          // [n_work] det * n_seg + K of active segments
     const int *seg_work;      // [Q][n_seg] position of (det, K) in `work`, -1 if inactive
@@ -124,6 +148,7 @@ struct BandDev {
     // writes two series per detector, y a_r and y b_r (stream s of detector X at X 2 + s), that
     // kernel transforms both
     int ps2;
+    LagDev lag;  // of the call's precision
 };
 
 // One work item of a batched launch: a run of consecutive templates of one band.  A batched
@@ -221,6 +246,26 @@ hipError_t launch_spectra_pairs_m(const BandDev *bands, const WorkItem *items, i
 // with `threads` threads and 2 n_s complex values of LDS.
 hipError_t launch_spectra_m(const BandDev *bands, const WorkItem *items, int n_items, int blocks, bool fp64,
                             bool reg16, int threads, int n_s, const void *y, void *F, hipStream_t stream);
+// Spectra and pair sums on the lag-resolved grid: the kernel variant of a band (transform length,
+// lags kept per step: 0, 1, 2 or 4, wavefronts, pairs across detectors only, per-sample antenna
+// functions), and its finishing kernel (fin_bpt bins a thread).
+constexpr int kLagSegs = 4;           // segments per step
+constexpr int kLagMaxR = 4;           // largest lag of the kernel
+constexpr int kLagFinThreads = 256;
+constexpr int kLagFinBins = 4;        // most bins per thread of the finishing kernel
+struct LagKey {
+    int ns = 0, rm = 0, waves = 0;
+    bool cross = false, ps = false;
+    bool operator==(const LagKey &o) const {
+        return ns == o.ns && rm == o.rm && waves == o.waves && cross == o.cross && ps == o.ps;
+    }
+};
+// Columns a wavefront of the kernel covers (64 U).
+constexpr int lag_cols(int ns) { return ns == 1024 ? 128 : 64; }
+hipError_t launch_lag_m(const LagKey &k, const BandDev *bands, const WorkItem *items, int n_items, int blocks,
+                        bool fp64, size_t lds, const void *y, double *part, hipStream_t stream);
+hipError_t launch_lag_finish_m(const BandDev *bands, const WorkItem *items, int n_items, int blocks, size_t lds,
+                               const double *part, hipStream_t stream);
 hipError_t launch_pairs_m(const BandDev *bands, const WorkItem *items, int n_items, int blocks, bool fp64,
                           const void *F, double *part, hipStream_t stream);
 hipError_t launch_finish_m(const BandDev *bands, const WorkItem *items, int n_items, int blocks, const double *part,
