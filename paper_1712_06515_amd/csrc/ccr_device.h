@@ -163,6 +163,9 @@ __device__ __forceinline__ BandDev global_view(const BandDev &b, const void *bas
     g.farrow = as_global(b.farrow, base);
     g.cls_m0 = as_global(b.cls_m0, base);
     if (b.pw) g.pw = as_global(b.pw, base);
+    if (b.pwf) g.pwf = as_global(b.pwf, base);
+    g.segwd = as_global(b.segwd, base);
+    g.seg_bits = as_global(b.seg_bits, base);
     if (b.lag.on) {
         g.lag.tw32 = as_global(b.lag.tw32, base);
         g.lag.tw64 = as_global(b.lag.tw64, base);

@@ -1421,6 +1421,7 @@ struct Variant {
     bool wallp = false;  // wide: every ordered pair (stream-sum partials)
     bool wps = false;    // wide: two spectra streams per segment (per-sample antenna functions)
     int wns = 0;         // wide: segment FFT length (256, 512 or 1024)
+    bool fold = false;   // every ordered pair: folded series
     bool lag = false;    // spectra + pair sum on the lag-resolved grid
     LagKey lk;
     int timer = 0;       // kernel-time slot of the spectra stage (not part of the kernel choice)
@@ -1431,7 +1432,7 @@ struct Variant {
         return sp == o.sp && reg16 == o.reg16 && z4 == o.z4 && ss == o.ss && far == o.far && wide == o.wide &&
                DT == o.DT && window == o.window && n_s == o.n_s && nr == o.nr && n_cheb == o.n_cheb &&
                wcols == o.wcols && wqm == o.wqm && wts == o.wts && wwv == o.wwv && wallp == o.wallp && wns == o.wns && wps == o.wps &&
-               lag == o.lag && lk == o.lk;
+               lag == o.lag && lk == o.lk && fold == o.fold;
     }
 };
 
@@ -1449,7 +1450,7 @@ struct Round {
     int i0 = 0, n = 0;  // items [i0, i0 + n) of the call's item table
     int64_t n_tmpl = 0;  // templates of those items
     Variant v;
-    size_t lds = 0;     // dynamic LDS of the spectra + pair-sum kernel
+    size_t lds = 0;     // dynamic LDS of the spectra + pair-sum kernel (folded series: n_s)
     size_t fin_lds = 0;  // and of the grid's finishing kernel
     int64_t blocks[kStages] = {0, 0, 0, 0, 0};
     size_t y_bytes = 0, F_bytes = 0, part_bytes = 0, coef_bytes = 0;
@@ -1494,7 +1495,7 @@ bool lag_fits(const BandDev &bd, LagKey &k) {
 }
 
 Variant variant_of(const BandDev &bd, bool fp64, bool short_series, bool farrow, bool prefer_wide,
-                   bool streams = true) {
+                   bool streams = true, bool fold = true) {
     Variant v;
     v.ss = short_series;
     v.far = farrow && !fp64 && bd.farrow != nullptr;
@@ -1517,13 +1518,14 @@ Variant variant_of(const BandDev &bd, bool fp64, bool short_series, bool farrow,
         v.lag = true;
         v.sp = false;
     }
-    v.wide = !v.sp && !v.lag && wide_ok;
+    v.fold = fold && bd.allp && bd.n_s >= kFoldThreads;
+    v.wide = !v.sp && !v.lag && !v.fold && wide_ok;
     v.wallp = v.wide && bd.allp;
     v.wps = v.wide && bd.pw != nullptr;
     v.DT = bd.D == 8 ? 8 : 0;
     v.window = bd.window;
     v.n_cheb = fp64 ? kCheb : bd.cheb_split;
-    if (v.lag) {
+    if (v.lag || v.fold) {
         // one kernel per key; the rest of the variant is the time base's and the resampler's
     } else if (v.wide) {
         v.wns = bd.n_s;
@@ -1548,8 +1550,9 @@ int64_t stage_max_blocks(const Variant &v, int st) {
     int threads = 64;
     if (st == kStTimebase) threads = tb_entries(v.n_cheb) * v.n_cheb;
     else if (st == kStResample) threads = v.far ? 256 : 64;
+    else if (st == kStSpectra && v.fold) threads = kFoldThreads;
     else if (st == kStSpectra) threads = v.lag ? 64 * v.lk.waves : v.sp ? 64 : (v.wide ? 64 * v.wwv : (v.reg16 ? 128 : spectra_threads(v.n_s)));
-    else if (st == kStPairs) threads = kPairsThreads;
+    else if (st == kStPairs) threads = v.fold ? kFoldThreads : kPairsThreads;
     else if (st == kStFinish) threads = kFinishThreads;
     return std::min<int64_t>(kMaxBlocks, (((int64_t)1 << 32) - 1) / threads);
 }
@@ -1604,7 +1607,18 @@ ccr_status build_plan(ccr_ctx *c, bool fp64, int n_bands, const int *band_ids, v
         BandDev bd = band_dev(B, fp64);
         bd.far_stage = (int)c->opt_farrow_stage;
         cp.bands.push_back(bd);
-        const Variant v = variant_of(bd, fp64, B.short_series, c->opt_farrow != 0, bp.spectra != 0, !bp.no_streams);
+        // folded series: the samples m + j N_FFT of one output sample in runs of fold_kc values of j,
+        // so that a template gives at least 128 workgroups
+        const int64_t fold_j = (pl.n_seg * pl.n_k + pl.n_fft - 1) / pl.n_fft;
+        const int64_t fold_kc = std::max<int64_t>(1, fold_j * pl.n_fft / (128 * kFoldThreads));
+        const int64_t fold_nch = (fold_j + fold_kc - 1) / fold_kc;
+        const size_t fold1 = (size_t)fold_nch * 2 * pl.n_fft * sizeof(double2);
+        const size_t fold_part = (size_t)pl.n_f * 4 * sizeof(double);
+        const size_t coef1 = (size_t)std::max(B.n_work, 1) * kCheb * sizeof(double);
+        const size_t ser1 = (size_t)B.Q * pl.n_seg * pl.n_k * cs;
+        // (a fixed workspace that cannot hold one template's folded series keeps the other kernels)
+        const bool fold = budget_override == 0 || arena_bytes_of(coef1, ser1, fold1, fold_part) <= budget;
+        const Variant v = variant_of(bd, fp64, B.short_series, c->opt_farrow != 0, bp.spectra != 0, !bp.no_streams, fold);
         if (v.wps) cp.bands.back().ps2 = 1;
         if (bi == 0) {
             c->last_grid_ns = v.lag ? bd.lag.ns : 0;
@@ -1614,33 +1628,33 @@ ccr_status build_plan(ccr_ctx *c, bool fp64, int n_bands, const int *band_ids, v
         if (std::find(variants.begin(), variants.end(), v) == variants.end()) variants.push_back(v);
         int64_t kc = bp.k_chunk > 0 ? bp.k_chunk : std::min<int64_t>(pl.n_seg, 256);
         kc = std::max<int64_t>(1, std::min<int64_t>(kc, pl.n_seg));
-        const size_t y1 = (size_t)B.Q * pl.n_seg * pl.n_k * cs * (v.wps ? 2 : 1);
+        const size_t y1 = ser1 * (v.wps ? 2 : 1);
         // two spectra streams per segment with per-sample weights; four partials per bin (the
         // stream sums) for every ordered pair
-        const size_t F1 = (v.sp || v.wide || v.lag) ? 0 : (size_t)B.Q * pl.n_seg * pl.n_f * cs * (bd.pw ? 2 : 1);
-        const size_t coef1 = (size_t)std::max(B.n_work, 1) * kCheb * sizeof(double);
+        const size_t F1 = v.fold ? fold1 : (v.sp || v.wide || v.lag) ? 0 : (size_t)B.Q * pl.n_seg * pl.n_f * cs * (bd.pw ? 2 : 1);
         const size_t lag1 = (size_t)bd.lag.n_sub * (2 * bd.R + 1) * bd.lag.P * bd.lag.span * sizeof(double);
         // a fixed workspace that one template's chunk partials would overflow: longer chunks
         while (v.lag && budget_override > 0 && kc < pl.n_seg &&
                arena_bytes_of(coef1, y1, F1, (size_t)((pl.n_seg + kc - 1) / kc) * lag1) > budget)
             kc = std::min<int64_t>(2 * kc, pl.n_seg);
+        if (v.fold) kc = pl.n_seg;  // one partial a bin
         const int nch = (int)((pl.n_seg + kc - 1) / kc);
         const size_t part1 = v.lag ? (size_t)nch * lag1
                                    : (size_t)nch * pl.n_f * sizeof(double) * (bd.allp ? 4 : 1);
         WorkItem proto;
         std::memset(&proto, 0, sizeof proto);
         proto.band = bi;
-        proto.k_chunk = (int)kc;
+        proto.k_chunk = v.fold ? (int)fold_kc : (int)kc;
         proto.n_chunks = nch;
         proto.factor = pl.norm > 0.0 ? std::sqrt(2.0) / pl.norm : 0.0;
         proto.out_fp64 = out_fp64 ? 1 : 0;
         proto.gx[kStTimebase] = (B.n_work + tb_entries(v.n_cheb) - 1) / tb_entries(v.n_cheb);
         proto.gx[kStResample] = B.n_work;
-        proto.gx[kStSpectra] = v.lag ? nch * bd.lag.n_sub * bd.lag.P
+        proto.gx[kStSpectra] = v.fold ? (int)(fold_nch * (pl.n_fft / kFoldThreads)) : v.lag ? nch * bd.lag.n_sub * bd.lag.P
                                : v.wide ? nch * (int)pl.P
                                : v.sp ? nch
                                       : (v.reg16 ? (B.n_work + kSpec16Groups - 1) / kSpec16Groups : B.n_work);
-        proto.gx[kStPairs] = (v.sp || v.wide || v.lag) ? 0 : (int)((pl.n_f + kPairsThreads - 1) / kPairsThreads);
+        proto.gx[kStPairs] = v.fold ? 2 * (int)pl.P : (v.sp || v.wide || v.lag) ? 0 : (int)((pl.n_f + kPairsThreads - 1) / kPairsThreads);
         const int fin = v.lag ? kLagFinThreads * bd.lag.fin_bpt : kFinishThreads;
         proto.gx[kStFinish] = (int)((pl.n_f + fin - 1) / fin);
         const int64_t per_t[kStages] = {proto.gx[0], proto.gx[1], proto.gx[2], (int64_t)proto.gx[3] * nch, proto.gx[4]};
@@ -1666,7 +1680,7 @@ ccr_status build_plan(ccr_ctx *c, bool fp64, int n_bands, const int *band_ids, v
             q.part = part1 * nb;
             q.coef = coef1 * nb;
             q.fin_lds = v.lag ? B.lag[fp64 ? 1 : 0].fin_lds : 0;
-            q.lds = v.lag ? lag_lds(bd) : v.sp ? spectra_pairs_lds(cp.bands.back()) : (v.wide ? spectra_wide_lds(cp.bands.back()) : 0);
+            q.lds = v.fold ? (size_t)pl.n_s : v.lag ? lag_lds(bd) : v.sp ? spectra_pairs_lds(cp.bands.back()) : (v.wide ? spectra_wide_lds(cp.bands.back()) : 0);
             for (int st = 0; st < kStages; ++st) q.blk[st] = per_t[st] * nb;
             q.blk[kStResample] = per_t[kStResample] * ((nb + res_t - 1) / res_t);
             pend.push_back(q);
@@ -1789,7 +1803,11 @@ ccr_status run_rounds(ccr_ctx *c, const CallPlan &cp, size_t r0, size_t r1, bool
             HIP_OK(c, launch_resample_m(db, di, r.n, (int)r.blocks[kStResample], fp64, r.v.DT, r.v.window,
                                         r.v.n_cheb, r.v.far, coef, ws.y, s));
         }
-        if (r.v.lag) {
+        if (r.v.fold) {
+            LaunchTimer lt(c, 7, s, timing);
+            HIP_OK(c, launch_fold_m(db, di, r.n, (int)r.blocks[kStSpectra], (int)r.blocks[kStPairs], fp64, (int)r.lds,
+                                    ws.y, ws.F, part, s));
+        } else if (r.v.lag) {
             LaunchTimer lt(c, r.v.timer, s, timing);
             HIP_OK(c, launch_lag_m(r.v.lk, db, di, r.n, (int)r.blocks[kStSpectra], fp64, r.lds, ws.y, part, s));
         } else if (r.v.sp) {

@@ -246,6 +246,12 @@ hipError_t launch_spectra_pairs_m(const BandDev *bands, const WorkItem *items, i
 // with `threads` threads and 2 n_s complex values of LDS.
 hipError_t launch_spectra_m(const BandDev *bands, const WorkItem *items, int n_items, int blocks, bool fp64,
                             bool reg16, int threads, int n_s, const void *y, void *F, hipStream_t stream);
+// Every ordered pair: the weighted series folded onto N_FFT samples (`blocks`, spectra stage; n_s >=
+// 256) and transformed at the output bins (`dft_blocks`, pair stage); `n_s`: the largest of the
+// round's bands.
+constexpr int kFoldThreads = 256;
+hipError_t launch_fold_m(const BandDev *bands, const WorkItem *items, int n_items, int blocks, int dft_blocks,
+                         bool fp64, int n_s, const void *y, void *F, double *part, hipStream_t stream);
 // Spectra and pair sums on the lag-resolved grid: the kernel variant of a band (transform length,
 // lags kept per step: 0, 1, 2 or 4, wavefronts, pairs across detectors only, per-sample antenna
 // functions), and its finishing kernel (fin_bpt bins a thread).

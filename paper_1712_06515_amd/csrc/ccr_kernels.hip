@@ -2490,6 +2490,110 @@ k_finish_m(const BandDev *__restrict__ bands, const WorkItem *__restrict__ items
                 it.out_fp64, l % gx, l / gx, B.allp, B.weight);
 }
 
+// ------------------------------------------------------------------ every ordered pair: folded series
+
+// With every ordered pair, autos included, the pair sum is |F_a|^2 + |F_b|^2 of the whole weighted
+// series, F_a(kbar) = sum_r hat a_r y_r exp(-2 pi i kbar r / N_FFT), r over all segments and
+// detectors.  The kernel's phase has period N_FFT in r, so the series is first folded onto N_FFT
+// samples, x_m = sum_j hat a_r y_r at r = m + j N_FFT, and transformed once per template instead
+// of N_FFT / n_s transforms of n_s points per segment.
+//
+// k_fold: one thread per (template, m, run of it.k_chunk values of j); both streams, every
+// detector, FP64 sums.  Bound by the read of the resampled series (one pass).  Absent segments
+// are not read (their samples are not written).
+template <typename T>
+__global__ void __launch_bounds__(kFoldThreads)
+k_fold(const BandDev *__restrict__ bands, const WorkItem *__restrict__ items, int n_items,
+       const c2<T> *__restrict__ y_, c2<T> *__restrict__ F) {
+    const WorkItem &it = items[find_item(items, n_items, kStSpectra, blockIdx.x)];
+    const BandDev B = global_view(bands[it.band], bands);
+    const int l = blockIdx.x - it.first[kStSpectra], gx = it.gx[kStSpectra];
+    const int N = B.n_fft, nb = N / kFoldThreads, nch = gx / nb, nk = B.n_k;
+    const int t = l / gx, c = (l % gx) / nb, m = (l % nb) * kFoldThreads + threadIdx.x;
+    const int64_t nr = (int64_t)B.n_seg * nk;
+    const int64_t r0 = m + (int64_t)c * it.k_chunk * N, r1 = min(nr, r0 + (int64_t)it.k_chunk * N);
+    const int dK = N / nk, ds = N - dK * nk;  // a step of N samples in segments and samples
+    double2 xa = make_double2(0.0, 0.0), xb = xa;
+    for (int X = 0; X < B.Q; ++X) {
+        const c2<T> *y = y_ + it.y_off + ((size_t)t * B.Q + X) * nr;
+        int K = (int)(r0 / nk), s = (int)(r0 - (int64_t)K * nk);
+#pragma unroll 4
+        for (int64_t r = r0; r < r1; r += N) {
+            if ((B.seg_bits[K] >> X) & 1u) {
+                const c2<T> v = y[r];
+                double wa, wb;
+                if (B.pw) {
+                    if constexpr (sizeof(T) == 8) {
+                        const double2 w = B.pw[(size_t)X * nr + r];
+                        wa = w.x;
+                        wb = w.y;
+                    } else {
+                        const float2 w = B.pwf[(size_t)X * nr + r];
+                        wa = w.x;
+                        wb = w.y;
+                    }
+                } else {
+                    const double2 w = B.segwd[X * B.n_seg + K];
+                    wa = w.x;
+                    wb = w.y;
+                }
+                xa.x = fma(wa, (double)v.x, xa.x);
+                xa.y = fma(wa, (double)v.y, xa.y);
+                xb.x = fma(wb, (double)v.x, xb.x);
+                xb.y = fma(wb, (double)v.y, xb.y);
+            }
+            K += dK;
+            s += ds;
+            if (s >= nk) {
+                s -= nk;
+                ++K;
+            }
+        }
+    }
+    double2 *o = reinterpret_cast<double2 *>(F + it.F_off) + ((size_t)t * nch + c) * 2 * N;
+    o[m] = xa;
+    o[N + m] = xb;
+}
+
+// k_fold_dft: the folded series at the bins of residue class p = kbar mod P (N_FFT = P n_s), one
+// workgroup per (template, class, stream): the P rows of n_s samples combine with W_P^(p j), the
+// class's twiddle W_N^(p s) and an n_s-point FP64 FFT in LDS give its bins.  Writes one complex
+// of the four partials a bin that the finishing kernel combines.
+__global__ void __launch_bounds__(kFoldThreads)
+k_fold_dft(const BandDev *__restrict__ bands, const WorkItem *__restrict__ items, int n_items,
+           const double2 *__restrict__ F_, size_t cs, double *__restrict__ part) {
+    extern __shared__ __align__(16) unsigned char smem[];
+    const WorkItem &it = items[find_item(items, n_items, kStPairs, blockIdx.x)];
+    const BandDev B = global_view(bands[it.band], bands);
+    const int l = blockIdx.x - it.first[kStPairs], gx = it.gx[kStPairs];
+    const int N = B.n_fft, ns = B.n_s, P = B.P, nch = it.gx[kStSpectra] / (N / kFoldThreads);
+    const int t = l / gx, p = (l % gx) >> 1, st = l & 1;
+    const double2 *x = reinterpret_cast<const double2 *>(reinterpret_cast<const char *>(F_) + it.F_off * cs) +
+                       ((size_t)t * nch * 2 + st) * N;
+    double2 *a = reinterpret_cast<double2 *>(smem), *b = a + ns;
+    for (int s = threadIdx.x; s < ns; s += kFoldThreads) {
+        double2 z = make_double2(0.0, 0.0);
+        int e = 0;  // p j mod P
+        for (int j = 0; j < P; ++j) {
+            double2 v = make_double2(0.0, 0.0);
+            for (int c = 0; c < nch; ++c) v = cadd<double>(v, x[(size_t)c * 2 * N + (size_t)j * ns + s]);
+            z = cadd<double>(z, cmul<double>(v, B.tw64[(size_t)e * ns]));
+            e += p;
+            if (e >= P) e -= P;
+        }
+        a[s] = cmul<double>(z, B.tw64[(size_t)p * s]);
+    }
+    __syncthreads();
+    const double2 *res = stockham<double>(a, b, ns, B.tw64, N, threadIdx.x, kFoldThreads);
+    for (int c = B.class_start[p] + (int)threadIdx.x; c < B.class_start[p + 1]; c += kFoldThreads) {
+        const int i = B.col_bin[c];
+        const double2 f = res[B.bin_m[i]];
+        double *o = part + it.part_off + ((size_t)t * B.n_f + i) * 4 + 2 * st;
+        o[0] = f.x;
+        o[1] = f.y;
+    }
+}
+
 }  // namespace
 
 hipError_t launch_timebase(const BandDev &B, const double *d_tmpl, int n_tmpl, double *coef,
@@ -2831,6 +2935,20 @@ hipError_t launch_pairs_m(const BandDev *bands, const WorkItem *items, int n_ite
     else
         hipLaunchKernelGGL(k_pairs_m<float>, dim3(blocks), dim3(kPairsThreads), 0, stream, bands, items, n_items,
                            (const float2 *)F, part);
+    return hipGetLastError();
+}
+
+hipError_t launch_fold_m(const BandDev *bands, const WorkItem *items, int n_items, int blocks, int dft_blocks,
+                         bool fp64, int n_s, const void *y, void *F, double *part, hipStream_t stream) {
+    if (blocks == 0) return hipSuccess;
+    if (fp64)
+        hipLaunchKernelGGL(k_fold<double>, dim3(blocks), dim3(kFoldThreads), 0, stream, bands, items, n_items,
+                           (const double2 *)y, (double2 *)F);
+    else
+        hipLaunchKernelGGL(k_fold<float>, dim3(blocks), dim3(kFoldThreads), 0, stream, bands, items, n_items,
+                           (const float2 *)y, (float2 *)F);
+    hipLaunchKernelGGL(k_fold_dft, dim3(dft_blocks), dim3(kFoldThreads), 2 * (size_t)n_s * sizeof(double2), stream,
+                       bands, items, n_items, (const double2 *)F, fp64 ? sizeof(double2) : sizeof(float2), part);
     return hipGetLastError();
 }
 

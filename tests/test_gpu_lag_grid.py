@@ -1,4 +1,5 @@
-"""Spectra and pair sums on the lag-resolved frequency grid against the oracle.
+"""Spectra and pair sums on the lag-resolved frequency grid, and every ordered pair from the folded
+series, against the oracle.
 
 The kernel's transform length, number of classes, folded rows, kept columns and interpolation
 taps follow from N_K, the band and the lag, so the cases sit at the edges of those choices: N_K
@@ -48,6 +49,12 @@ CASES = {
     "ps_cross_q3_circ": (3, 2, 1, 1, True, 300, 400.0, 0.1, 15, 5, 0.2),
     "ps_same_q2_lag4": (2, 4, 2, 0, True, 700, 900.0, 0.2, 17, 8, 0.2),
     "ps_lag0": (2, 0, 1, 1, True, 1100, 1500.0, 0.2, 10, 3, 0.2),
+    # every ordered pair: series folded onto N_FFT samples many times, less than once, on 2048-point
+    # classes, with both weightings of several detectors
+    "all_fold_many": (2, 0, 4, 0, False, 0, 400.0, 0.1, 60, 256, 0.2),
+    "all_fold_less_than_once": (2, 4, 4, 0, False, 0, 400.0, 0.1, 3, 256, 0.0),
+    "all_nk1100_circ": (2, 1, 4, 1, False, 1100, 1500.0, 0.2, 9, 256, 0.2),
+    "all_ps_q3_circ": (3, 1, 4, 1, True, 300, 400.0, 0.1, 15, 256, 0.2),
     "mu_repeated_bins": (2, 1, 3, 0, False, 200, 400.0, 0.1, 15, 6, 0.2),
 }
 
@@ -79,5 +86,5 @@ def test_lag_grid(ccr, case):
             kt = ctx.kernel_times(reset=True)
             e = err(r)
             print(f"  error {e:.2e}, max|rho| {np.abs(ref).max():.2f}", flush=True)
-            assert kt["spectra"][1] == 0 and kt["pairs"][1] == 0, kt  # the grid, not the general path
+            assert kt["spectra"][1] == 0 and kt["pairs"][1] == 0, kt  # not the general path
             assert e < (1e-10 if prec == ccr.PREC_FP64 else 1e-4)
