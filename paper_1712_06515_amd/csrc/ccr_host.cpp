@@ -331,7 +331,10 @@ bool lag_plan(const Plan &pl, const ccr_band &b, int Q, bool streams, bool fp64,
     if (b.pairs == CCR_PAIRS_ALL || R > kLagMaxR || pl.n_s < 256) return false;
     const int64_t k0 = bin_index(pl, 0), k1 = bin_index(pl, pl.n_f - 1);
     double best = HUGE_VAL;
-    for (int ns = 256; ns <= (fp64 ? 512 : 1024); ns *= 2) {
+    // 1024 points: split precision, per-segment weights, pairs within the detectors too (the other
+    // forms keep twice the streams, which at 1024 points does not fit the registers)
+    const bool big = !fp64 && !streams && (same || R == 0);
+    for (int ns = 256; ns <= (big ? 1024 : 512); ns *= 2) {
         const int nf = (int)((pl.n_k + ns - 1) / ns);
         if (nf > 4) continue;
         const int64_t pmin = std::max<int64_t>(1, (int64_t)std::ceil(kLagSigmaMin * (double)(2 * pl.n_k - 1) / ns));
@@ -355,7 +358,8 @@ bool lag_plan(const Plan &pl, const ccr_band &b, int Q, bool streams, bool fp64,
             }
             const int exch = (ns + 64) * cs / 2;  // ns + ns / V = ns + 64 values of one component
             const int slot = (int)std::max<int64_t>(exch, (span + 63) / 64 * 64 * cs);
-            if ((size_t)kLagSegs * lag_dets(Q, R, b.pairs) * (streams ? 2 : 1) * slot > kLagMaxLds) continue;
+            if ((size_t)kLagSegs * lag_dets(Q, R, b.pairs) * (streams ? 2 : 1) * slot + lag_tw_lds(ns, fp64) > kLagMaxLds)
+                continue;
             const double fft = ns == 1024 ? 570.0 : (ns == 512 ? 255.0 : 115.0);
             const double cost = (double)P * (Q * (fft + 4.0 * (nf - 1) * v) +
                                              (double)((span + 63) / 64) * (8.0 * R + 4.0 * Q + 12.0));
@@ -441,12 +445,9 @@ void lag_tables(const Plan &pl, bool fp64, LagGrid &L, LagTables &t) {
         t.g0[(size_t)i] = (int)(rel0 + (g - (w > 1 ? w / 2 - 1 : 0) - first));
         t.frac[(size_t)i] = (int)((num - g * nfft) / gc);
     }
-    // bins per thread: all of kLagFinBins where that leaves a template several workgroups
-    d.fin_bpt = pl.n_f > 4 * kLagFinThreads ? kLagFinBins : 1;
     int64_t cols = 0;
-    const int64_t nb = (int64_t)kLagFinThreads * d.fin_bpt;
-    for (int64_t b0 = 0; b0 < pl.n_f; b0 += nb) {
-        const int64_t b1 = std::min<int64_t>(pl.n_f, b0 + nb);
+    for (int64_t b0 = 0; b0 < pl.n_f; b0 += kLagFinThreads) {
+        const int64_t b1 = std::min<int64_t>(pl.n_f, b0 + kLagFinThreads);
         cols = std::max<int64_t>(cols, t.g0[(size_t)b1 - 1] + w - t.g0[(size_t)b0]);
     }
     L.fin_lds = (size_t)cols * sizeof(double2);
@@ -957,7 +958,7 @@ ccr_status prepare(ccr_ctx *c, Band &B) {
                 if (seg_work[(size_t)X * M + K] >= 0) bits[(size_t)K] |= 1u << X;
         B.off_segwd = put(segwd);
         B.off_seg_bits = put(bits);
-        size_t off[2][5] = {};
+        size_t off[2][7] = {};
         for (int f = 0; f < 2; ++f) {
             LagGrid &L = B.lag[f];
             if (!lag_plan(pl, B.p, Q, per_sample, f == 1, L.d)) continue;
@@ -972,16 +973,47 @@ ccr_status prepare(ccr_ctx *c, Band &B) {
             off[f][2] = put(t.g0);
             off[f][3] = put(t.frac);
             off[f][4] = put(t.wt);
+            // per-detector weights and per-problem activity with a step of zeros at either end
+            const size_t row = (size_t)M + 2 * kLagSegs;
+            std::vector<double2> wd((size_t)Q * row, make_double2(0.0, 0.0));
+            for (int X = 0; X < Q; ++X)
+                for (int64_t K = 0; K < M; ++K) wd[X * row + kLagSegs + K] = segwd[(size_t)X * M + K];
+            if (f == 1) {
+                off[f][5] = put(wd);
+            } else {
+                std::vector<float2> wf(wd.size());
+                for (size_t e = 0; e < wd.size(); ++e) wf[e] = make_float2((float)wd[e].x, (float)wd[e].y);
+                off[f][5] = put(wf);
+            }
+            const int nd = lag_dets(Q, R, B.p.pairs);
+            std::vector<uint32_t> sb((size_t)L.d.n_sub * row, 0);
+            for (int sub = 0, X = 0, Y = 1; sub < L.d.n_sub; ++sub) {
+                for (int64_t K = -kLagSegs; K < M; ++K)
+                    for (int tt = 0; tt < kLagSegs; ++tt)
+                        for (int i = 0; i < nd; ++i) {
+                            const int det = nd == 1 ? (L.d.n_sub > 1 ? sub : 0) : (nd == 2 ? (i ? Y : X) : i);
+                            if (K + tt >= 0 && K + tt < M && (bits[(size_t)(K + tt)] >> det & 1u))
+                                sb[sub * row + kLagSegs + K] |= 1u << (tt * nd + i);
+                        }
+                if (++Y == Q) {
+                    ++X;
+                    Y = X + 1;
+                }
+            }
+            off[f][6] = put(sb);
         }
         if ((st = upload(c, B.d_lag, pack))) return st;
         const char *base = B.d_lag.as<char>();
         for (int f = 0; f < 2; ++f) {
             LagDev &d = B.lag[f].d;
             if (!d.on) continue;
+            d.step_bits = reinterpret_cast<const uint32_t *>(base + off[f][6]);
             if (f == 1) {
+                d.segwd = reinterpret_cast<const double2 *>(base + off[f][5]);
                 d.tw64 = reinterpret_cast<const double2 *>(base + off[f][0]);
                 d.step64 = reinterpret_cast<const double2 *>(base + off[f][1]);
             } else {
+                d.segwf = reinterpret_cast<const float2 *>(base + off[f][5]);
                 d.tw32 = reinterpret_cast<const float2 *>(base + off[f][0]);
                 d.step32 = reinterpret_cast<const float2 *>(base + off[f][1]);
             }
@@ -1475,9 +1507,10 @@ struct BatchParams {
     int spectra = 0;  // 1: the wide spectra + pair-sum kernel wherever it applies, 0: the 256-point one first
 };
 
-// LDS of a workgroup of the grid's kernel: a step's transforms.
-size_t lag_lds(const BandDev &bd) {
-    return (size_t)kLagSegs * lag_dets(bd.Q, bd.R, bd.pairs) * (bd.pw ? 2 : 1) * bd.lag.slot_bytes;
+// LDS of a workgroup of the grid's kernel: the twiddles and a step's transforms.
+size_t lag_lds(const BandDev &bd, bool fp64) {
+    return (size_t)kLagSegs * lag_dets(bd.Q, bd.R, bd.pairs) * (bd.pw ? 2 : 1) * bd.lag.slot_bytes +
+           lag_tw_lds(bd.lag.ns, fp64);
 }
 
 // Whether a band runs on the lag-resolved grid, and the kernel variant that takes it.
@@ -1487,11 +1520,11 @@ bool lag_fits(const BandDev &bd, LagKey &k) {
     k.ns = bd.lag.ns;
     k.cross = bd.pairs == CCR_PAIRS_CROSS && bd.R > 0;
     k.ps = bd.pw != nullptr;
-    k.rm = bd.R == 0 ? 0 : (k.cross || k.ps || bd.R > 2 ? 4 : bd.R);
-    const int per = lag_cols(k.ns);
+    k.circ = bd.weight == CCR_WEIGHT_CIRC && !k.cross && !k.ps;
+    k.rm = bd.R == 0 ? 0 : (k.cross || k.ps || bd.R > 2 || (k.circ && bd.R > 1) ? 4 : bd.R);
     k.waves = 2;
-    while (k.waves * per < bd.lag.span) k.waves *= 2;
-    return k.waves <= 8;
+    while (64 * k.waves < bd.lag.span) k.waves *= 2;
+    return true;
 }
 
 Variant variant_of(const BandDev &bd, bool fp64, bool short_series, bool farrow, bool prefer_wide,
@@ -1543,6 +1576,21 @@ Variant variant_of(const BandDev &bd, bool fp64, bool short_series, bool farrow,
     return v;
 }
 
+// Segments per chunk when the caller and the tuner leave it open: 256, or fewer (not below 16) so
+// that a call of few templates or short series still gives the GPU about 4096 workgroups (4-8
+// wavefronts each on the grid; 8192 of the 256-point kernel's single wavefronts).  Shorter chunks
+// repeat more halo segments (R per chunk), so full calls keep 256.  In FP64 the rule looks at the
+// band alone, never at the template count, which keeps results bitwise independent of how templates
+// are split over calls: 64 chunks a band.
+int64_t default_chunk(const Band &B, const Variant &v, const BandDev &bd, bool fp64) {
+    const int64_t M = B.plan.n_seg;
+    int64_t chunks = 0;
+    if (v.lag) chunks = fp64 ? 64 : 4096 / ((int64_t)B.n_tmpl * bd.lag.P * bd.lag.n_sub);
+    else if (v.sp) chunks = 8192 / B.n_tmpl;
+    const int64_t kc = chunks > 0 ? std::max<int64_t>(16, M / chunks) : 256;
+    return std::min<int64_t>({kc, (int64_t)256, M});
+}
+
 constexpr int64_t kMaxBlocks = ((int64_t)1 << 31) - 1;
 
 // Largest grid of a stage's kernel: at most 2^31 - 1 workgroups and 2^32 - 1 work-items.
@@ -1552,7 +1600,7 @@ int64_t stage_max_blocks(const Variant &v, int st) {
     else if (st == kStResample) threads = v.far ? 256 : 64;
     else if (st == kStSpectra && v.fold) threads = kFoldThreads;
     else if (st == kStSpectra) threads = v.lag ? 64 * v.lk.waves : v.sp ? 64 : (v.wide ? 64 * v.wwv : (v.reg16 ? 128 : spectra_threads(v.n_s)));
-    else if (st == kStPairs) threads = v.fold ? kFoldThreads : kPairsThreads;
+    else if (st == kStPairs) threads = v.fold ? kFoldThreads : (v.lag ? kLagFinThreads : kPairsThreads);
     else if (st == kStFinish) threads = kFinishThreads;
     return std::min<int64_t>(kMaxBlocks, (((int64_t)1 << 32) - 1) / threads);
 }
@@ -1626,7 +1674,7 @@ ccr_status build_plan(ccr_ctx *c, bool fp64, int n_bands, const int *band_ids, v
         }
         const int res_t = v.far ? kFarTemplates : kResTemplates;  // templates per resampler workgroup
         if (std::find(variants.begin(), variants.end(), v) == variants.end()) variants.push_back(v);
-        int64_t kc = bp.k_chunk > 0 ? bp.k_chunk : std::min<int64_t>(pl.n_seg, 256);
+        int64_t kc = bp.k_chunk > 0 ? bp.k_chunk : default_chunk(B, v, bd, fp64);
         kc = std::max<int64_t>(1, std::min<int64_t>(kc, pl.n_seg));
         const size_t y1 = ser1 * (v.wps ? 2 : 1);
         // two spectra streams per segment with per-sample weights; four partials per bin (the
@@ -1654,10 +1702,12 @@ ccr_status build_plan(ccr_ctx *c, bool fp64, int n_bands, const int *band_ids, v
                                : v.wide ? nch * (int)pl.P
                                : v.sp ? nch
                                       : (v.reg16 ? (B.n_work + kSpec16Groups - 1) / kSpec16Groups : B.n_work);
-        proto.gx[kStPairs] = v.fold ? 2 * (int)pl.P : (v.sp || v.wide || v.lag) ? 0 : (int)((pl.n_f + kPairsThreads - 1) / kPairsThreads);
-        const int fin = v.lag ? kLagFinThreads * bd.lag.fin_bpt : kFinishThreads;
+        proto.gx[kStPairs] = v.fold  ? 2 * (int)pl.P
+                             : v.lag ? (int)((lag1 / sizeof(double) / bd.lag.n_sub + kLagFinThreads - 1) / kLagFinThreads)
+                             : (v.sp || v.wide) ? 0 : (int)((pl.n_f + kPairsThreads - 1) / kPairsThreads);
+        const int fin = v.lag ? kLagFinThreads : kFinishThreads;
         proto.gx[kStFinish] = (int)((pl.n_f + fin - 1) / fin);
-        const int64_t per_t[kStages] = {proto.gx[0], proto.gx[1], proto.gx[2], (int64_t)proto.gx[3] * nch, proto.gx[4]};
+        const int64_t per_t[kStages] = {proto.gx[0], proto.gx[1], proto.gx[2], (int64_t)proto.gx[3] * (v.lag ? 1 : nch), proto.gx[4]};
         int64_t tb = bp.template_batch > 0 ? bp.template_batch : c->opt_template_batch;
         if (tb <= 0) tb = (int64_t)std::max<size_t>(1, budget / std::max<size_t>(y1 + F1 + part1 + coef1, 1));
         for (int st = 0; st < kStages; ++st) {
@@ -1680,7 +1730,7 @@ ccr_status build_plan(ccr_ctx *c, bool fp64, int n_bands, const int *band_ids, v
             q.part = part1 * nb;
             q.coef = coef1 * nb;
             q.fin_lds = v.lag ? B.lag[fp64 ? 1 : 0].fin_lds : 0;
-            q.lds = v.fold ? (size_t)pl.n_s : v.lag ? lag_lds(bd) : v.sp ? spectra_pairs_lds(cp.bands.back()) : (v.wide ? spectra_wide_lds(cp.bands.back()) : 0);
+            q.lds = v.fold ? (size_t)pl.n_s : v.lag ? lag_lds(bd, fp64) : v.sp ? spectra_pairs_lds(cp.bands.back()) : (v.wide ? spectra_wide_lds(cp.bands.back()) : 0);
             for (int st = 0; st < kStages; ++st) q.blk[st] = per_t[st] * nb;
             q.blk[kStResample] = per_t[kStResample] * ((nb + res_t - 1) / res_t);
             pend.push_back(q);
@@ -1831,7 +1881,8 @@ ccr_status run_rounds(ccr_ctx *c, const CallPlan &cp, size_t r0, size_t r1, bool
         {
             LaunchTimer lt(c, 3, s, timing);
             if (r.v.lag)
-                HIP_OK(c, launch_lag_finish_m(db, di, r.n, (int)r.blocks[kStFinish], r.fin_lds, part, s));
+                HIP_OK(c, launch_lag_finish_m(db, di, r.n, (int)r.blocks[kStPairs], (int)r.blocks[kStFinish], r.fin_lds,
+                                              part, s));
             else
                 HIP_OK(c, launch_finish_m(db, di, r.n, (int)r.blocks[kStFinish], part, s));
         }

@@ -53,6 +53,7 @@ constexpr int cheb_x_off(int nn) {
 constexpr int kChebNodesAll = kCheb + kChebSplit + kChebSplitMin + kChebSplitLow;
 #define CCR_MAX_DET_K 8
 
+constexpr int kLagSegs = 4;  // segments per step of the lag-resolved grid's kernel
 // Lag-resolved frequency grid of a band for one precision (ccr_lag.hip): N_G = P ns grid points
 // per cycle/sample, residue class p holding the grid indices p + P (m0 + i), i < span.
 struct LagDev {
@@ -65,11 +66,16 @@ struct LagDev {
                      // per pair of detectors (pairs across detectors only, with lags)
     int slot_bytes;  // LDS slot of one transform
     int taps;        // interpolation taps from the grid to an output bin (1: the bins are grid points)
-    int fin_bpt;     // finishing kernel: bins per thread
     const float2 *tw32;    // [ng] exp(-2 pi i j / ng)
     const double2 *tw64;
     const float2 *step32;  // [P][nfold ns / 64] class input twiddle W^(64 (p + P m0) r)
     const double2 *step64;
+    // [Q][n_seg + 2 kLagSegs] pair weights (hat a scale, hat b scale), zero for absent segments
+    const float2 *segwf;
+    const double2 *segwd;
+    // [n_sub][n_seg + 2 kLagSegs] entry kLagSegs + K, K >= -kLagSegs: bit t n + i set when segment
+    // K + t of the problem's i-th of n detectors has a spectrum, t < kLagSegs
+    const uint32_t *step_bits;
     const int *g0;         // [n_f] first tap of a bin, relative to grid index P m0
     const int *frac;       // [n_f] row of wt
     const double *wt;      // [fractions][taps]
@@ -254,24 +260,24 @@ hipError_t launch_fold_m(const BandDev *bands, const WorkItem *items, int n_item
                          bool fp64, int n_s, const void *y, void *F, double *part, hipStream_t stream);
 // Spectra and pair sums on the lag-resolved grid: the kernel variant of a band (transform length,
 // lags kept per step: 0, 1, 2 or 4, wavefronts, pairs across detectors only, per-sample antenna
-// functions), and its finishing kernel (fin_bpt bins a thread).
-constexpr int kLagSegs = 4;           // segments per step
+// functions), and its finishing kernels.
 constexpr int kLagMaxR = 4;           // largest lag of the kernel
 constexpr int kLagFinThreads = 256;
-constexpr int kLagFinBins = 4;        // most bins per thread of the finishing kernel
 struct LagKey {
     int ns = 0, rm = 0, waves = 0;
-    bool cross = false, ps = false;
+    bool cross = false, ps = false, circ = false;
     bool operator==(const LagKey &o) const {
-        return ns == o.ns && rm == o.rm && waves == o.waves && cross == o.cross && ps == o.ps;
+        return ns == o.ns && rm == o.rm && waves == o.waves && cross == o.cross && ps == o.ps && circ == o.circ;
     }
 };
-// Columns a wavefront of the kernel covers (64 U).
-constexpr int lag_cols(int ns) { return ns == 1024 ? 128 : 64; }
+// Most threads of a workgroup (a lane per kept column), and the LDS of its twiddle table.
+constexpr int lag_max_threads(int ns, bool fp64) { return ns < 512 ? 256 : (ns == 512 || fp64 ? 512 : 1024); }
+constexpr int lag_tw_lds(int ns, bool fp64) { return ns == 1024 && !fp64 ? 32 * 64 * 8 : 0; }
 hipError_t launch_lag_m(const LagKey &k, const BandDev *bands, const WorkItem *items, int n_items, int blocks,
                         bool fp64, size_t lds, const void *y, double *part, hipStream_t stream);
-hipError_t launch_lag_finish_m(const BandDev *bands, const WorkItem *items, int n_items, int blocks, size_t lds,
-                               const double *part, hipStream_t stream);
+// reduce_blocks: pair stage, 0 when every item has a single partial a template; blocks: finish stage.
+hipError_t launch_lag_finish_m(const BandDev *bands, const WorkItem *items, int n_items, int reduce_blocks,
+                               int blocks, size_t lds, double *part, hipStream_t stream);
 hipError_t launch_pairs_m(const BandDev *bands, const WorkItem *items, int n_items, int blocks, bool fp64,
                           const void *F, double *part, hipStream_t stream);
 hipError_t launch_finish_m(const BandDev *bands, const WorkItem *items, int n_items, int blocks, const double *part,

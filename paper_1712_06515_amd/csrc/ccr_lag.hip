@@ -13,7 +13,8 @@
 //
 //   k_lag         transforms and pair sums: S_d on the grid's bins inside the band plus the
 //                 interpolation margin, per (template, chunk of segments, residue class)
-//   k_lag_finish  chunk sums, interpolation to the output bins, lag phases, sqrt(2) / N
+//   k_lag_reduce  chunk sums
+//   k_lag_finish  interpolation to the output bins, lag phases, sqrt(2) / N
 #include "ccr_device.h"
 #include "ccr_internal.h"
 
@@ -47,103 +48,161 @@ __device__ __forceinline__ void exchange(c2<T> *v, T *ex, WI wi, WP wp, RD rd) {
 // splits into the uniform W^(64 q r), applied to the input, and W^(q lane), which commutes
 // through the first pass (a DFT over r for one lane) and is folded into the second pass's
 // twiddles: its butterfly l reads first-pass outputs of butterfly (l + 64 r) / V.
-template <typename T, int NS> struct LagTw;
-template <typename T> struct LagTw<T, 1024> {
-    c2<T> a[16], b[4][3];
-    __device__ __forceinline__ void load(const c2<T> *tw, int P, int q, int lane) {
-        const unsigned N = (unsigned)P * 1024;
-#pragma unroll
-        for (int r = 0; r < 16; ++r)
-            a[r] = tw[((unsigned)(r * (lane & 15) * 4 * P) + (unsigned)q * (unsigned)((lane >> 4) + 4 * r)) % N];
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-#pragma unroll
-            for (int r = 1; r < 4; ++r) b[j][r - 1] = tw[(unsigned)(r * (lane + 64 * j) * P) % N];
+// Index of this lane's factor in `tw`: a(r), r < V, of the second pass; b(r), r >= 1, of the third
+// (1024 points: b(4 j + r) of its butterfly j); c(r), r >= 1, of the fourth (256 points).
+template <int NS> struct LagIdx;
+template <> struct LagIdx<1024> {
+    static constexpr int NA = 16, NB = 16, NC [[maybe_unused]] = 0;
+    static __device__ __forceinline__ unsigned a(int r, int P, int q, int lane) {
+        return ((unsigned)(r * (lane & 15) * 4 * P) + (unsigned)q * (unsigned)((lane >> 4) + 4 * r)) % (unsigned)(P * 1024);
+    }
+    static __device__ __forceinline__ unsigned b(int r, int P, int lane) {
+        return (unsigned)((r & 3) * (lane + 64 * (r >> 2)) * P) % (unsigned)(P * 1024);
+    }
+    static __device__ __forceinline__ unsigned c(int, int, int) { return 0; }
+};
+template <> struct LagIdx<512> {
+    static constexpr int NA = 8, NB = 8, NC = 0;
+    static __device__ __forceinline__ unsigned a(int r, int P, int q, int lane) {
+        return ((unsigned)(r * (lane & 7) * 8 * P) + (unsigned)q * (unsigned)((lane >> 3) + 8 * r)) % (unsigned)(P * 512);
+    }
+    static __device__ __forceinline__ unsigned b(int r, int P, int lane) {
+        return (unsigned)(r * lane * P) % (unsigned)(P * 512);
+    }
+    static __device__ __forceinline__ unsigned c(int, int, int) { return 0; }
+};
+template <> struct LagIdx<256> {
+    static constexpr int NA = 4, NB = 4, NC = 4;
+    static __device__ __forceinline__ unsigned a(int r, int P, int q, int lane) {
+        return ((unsigned)(r * (lane & 3) * 16 * P) + (unsigned)q * (unsigned)((lane >> 2) + 16 * r)) % (unsigned)(P * 256);
+    }
+    static __device__ __forceinline__ unsigned b(int r, int P, int lane) {
+        return (unsigned)(r * (lane & 15) * 4 * P) % (unsigned)(P * 256);
+    }
+    static __device__ __forceinline__ unsigned c(int r, int P, int lane) {
+        return (unsigned)(r * lane * P) % (unsigned)(P * 256);
     }
 };
-template <typename T> struct LagTw<T, 512> {
-    c2<T> a[8], b[7];
-    __device__ __forceinline__ void load(const c2<T> *tw, int P, int q, int lane) {
-        const unsigned N = (unsigned)P * 512;
+
+// The factors in registers, or (1024 points) in LDS, one copy a workgroup: 56 registers a lane
+// less, which is what lets four wavefronts share a SIMD.
+template <typename T, int NS, bool LDS> struct LagTw;
+template <typename T, int NS> struct LagTw<T, NS, false> {
+    using I = LagIdx<NS>;
+    c2<T> va[I::NA], vb[I::NB], vc[I::NC > 0 ? I::NC : 1];
+    __device__ __forceinline__ void load(const c2<T> *tw, c2<T> *, int P, int q, int lane) {
 #pragma unroll
-        for (int r = 0; r < 8; ++r)
-            a[r] = tw[((unsigned)(r * (lane & 7) * 8 * P) + (unsigned)q * (unsigned)((lane >> 3) + 8 * r)) % N];
+        for (int r = 0; r < I::NA; ++r) va[r] = tw[I::a(r, P, q, lane)];
 #pragma unroll
-        for (int r = 1; r < 8; ++r) b[r - 1] = tw[(unsigned)(r * lane * P) % N];
+        for (int r = 1; r < I::NB; ++r) vb[r] = tw[I::b(r, P, lane)];
+#pragma unroll
+        for (int r = 1; r < I::NC; ++r) vc[r] = tw[I::c(r, P, lane)];
     }
+    __device__ __forceinline__ c2<T> a(int r) const { return va[r]; }
+    __device__ __forceinline__ c2<T> b(int r) const { return vb[r]; }
+    __device__ __forceinline__ c2<T> c(int r) const { return vc[r]; }
 };
-template <typename T> struct LagTw<T, 256> {
-    c2<T> a[4], b[3], c[3];
-    __device__ __forceinline__ void load(const c2<T> *tw, int P, int q, int lane) {
-        const unsigned N = (unsigned)P * 256;
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-            a[r] = tw[((unsigned)(r * (lane & 3) * 16 * P) + (unsigned)q * (unsigned)((lane >> 2) + 16 * r)) % N];
-#pragma unroll
-        for (int r = 1; r < 4; ++r) {
-            b[r - 1] = tw[(unsigned)(r * (lane & 15) * 4 * P) % N];
-            c[r - 1] = tw[(unsigned)(r * lane * P) % N];
+template <typename T, int NS> struct LagTw<T, NS, true> {
+    using I = LagIdx<NS>;
+    const c2<T> *l;
+    __device__ __forceinline__ void load(const c2<T> *tw, c2<T> *lds, int P, int q, int lane) {
+        for (int e = threadIdx.x; e < 64 * (I::NA + I::NB); e += blockDim.x) {
+            const int r = e >> 6, ln = e & 63;
+            lds[e] = tw[r < I::NA ? I::a(r, P, q, ln) : I::b(r - I::NA, P, ln)];
         }
+        l = lds + lane;
+        __syncthreads();
     }
+    __device__ __forceinline__ c2<T> a(int r) const { return l[64 * r]; }
+    __device__ __forceinline__ c2<T> b(int r) const { return l[64 * (I::NA + r)]; }
+    __device__ __forceinline__ c2<T> c(int) const { return l[0]; }
 };
 
 // NS-point forward FFT of one wavefront (V = NS / 64 values a lane, x[l + 64 r] in v[r] on
 // entry, X[l + 64 J] in v[J] on return), self-sorting passes of radix 16, 16, 4 (1024), 8, 8, 8
 // (512) or 4, 4, 4, 4 (256): a pass of radix V with stride Ns has butterfly l read a[l + 64 r],
 // twiddle input r and write output r to (l / Ns) V Ns + l % Ns + r Ns.  Between passes the values
-// go through `ex` (NS + NS / V entries), index i at i + i / V.
-template <typename T>
-__device__ __forceinline__ void lag_fft(c2<T> *v, T *ex, const LagTw<T, 1024> &t, int lane) {
+// go through `ex` (at most NS + 64 entries), padded so that the lanes served together -- 32 for
+// 4-byte values, 16 for 8-byte ones -- fall on distinct banks on both sides: 4-byte values at
+// i + i / 32 in the first exchange and with 16 (8, 4, 16) entries after each 256 (64, 32, 64)
+// in the later ones, 8-byte values at i + i / V.
+template <typename T, bool L>
+__device__ __forceinline__ void lag_fft(c2<T> *v, T *ex, const LagTw<T, 1024, L> &t, int lane) {
     const int g = lane >> 4, k = lane & 15;
     auto perm = [](int i) { return 4 * (i & 3) + (i >> 2); };
     dft16<T>(v);
-    exchange<T, 16>(v, ex, perm, [&](int i) { return 17 * lane + i; }, [&](int r) { return lane + g + 68 * r; });
+    if constexpr (sizeof(T) == 4)
+        exchange<T, 16>(v, ex, perm, [&](int i) { return 16 * lane + (lane >> 1) + i; },
+                        [&](int r) { return lane + (lane >> 5) + 66 * r; });
+    else
+        exchange<T, 16>(v, ex, perm, [&](int i) { return 17 * lane + i; }, [&](int r) { return lane + g + 68 * r; });
 #pragma unroll
-    for (int r = 0; r < 16; ++r) v[r] = cmul<T>(v[r], t.a[r]);
+    for (int r = 0; r < 16; ++r) v[r] = cmul<T>(v[r], t.a(r));
     dft16<T>(v);
-    exchange<T, 16>(v, ex, perm, [&](int i) { return 272 * g + k + 17 * i; },
-                    [&](int r) { return lane + g + 68 * (r & 3) + 272 * (r >> 2); });
+    if constexpr (sizeof(T) == 4)
+        exchange<T, 16>(v, ex, perm, [&](int i) { return 272 * g + k + 16 * i; },
+                        [&](int r) { return lane + 64 * (r & 3) + 272 * (r >> 2); });
+    else
+        exchange<T, 16>(v, ex, perm, [&](int i) { return 272 * g + k + 17 * i; },
+                        [&](int r) { return lane + g + 68 * (r & 3) + 272 * (r >> 2); });
 #pragma unroll
     for (int j = 0; j < 4; ++j) {  // v[j + 4 r] = a[l + 64 j + 256 r]
 #pragma unroll
-        for (int r = 1; r < 4; ++r) v[j + 4 * r] = cmul<T>(v[j + 4 * r], t.b[j][r - 1]);
+        for (int r = 1; r < 4; ++r) v[j + 4 * r] = cmul<T>(v[j + 4 * r], t.b(4 * j + r));
         dft4<T>(v[j], v[j + 4], v[j + 8], v[j + 12]);
     }
 }
 
-template <typename T>
-__device__ __forceinline__ void lag_fft(c2<T> *v, T *ex, const LagTw<T, 512> &t, int lane) {
+template <typename T, bool L>
+__device__ __forceinline__ void lag_fft(c2<T> *v, T *ex, const LagTw<T, 512, L> &t, int lane) {
     const int g = lane >> 3, k = lane & 7;
     auto id = [](int i) { return i; };
-    auto rd = [&](int r) { return lane + g + 72 * r; };
     dft8<T>(v);
-    exchange<T, 8>(v, ex, id, [&](int i) { return 9 * lane + i; }, rd);
+    if constexpr (sizeof(T) == 4)
+        exchange<T, 8>(v, ex, id, [&](int i) { return 8 * lane + (lane >> 2) + i; },
+                       [&](int r) { return lane + (lane >> 5) + 66 * r; });
+    else
+        exchange<T, 8>(v, ex, id, [&](int i) { return 9 * lane + i; }, [&](int r) { return lane + g + 72 * r; });
 #pragma unroll
-    for (int r = 0; r < 8; ++r) v[r] = cmul<T>(v[r], t.a[r]);
+    for (int r = 0; r < 8; ++r) v[r] = cmul<T>(v[r], t.a(r));
     dft8<T>(v);
-    exchange<T, 8>(v, ex, id, [&](int i) { return 72 * g + k + 9 * i; }, rd);
+    if constexpr (sizeof(T) == 4)
+        exchange<T, 8>(v, ex, id, [&](int i) { return 72 * g + k + 8 * i; }, [&](int r) { return lane + 72 * r; });
+    else
+        exchange<T, 8>(v, ex, id, [&](int i) { return 72 * g + k + 9 * i; }, [&](int r) { return lane + g + 72 * r; });
 #pragma unroll
-    for (int r = 1; r < 8; ++r) v[r] = cmul<T>(v[r], t.b[r - 1]);
+    for (int r = 1; r < 8; ++r) v[r] = cmul<T>(v[r], t.b(r));
     dft8<T>(v);
 }
 
-template <typename T>
-__device__ __forceinline__ void lag_fft(c2<T> *v, T *ex, const LagTw<T, 256> &t, int lane) {
+template <typename T, bool L>
+__device__ __forceinline__ void lag_fft(c2<T> *v, T *ex, const LagTw<T, 256, L> &t, int lane) {
     const int g4 = lane >> 2, k4 = lane & 3, g16 = lane >> 4, k16 = lane & 15;
     auto id = [](int i) { return i; };
     auto rd = [&](int r) { return lane + g4 + 80 * r; };
     dft4<T>(v[0], v[1], v[2], v[3]);
-    exchange<T, 4>(v, ex, id, [&](int i) { return 5 * lane + i; }, rd);
+    if constexpr (sizeof(T) == 4)
+        exchange<T, 4>(v, ex, id, [&](int i) { return 4 * lane + (lane >> 3) + i; },
+                       [&](int r) { return lane + (lane >> 5) + 66 * r; });
+    else
+        exchange<T, 4>(v, ex, id, [&](int i) { return 5 * lane + i; }, rd);
 #pragma unroll
-    for (int r = 0; r < 4; ++r) v[r] = cmul<T>(v[r], t.a[r]);
+    for (int r = 0; r < 4; ++r) v[r] = cmul<T>(v[r], t.a(r));
     dft4<T>(v[0], v[1], v[2], v[3]);
-    exchange<T, 4>(v, ex, id, [&](int i) { return 20 * g4 + k4 + 5 * i; }, rd);
+    if constexpr (sizeof(T) == 4)
+        exchange<T, 4>(v, ex, id, [&](int i) { return 16 * g4 + 4 * (g4 >> 1) + k4 + 4 * i; },
+                       [&](int r) { return lane + 4 * (lane >> 5) + 72 * r; });
+    else
+        exchange<T, 4>(v, ex, id, [&](int i) { return 20 * g4 + k4 + 5 * i; }, rd);
 #pragma unroll
-    for (int r = 1; r < 4; ++r) v[r] = cmul<T>(v[r], t.b[r - 1]);
+    for (int r = 1; r < 4; ++r) v[r] = cmul<T>(v[r], t.b(r));
     dft4<T>(v[0], v[1], v[2], v[3]);
-    exchange<T, 4>(v, ex, id, [&](int i) { return 80 * g16 + k16 + (k16 >> 2) + 20 * i; }, rd);
+    if constexpr (sizeof(T) == 4)
+        exchange<T, 4>(v, ex, id, [&](int i) { return 80 * g16 + k16 + 16 * i; }, [&](int r) { return lane + 80 * r; });
+    else
+        exchange<T, 4>(v, ex, id, [&](int i) { return 80 * g16 + k16 + (k16 >> 2) + 20 * i; }, rd);
 #pragma unroll
-    for (int r = 1; r < 4; ++r) v[r] = cmul<T>(v[r], t.c[r - 1]);
+    for (int r = 1; r < 4; ++r) v[r] = cmul<T>(v[r], t.c(r));
     dft4<T>(v[0], v[1], v[2], v[3]);
 }
 
@@ -157,25 +216,27 @@ template <> __device__ __forceinline__ double2 ld_uniform_c2<double>(const doubl
 }
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-template <typename T> __device__ __forceinline__ c2<T> ld_buf(__amdgpu_buffer_rsrc_t rs, int i);
-template <> __device__ __forceinline__ float2 ld_buf<float>(__amdgpu_buffer_rsrc_t rs, int i) {
-    return __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(rs, i * 8, 0, 0));
+// Value at byte offset `lane` + 64 r values (`lane`: the lane's own byte offset, opaque to the
+// compiler so that the rows' offsets stay additions, which the load's immediate field holds).
+template <typename T> __device__ __forceinline__ c2<T> ld_buf(__amdgpu_buffer_rsrc_t rs, int lane, int r);
+template <> __device__ __forceinline__ float2 ld_buf<float>(__amdgpu_buffer_rsrc_t rs, int lane, int r) {
+    return __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(rs, lane + 512 * r, 0, 0));
 }
-template <> __device__ __forceinline__ double2 ld_buf<double>(__amdgpu_buffer_rsrc_t rs, int i) {
-    return __builtin_bit_cast(double2, (u32x4)__builtin_amdgcn_raw_buffer_load_b128(rs, i * 16, 0, 0));
+template <> __device__ __forceinline__ double2 ld_buf<double>(__amdgpu_buffer_rsrc_t rs, int lane, int r) {
+    return __builtin_bit_cast(double2, (u32x4)__builtin_amdgcn_raw_buffer_load_b128(rs, lane + 1024 * r, 0, 0));
 }
 
 template <typename T> struct LagTab;
 template <> struct LagTab<float> {
     static __device__ __forceinline__ const float2 *tw(const LagDev &G) { return G.tw32; }
     static __device__ __forceinline__ const float2 *step(const LagDev &G) { return G.step32; }
-    static __device__ __forceinline__ const float2 *segw(const BandDev &B) { return B.segwf; }
+    static __device__ __forceinline__ const float2 *segw(const LagDev &G) { return G.segwf; }
     static __device__ __forceinline__ const float2 *pw(const BandDev &B) { return B.pwf; }
 };
 template <> struct LagTab<double> {
     static __device__ __forceinline__ const double2 *tw(const LagDev &G) { return G.tw64; }
     static __device__ __forceinline__ const double2 *step(const LagDev &G) { return G.step64; }
-    static __device__ __forceinline__ const double2 *segw(const BandDev &B) { return B.segwd; }
+    static __device__ __forceinline__ const double2 *segw(const LagDev &G) { return G.segwd; }
     static __device__ __forceinline__ const double2 *pw(const BandDev &B) { return B.pw; }
 };
 
@@ -187,24 +248,17 @@ template <> struct LagTab<double> {
 struct LagDets {
     int n, d0, d1;
     __device__ __forceinline__ int at(int i) const { return i == 0 ? d0 : (i == 1 ? d1 : i); }
-    // activity of segment K's spectra, bit i for detector at(i)
-    __device__ __forceinline__ unsigned bits(unsigned b) const {
-        if (n == 1) return (b >> d0) & 1u;
-        if (n == 2) return ((b >> d0) & 1u) | (((b >> d1) & 1u) << 1);
-        return b;
-    }
 };
 
 // Streams of one grid column at the step's kLagSegs segments from the spectra in LDS: NST = 2:
 // the sums over the detectors of hat a_X F_X and hat b_X F_X (n[t] = {A, B}); NST = 4 (two
 // detectors, pairs across them only): {a_0, a_1, b_0, b_1}.  s0: the same-time products of the
-// pairs X < Y, Re[conj(a_X) a_Y + conj(b_X) b_Y], or for Gamma^circ Im[conj(b_X) a_Y - conj(a_X) b_Y],
-// of the segments from t0 on (the ones before them are halo); null with no pairs across detectors.
-// PS (per-sample antenna functions): the two streams are transforms of their own.
+// pairs X < Y, Re[conj(a_X) a_Y + conj(b_X) b_Y], or for Gamma^circ Im[conj(b_X) a_Y - conj(a_X) b_Y]
+// (a workgroup with more than one detector always sums pairs across them).  PS (per-sample
+// antenna functions): the two streams are transforms of their own.
 template <typename T, int ND, int NST, bool PS>
 __device__ __forceinline__ void lag_gather(const BandDev &B, const LagDets &D, const char *slots, int slot_bytes,
-                                           int col, int Kb, int nd, bool circ, bool cross, int t0, T &s0,
-                                           c2<T> (&n)[kLagSegs][NST]) {
+                                           int col, int Kb, int nd, bool circ, T &s0, c2<T> (&n)[kLagSegs][NST]) {
     const int NDr = ND > 0 ? ND : nd;
     constexpr int NM = ND > 0 ? ND : CCR_MAX_DET_K;
 #pragma unroll
@@ -220,20 +274,25 @@ __device__ __forceinline__ void lag_gather(const BandDev &B, const LagDets &D, c
                 a = f;
                 b = reinterpret_cast<const c2<T> *>(slots + (size_t)(u + 1) * slot_bytes)[col];
             } else {
-                const c2<T> w = ld_uniform_c2<T>(LagTab<T>::segw(B), D.at(i) * B.n_seg + min(Kb + t, B.n_seg - 1));
+                const c2<T> w = ld_uniform_c2<T>(LagTab<T>::segw(B.lag), D.at(i) * (B.n_seg + 2 * kLagSegs) + kLagSegs + Kb + t);
                 a = cscale<T>(f, w.x);
                 b = cscale<T>(f, w.y);
             }
-            if (i > 0 && cross && t >= t0) {
-                if (circ) s0 += (Bs.x * a.y - Bs.y * a.x) - (A.x * b.y - A.y * b.x);
-                else s0 += (A.x * a.x + A.y * a.y) + (Bs.x * b.x + Bs.y * b.y);
+            if (i > 0) {
+                if (circ) {
+                    s0 = fma(Bs.x, a.y, fma(-Bs.y, a.x, s0));
+                    s0 = fma(-A.x, b.y, fma(A.y, b.x, s0));
+                } else {
+                    s0 = fma(A.x, a.x, fma(A.y, a.y, s0));
+                    s0 = fma(Bs.x, b.x, fma(Bs.y, b.y, s0));
+                }
             }
             if constexpr (NST == 4) {
                 n[t][i & 1] = a;
                 n[t][2 + (i & 1)] = b;
             }
-            A = cadd<T>(A, a);
-            Bs = cadd<T>(Bs, b);
+            A = i == 0 ? a : cadd<T>(A, a);
+            Bs = i == 0 ? b : cadd<T>(Bs, b);
         }
         if constexpr (NST == 2) {
             n[t][0] = A;
@@ -250,33 +309,36 @@ __device__ __forceinline__ void lag_gather(const BandDev &B, const LagDets &D, c
 //   mod N_S only), applies the class's input twiddle, transforms them and writes the class's
 //   bins inside the band to the unit's LDS slot, which also serves as the transform's exchange
 //   buffer.  Units of absent segments write zeros.  The next unit's input is loaded meanwhile.
-//   Pair sums.  Lane j of the workgroup owns columns j + 64 W u (u < U): it forms the step's
-//   streams, multiplies each segment's with those of the RM segments before it -- the step's own
+//   Pair sums.  Lane j of the workgroup owns column j: it forms the step's streams, multiplies each segment's with those of the RM segments before it -- the step's own
 //   or the last step's, kept in registers -- and adds them to S_1 .. S_RM (lags above R are
 //   computed and dropped).  FP32 products of a step are summed in FP32, steps in FP64.
 // Two barriers a step.  Partials: [comp][P][span], comp 0: S_0 (same-time pairs across
 // detectors), 2 d - 1 and 2 d: Re and Im of S_d.
 //
-// Bound: VALU issue (transforms ~3/4 of the instructions, pair sums ~1/4 at lag 4).  Against the
-// transform at every output bin with window sums over an LDS ring of spectra: 1300 -> 175 ms for
-// 1002 templates of the 240-day, lag-4 band; in FP64 (spectra through memory, then pair sums)
-// 23.4 -> 1.7 ms for 5 templates of 120 days of it.
-template <typename T, int NS, int U, int RM, bool CR, bool PS>
+// Bound: VALU issue (71 % busy at 1024 points, lag 4; transforms ~70 % of the instructions).
+// 60 templates of the 240-day, lag-4 band: transforms at every output bin with window sums over
+// an LDS ring of spectra 80.4 ms; this kernel with two columns a lane, twiddles in registers (256,
+// two wavefronts a SIMD), per-unit scalar searches and one bank conflict a read 10.9 ms; one
+// column a lane and twiddles in LDS (four wavefronts a SIMD), halo as whole steps, fused
+// multiply-adds in the products 8.4 ms; conflict-free padding and table lookups for the activity
+// masks and weights 7.25 ms.  FP64, 5 templates of 120 days: 23.4 ms (spectra through memory) -> 0.94 ms.
+template <typename T, int NS, int RM, bool CR, bool PS, int CM>
 __device__ __forceinline__ void lag_body(const BandDev &B, const c2<T> *__restrict__ y, double *__restrict__ part,
                                          int k_chunk, int n_chunks, int c, int sub, int p, int tb) {
     extern __shared__ __align__(16) char smem[];
     constexpr int V = NS / 64;
     constexpr int S = PS ? 2 : 1;
     constexpr int NST = CR ? 4 : 2;
+    constexpr bool LTW = lag_tw_lds(NS, sizeof(T) == 8) > 0;
     const LagDev &G = B.lag;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int W = blockDim.x >> 6;
     const int n_k = B.n_k, R = B.R, P = G.P, span = G.span, nf = G.nfold;
-    const bool circ = B.weight != 0, cross = (B.pairs & 1) != 0;
+    const bool circ = CM == 2 ? B.weight != 0 : CM == 1;
     // the workgroup's detectors
     LagDets D{B.Q, 0, 1};
     if (G.n_sub > 1 || CR) {
-        if (!cross) {
+        if (!(B.pairs & 1)) {
             D = LagDets{1, sub, sub};
         } else {
             int X = 0, r = sub;
@@ -291,111 +353,118 @@ __device__ __forceinline__ void lag_body(const BandDev &B, const c2<T> *__restri
     const int slot_bytes = G.slot_bytes;
     const int nunit = kLagSegs * nd;  // units of a step (times the streams)
 
-    const int q = (p + P * G.m0) % G.ng;
-    LagTw<T, NS> tw;
-    tw.load(LagTab<T>::tw(G), P, q, lane);
+    LagTw<T, NS, LTW> tw;
+    tw.load(LagTab<T>::tw(G), reinterpret_cast<c2<T> *>(smem), P, (p + P * G.m0) % G.ng, lane);
+    char *slots = smem + lag_tw_lds(NS, sizeof(T) == 8);
     const c2<T> *step = LagTab<T>::step(G) + (size_t)p * V * nf;
 
-    const int K0 = c * k_chunk, K1 = min(B.n_seg, K0 + k_chunk);
-    const int Kh = max(0, K0 - R);
+    // steps of kLagSegs segments from K0 on, after one of halo segments (of which the R before K0 count)
+    const int K0 = c * k_chunk, K1 = min(B.n_seg, K0 + k_chunk), Kh = max(0, K0 - R);
+    const int Ks = RM > 0 && K0 > 0 ? K0 - kLagSegs : K0;
     const int64_t nr = (int64_t)B.n_seg * n_k;
     const c2<T> *yb = y + (size_t)tb * B.Q * nr;
 
-    // active units of the step at Kb: bit t nd + i
+    // active units of the step at Kb: bit t nd + i.  The table holds them per first segment (with a
+    // step of zeros at either end); the chunk's ends cut the first and the last step.
+    const uint32_t *tab = G.step_bits + (size_t)sub * (B.n_seg + 2 * kLagSegs) + kLagSegs;
     auto step_mask = [&](int Kb) -> unsigned {
-        unsigned m = 0;
-#pragma unroll
-        for (int t = 0; t < kLagSegs; ++t)
-            if (Kb + t < K1) m |= D.bits(ld_uniform(B.seg_bits, Kb + t)) << (t * nd);
+        unsigned m = ld_uniform(tab, Kb);
+        if (Kb < Kh) m &= ~0u << ((Kh - Kb) * nd);
+        if (Kb + kLagSegs > K1) m &= (1u << ((K1 - Kb) * nd)) - 1u;
         return m;
     };
     // n-th set bit of m (from 0), -1 if there is none
-    auto nth = [](unsigned m, int n) -> int {
+    const unsigned all = nunit >= 32 ? ~0u : (1u << nunit) - 1u;
+    auto nth = [&](unsigned m, int n) -> int {
+        if (m == all) return n < nunit ? n : -1;
         for (int k = 0; k < n && m; ++k) m &= m - 1;
         return m ? __builtin_ctz(m) : -1;
     };
-    auto src = [&](const c2<T> *base, int det, int K) {
+    const unsigned rnd = (65536u + nd - 1) / nd;  // u / nd = u rnd >> 16 for u < 32, nd <= 8
+    int lo = lane * (int)sizeof(c2<T>);
+    asm("" : "+v"(lo));
+    // input of segment K of detector det; reads past its N_K samples give zero (on = false: all)
+    auto src = [&](const c2<T> *base, int det, int K, bool on) {
         return __builtin_amdgcn_make_buffer_rsrc((void *)(base + (size_t)det * nr + (size_t)K * n_k), (short)0,
-                                                 n_k * (int)sizeof(c2<T>), 0x00020000);
+                                                 on ? n_k * (int)sizeof(c2<T>) : 0, 0x00020000);
     };
+    // this wavefront's units in order: (step iK, unit iu, stream in % S); nxt holds that unit's input
     c2<T> nxt[V];
-    auto load = [&](int Kb, int unit) {
-        const int t = unit / nd, i = unit - t * nd;
-        const __amdgpu_buffer_rsrc_t rs = src(yb, D.at(i), Kb + t);
+    int iK = Ks, in = wv;
+    unsigned im = step_mask(Ks);
+    int iu = nth(im, in / S);
+    auto seek = [&]() {  // to the first unit at or after the iterator's place
+        while (iu < 0 && iK + kLagSegs < K1) {
+            iK += kLagSegs;
+            im = step_mask(iK);
+            in = wv;
+            iu = nth(im, in / S);
+        }
+        const int t = (int)((unsigned)max(iu, 0) * rnd >> 16), i = max(iu, 0) - t * nd;
+        const __amdgpu_buffer_rsrc_t rs = src(yb, D.at(i), iu >= 0 ? iK + t : 0, iu >= 0);
 #pragma unroll
-        for (int r = 0; r < V; ++r) nxt[r] = ld_buf<T>(rs, lane + 64 * r);
+        for (int r = 0; r < V; ++r) nxt[r] = ld_buf<T>(rs, lo, r);
     };
+    seek();
 
-    c2<T> hist[U][RM > 0 ? RM : 1][NST];
-    double acc0[U], acc[U][RM > 0 ? 2 * RM : 1];
+    c2<T> hist[RM > 0 ? RM : 1][NST];
+    double acc0 = 0.0, acc[RM > 0 ? 2 * RM : 1];
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-        acc0[u] = 0.0;
+    for (int k = 0; k < (RM > 0 ? 2 * RM : 1); ++k) acc[k] = 0.0;
 #pragma unroll
-        for (int k = 0; k < (RM > 0 ? 2 * RM : 1); ++k) acc[u][k] = 0.0;
+    for (int d = 0; d < (RM > 0 ? RM : 1); ++d)
 #pragma unroll
-        for (int d = 0; d < (RM > 0 ? RM : 1); ++d)
-#pragma unroll
-            for (int j = 0; j < NST; ++j) hist[u][d][j] = mk<T>((T)0, (T)0);
-    }
+        for (int j = 0; j < NST; ++j) hist[d][j] = mk<T>((T)0, (T)0);
+    const int col = min((int)threadIdx.x, span - 1);
 
-    unsigned mask = step_mask(Kh);
-    {
-        const int u0 = nth(mask, wv / S);
-        if (u0 >= 0) load(Kh, u0);
-    }
-    for (int Kb = Kh; Kb < K1; Kb += kLagSegs) {
-        const unsigned nmask = Kb + kLagSegs < K1 ? step_mask(Kb + kLagSegs) : 0u;
-        const int nu0 = nth(nmask, wv / S);
+#pragma unroll 1
+    for (int Kb = Ks; Kb < K1; Kb += kLagSegs) {
+        const unsigned mask = step_mask(Kb);
         if (mask == 0) {  // no spectra in the step (uniform over the workgroup)
 #pragma unroll
-            for (int u = 0; u < U; ++u)
+            for (int d = 0; d < (RM > 0 ? RM : 1); ++d)
 #pragma unroll
-                for (int d = 0; d < (RM > 0 ? RM : 1); ++d)
-#pragma unroll
-                    for (int j = 0; j < NST; ++j) hist[u][d][j] = mk<T>((T)0, (T)0);
-            if (nu0 >= 0) load(Kb + kLagSegs, nu0);
-            mask = nmask;
+                for (int j = 0; j < NST; ++j) hist[d][j] = mk<T>((T)0, (T)0);
             continue;
         }
         // transforms: this wavefront takes active (unit, stream) numbers wv, wv + W, ...
-        int nn = wv;
-        int unit = nth(mask, nn / S);
-        if (unit < 0 && nu0 >= 0) load(Kb + kLagSegs, nu0);
 #pragma unroll 1
-        while (unit >= 0) {
-            const int s = PS ? nn % S : 0;
-            const int t = unit / nd, i = unit - t * nd;
-            char *slot = smem + (size_t)(unit * S + s) * slot_bytes;
+        while (iu >= 0 && iK == Kb) {
+            const int s = PS ? in % S : 0;
+            const int t = (int)((unsigned)iu * rnd >> 16), i = iu - t * nd;
+            char *slot = slots + (size_t)(iu * S + s) * slot_bytes;
             c2<T> v[V];
-#pragma unroll
-            for (int r = 0; r < V; ++r) v[r] = nxt[r];
-            // the next input: this wavefront's next unit of the step, or its first of the next step
-            nn += W;
-            const int un = nth(mask, nn / S);
-            if (un >= 0) load(Kb, un);
-            else if (nu0 >= 0) load(Kb + kLagSegs, nu0);
             if constexpr (PS) {
-                const __amdgpu_buffer_rsrc_t rw = src(LagTab<T>::pw(B), D.at(i), Kb + t);
+                const __amdgpu_buffer_rsrc_t rw = src(LagTab<T>::pw(B), D.at(i), Kb + t, true);
 #pragma unroll
                 for (int r = 0; r < V; ++r) {
-                    const c2<T> w = ld_buf<T>(rw, lane + 64 * r);
-                    v[r] = cscale<T>(v[r], s ? w.y : w.x);
+                    const c2<T> w = ld_buf<T>(rw, lo, r);
+                    v[r] = cscale<T>(nxt[r], s ? w.y : w.x);
                 }
-            }
-            if (p > 0) {
+                if (p > 0) {
 #pragma unroll
-                for (int r = 0; r < V; ++r) v[r] = cmul<T>(v[r], ld_uniform_c2<T>(step, r));
+                    for (int r = 0; r < V; ++r) v[r] = cmul<T>(v[r], ld_uniform_c2<T>(step, r));
+                }
+            } else if (p > 0) {
+#pragma unroll
+                for (int r = 0; r < V; ++r) v[r] = cmul<T>(nxt[r], ld_uniform_c2<T>(step, r));
+            } else {
+#pragma unroll
+                for (int r = 0; r < V; ++r) v[r] = nxt[r];
             }
+            // the next unit's input is loaded while this one is transformed
+            in += W;
+            iu = nth(im, in / S);
+            seek();
             for (int j = 1; j < nf; ++j) {
-                const __amdgpu_buffer_rsrc_t rs = src(yb, D.at(i), Kb + t);
-                const __amdgpu_buffer_rsrc_t rw = src(PS ? LagTab<T>::pw(B) : yb, D.at(i), Kb + t);
+                const __amdgpu_buffer_rsrc_t rs = src(yb, D.at(i), Kb + t, true);
+                const __amdgpu_buffer_rsrc_t rw = src(PS ? LagTab<T>::pw(B) : yb, D.at(i), Kb + t, true);
 #pragma unroll
                 for (int r = 0; r < V; ++r) {
                     if (64 * r + NS * j >= n_k) continue;  // uniform
-                    c2<T> z = ld_buf<T>(rs, lane + 64 * r + NS * j);
+                    c2<T> z = ld_buf<T>(rs, lo, r + V * j);
                     if constexpr (PS) {
-                        const c2<T> w = ld_buf<T>(rw, lane + 64 * r + NS * j);
+                        const c2<T> w = ld_buf<T>(rw, lo, r + V * j);
                         z = cscale<T>(z, s ? w.y : w.x);
                     }
                     v[r] = cadd<T>(v[r], cmul<T>(z, ld_uniform_c2<T>(step, r + V * j)));
@@ -406,97 +475,90 @@ __device__ __forceinline__ void lag_body(const BandDev &B, const c2<T> *__restri
 #pragma unroll
             for (int J = 0; J < V; ++J)
                 if (64 * J < span) reinterpret_cast<c2<T> *>(slot)[lane + 64 * J] = v[J];
-            unit = un;
         }
         // zeros for the units without a spectrum
         {
-            unsigned off = ~mask & (nunit >= 32 ? ~0u : (1u << nunit) - 1u);
+            unsigned off = ~mask & all;
             for (int k = 0; off; off &= off - 1, ++k) {
                 if (k % W != wv) continue;
-                c2<T> *slot = reinterpret_cast<c2<T> *>(smem + (size_t)(__builtin_ctz(off) * S) * slot_bytes);
+                c2<T> *slot = reinterpret_cast<c2<T> *>(slots + (size_t)(__builtin_ctz(off) * S) * slot_bytes);
                 for (int e = lane; e < S * slot_bytes / (int)sizeof(c2<T>); e += 64) slot[e] = mk<T>((T)0, (T)0);
             }
         }
         __syncthreads();
-        const int t0 = max(0, K0 - Kb);  // halo segments before t0 only enter the history
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-            if (wv * 64 + 64 * W * u >= span) continue;  // uniform: no lane of this wavefront has a column
-            const int col = min((int)threadIdx.x + 64 * W * u, span - 1);
+        if (wv * 64 < span) {  // uniform: some lane of this wavefront has a column
             c2<T> n[kLagSegs][NST];
             T s0 = (T)0;
             if constexpr (CR) {
-                lag_gather<T, 2, NST, PS>(B, D, smem, slot_bytes, col, Kb, nd, circ, cross, t0, s0, n);
+                lag_gather<T, 2, NST, PS>(B, D, slots, slot_bytes, col, Kb, nd, circ, s0, n);
             } else {
                 switch (nd) {
-                    case 1: lag_gather<T, 1, NST, PS>(B, D, smem, slot_bytes, col, Kb, nd, circ, cross, t0, s0, n); break;
-                    case 2: lag_gather<T, 2, NST, PS>(B, D, smem, slot_bytes, col, Kb, nd, circ, cross, t0, s0, n); break;
-                    case 3: lag_gather<T, 3, NST, PS>(B, D, smem, slot_bytes, col, Kb, nd, circ, cross, t0, s0, n); break;
-                    default: lag_gather<T, 0, NST, PS>(B, D, smem, slot_bytes, col, Kb, nd, circ, cross, t0, s0, n); break;
+                    case 1: lag_gather<T, 1, NST, PS>(B, D, slots, slot_bytes, col, Kb, nd, circ, s0, n); break;
+                    case 2: lag_gather<T, 2, NST, PS>(B, D, slots, slot_bytes, col, Kb, nd, circ, s0, n); break;
+                    case 3: lag_gather<T, 3, NST, PS>(B, D, slots, slot_bytes, col, Kb, nd, circ, s0, n); break;
+                    default: lag_gather<T, 0, NST, PS>(B, D, slots, slot_bytes, col, Kb, nd, circ, s0, n); break;
                 }
             }
-            acc0[u] += (double)s0;
-            if constexpr (RM > 0) {
-                T st[2 * RM];
+            if (Kb >= K0) {  // uniform; halo segments only enter the history
+                acc0 += (double)s0;
+                if constexpr (RM > 0) {
+                    T st[2 * RM];
 #pragma unroll
-                for (int k = 0; k < 2 * RM; ++k) st[k] = (T)0;
+                    for (int k = 0; k < 2 * RM; ++k) st[k] = (T)0;
 #pragma unroll
-                for (int t = 0; t < kLagSegs; ++t) {
-                    if (t < t0) continue;  // uniform
-                    // x[j]: the stream multiplied with the earlier segment's stream h[j]
-                    c2<T> x[NST];
-                    if constexpr (NST == 2) {
-                        x[0] = circ ? n[t][1] : n[t][0];
-                        x[1] = circ ? mk<T>(-n[t][0].x, -n[t][0].y) : n[t][1];
-                    } else {
+                    for (int t = 0; t < kLagSegs; ++t) {
+                        // x[j]: the stream multiplied with the earlier segment's stream h[j]
+                        c2<T> x[NST];
+                        if constexpr (NST == 2) {
+                            x[0] = circ ? n[t][1] : n[t][0];
+                            x[1] = circ ? mk<T>(-n[t][0].x, -n[t][0].y) : n[t][1];
+                        } else {
 #pragma unroll
-                        for (int j = 0; j < 2; ++j) {
-                            x[j] = circ ? n[t][3 - j] : n[t][1 - j];
-                            x[2 + j] = circ ? mk<T>(-n[t][1 - j].x, -n[t][1 - j].y) : n[t][3 - j];
+                            for (int j = 0; j < 2; ++j) {
+                                x[j] = circ ? n[t][3 - j] : n[t][1 - j];
+                                x[2 + j] = circ ? mk<T>(-n[t][1 - j].x, -n[t][1 - j].y) : n[t][3 - j];
+                            }
+                        }
+#pragma unroll
+                        for (int d = 1; d <= RM; ++d) {
+#pragma unroll
+                            for (int j = 0; j < NST; ++j) {
+                                const c2<T> h = t >= d ? n[t >= d ? t - d : 0][j] : hist[d > t ? d - t - 1 : 0][j];
+                                st[2 * d - 2] = fma(x[j].x, h.x, fma(x[j].y, h.y, st[2 * d - 2]));
+                                st[2 * d - 1] = fma(x[j].x, h.y, fma(-x[j].y, h.x, st[2 * d - 1]));
+                            }
                         }
                     }
 #pragma unroll
-                    for (int d = 1; d <= RM; ++d) {
-#pragma unroll
-                        for (int j = 0; j < NST; ++j) {
-                            const c2<T> h = t - d >= 0 ? n[t - d >= 0 ? t - d : 0][j] : hist[u][d - t - 1 >= 0 ? d - t - 1 : 0][j];
-                            st[2 * d - 2] += x[j].x * h.x + x[j].y * h.y;
-                            st[2 * d - 1] += x[j].x * h.y - x[j].y * h.x;
-                        }
-                    }
+                    for (int k = 0; k < 2 * RM; ++k) acc[k] += (double)st[k];
                 }
-#pragma unroll
-                for (int k = 0; k < 2 * RM; ++k) acc[u][k] += (double)st[k];
-                // the step's last RM segments become the history (kLagSegs >= RM)
+            }
+            // the step's last RM segments become the history (kLagSegs >= RM)
+            if constexpr (RM > 0) {
 #pragma unroll
                 for (int d = 0; d < RM; ++d)
 #pragma unroll
-                    for (int j = 0; j < NST; ++j) hist[u][d][j] = n[kLagSegs - 1 - d][j];
+                    for (int j = 0; j < NST; ++j) hist[d][j] = n[kLagSegs - 1 - d][j];
             }
         }
         __syncthreads();
-        mask = nmask;
     }
+    if ((int)threadIdx.x >= span) return;
     const int nc = 2 * R + 1;
-    double *o = part + (((size_t)tb * n_chunks + c) * G.n_sub + sub) * nc * P * span + (size_t)p * span;
+    double *o = part + (((size_t)tb * n_chunks + c) * G.n_sub + sub) * nc * P * span + (size_t)p * span + threadIdx.x;
+    o[0] = acc0;
+    if constexpr (RM > 0) {
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-        const int col = threadIdx.x + 64 * W * u;
-        if (col >= span) continue;
-        o[col] = acc0[u];
-        if constexpr (RM > 0) {
-#pragma unroll
-            for (int k = 0; k < 2 * RM; ++k)
-                if (k + 1 < nc) o[(size_t)(k + 1) * P * span + col] = acc[u][k];
-        }
+        for (int k = 0; k < 2 * RM; ++k)
+            if (k + 1 < nc) o[(size_t)(k + 1) * P * span] = acc[k];
     }
 }
 
 // Blocks of an item: G = n_tmpl n_chunks n_sub groups of P class workgroups; the dispatcher
 // hands workgroups to the 8 XCDs in turn, so a group's classes get indices with equal value mod
 // 8 and read the group's resampled series through one XCD's L2.
-template <typename T, int NS, int U, int RM, bool CR, bool PS>
-__global__ void __launch_bounds__(512)
+template <typename T, int NS, int RM, bool CR, bool PS, int CM>
+__global__ void __launch_bounds__(lag_max_threads(NS, sizeof(T) == 8))
 k_lag(const BandDev *__restrict__ bands, const WorkItem *__restrict__ items, int n_items,
       const c2<T> *__restrict__ y, double *__restrict__ part) {
     const WorkItem &it = items[find_item(items, n_items, kStSpectra, blockIdx.x)];
@@ -514,17 +576,35 @@ k_lag(const BandDev *__restrict__ bands, const WorkItem *__restrict__ items, int
         p = (l - full) % P;
     }
     const int per = it.n_chunks * B.lag.n_sub;
-    lag_body<T, NS, U, RM, CR, PS>(B, y + it.y_off, part + it.part_off, it.k_chunk, it.n_chunks,
+    lag_body<T, NS, RM, CR, PS, CM>(B, y + it.y_off, part + it.part_off, it.k_chunk, it.n_chunks,
                                    (g % per) / B.lag.n_sub, g % B.lag.n_sub, p, g / per);
 }
 
 // ------------------------------------------------------------------ interpolation to the output bins
 
-// rho of kLagFinThreads * bpt consecutive bins of one template: per lag, the chunk (and
-// detector) partials of the grid columns the block's bins reach are summed into LDS, then each
-// bin takes its `taps`-point interpolation (weights by the bin's fraction of a grid step, exact
-// to LagDev's design error) and adds Re (Gamma^circ: Im) of e^{2 pi i kbar d N_K / N_FFT} S_d.
-// Sums in FP64, in chunk order.
+// Sum of a template's chunk (and detector) partials into the first one, one thread per component
+// and column, in chunk order.  A kernel of its own: a bin's interpolation reaches ~100 columns, so
+// summing them where they are used read every partial 4 times over and left calls of few templates
+// on a few workgroups.
+__global__ void __launch_bounds__(kLagFinThreads)
+k_lag_reduce(const BandDev *__restrict__ bands, const WorkItem *__restrict__ items, int n_items,
+             double *__restrict__ part_) {
+    const WorkItem &it = items[find_item(items, n_items, kStPairs, blockIdx.x)];
+    const LagDev &G = bands[it.band].lag;
+    const int l = blockIdx.x - it.first[kStPairs], gx = it.gx[kStPairs];
+    const int n = (2 * bands[it.band].R + 1) * G.P * G.span, np = it.n_chunks * G.n_sub;
+    const int x = (l % gx) * kLagFinThreads + threadIdx.x;
+    if (x >= n) return;
+    double *o = part_ + it.part_off + (size_t)(l / gx) * np * n + x;
+    double v = 0.0;
+#pragma unroll 8
+    for (int k = 0; k < np; ++k) v += o[(size_t)k * n];
+    o[0] = v;
+}
+
+// rho of kLagFinThreads consecutive bins of one template: per lag, the grid columns the block's
+// bins reach go to LDS, then each bin takes its `taps`-point interpolation (weights by the bin's
+// fraction of a grid step) and adds Re (Gamma^circ: Im) of e^{2 pi i kbar d N_K / N_FFT} S_d.
 __global__ void __launch_bounds__(kLagFinThreads)
 k_lag_finish(const BandDev *__restrict__ bands, const WorkItem *__restrict__ items, int n_items,
              const double *__restrict__ part_) {
@@ -533,82 +613,74 @@ k_lag_finish(const BandDev *__restrict__ bands, const WorkItem *__restrict__ ite
     const BandDev B = global_view(bands[it.band], bands);
     const LagDev &G = B.lag;
     const int l = blockIdx.x - it.first[kStFinish], gx = it.gx[kStFinish];
-    const int t = l / gx, bpt = G.fin_bpt;
-    const int b0 = (l % gx) * kLagFinThreads * bpt, b1 = min(B.n_f, b0 + kLagFinThreads * bpt);
+    const int t = l / gx, b0 = (l % gx) * kLagFinThreads, b1 = min(B.n_f, b0 + kLagFinThreads);
     const int r0 = G.g0[b0], ncol = G.g0[b1 - 1] + G.taps - r0;
-    const int R = B.R, P = G.P, span = G.span, nc = 2 * R + 1, np = it.n_chunks * G.n_sub;
+    const int R = B.R, P = G.P, span = G.span;
     const size_t plane = (size_t)P * span;
-    const double *part = part_ + it.part_off + (size_t)t * np * nc * plane;
+    const double *part = part_ + it.part_off + (size_t)t * it.n_chunks * G.n_sub * (2 * R + 1) * plane;
     double2 *S = reinterpret_cast<double2 *>(smem);
-    double rho[kLagFinBins];
-#pragma unroll
-    for (int k = 0; k < kLagFinBins; ++k) rho[k] = 0.0;
+    const int i = min(b0 + (int)threadIdx.x, b1 - 1);
+    const double *w = G.wt + (size_t)G.frac[i] * G.taps;
+    const double2 *s = S + (G.g0[i] - r0);
+    double rho = 0.0;
     for (int d = 0; d <= R; ++d) {
         for (int x = threadIdx.x; x < ncol; x += kLagFinThreads) {
             int rel = r0 + x;
             if (G.wrap) rel %= G.ng;
             const double *src = part + (size_t)(d == 0 ? 0 : 2 * d - 1) * plane + (size_t)(rel % P) * span + rel / P;
-            double re = 0.0, im = 0.0;
-            for (int k = 0; k < np; ++k) {
-                re += src[(size_t)k * nc * plane];
-                if (d > 0) im += src[(size_t)k * nc * plane + plane];
-            }
-            S[x] = make_double2(re, im);
+            S[x] = make_double2(src[0], d > 0 ? src[plane] : 0.0);
         }
         __syncthreads();
-#pragma unroll
-        for (int k = 0; k < kLagFinBins; ++k) {
-            const int i = b0 + threadIdx.x + kLagFinThreads * k;
-            if (k >= bpt || i >= b1) continue;
-            const double *w = G.wt + (size_t)G.frac[i] * G.taps;
-            const double2 *s = S + (G.g0[i] - r0);
-            double re = 0.0, im = 0.0;
-            for (int j = 0; j < G.taps; ++j) {
-                re = fma(w[j], s[j].x, re);
-                im = fma(w[j], s[j].y, im);
-            }
-            if (d == 0) {
-                rho[k] = re;
-            } else {
-                const int e = (int)(((int64_t)B.bin_kb[i] * (((int64_t)d * B.n_k) % B.n_fft)) % B.n_fft);
-                const double2 ph = B.tw64[e];  // exp(-2 pi i e / N_FFT)
-                rho[k] += B.weight != 0 ? im * ph.x - re * ph.y : re * ph.x + im * ph.y;
-            }
+        double re = 0.0, im = 0.0;
+#pragma unroll 4
+        for (int j = 0; j < G.taps; ++j) {
+            re = fma(w[j], s[j].x, re);
+            im = fma(w[j], s[j].y, im);
+        }
+        if (d == 0) {
+            rho = re;
+        } else {
+            const int e = (int)(((int64_t)B.bin_kb[i] * (((int64_t)d * B.n_k) % B.n_fft)) % B.n_fft);
+            const double2 ph = B.tw64[e];  // exp(-2 pi i e / N_FFT)
+            rho += B.weight != 0 ? im * ph.x - re * ph.y : re * ph.x + im * ph.y;
         }
         __syncthreads();
     }
+    if (b0 + (int)threadIdx.x >= b1) return;
     void *out = as_global(it.out, (const gchar *)part_);
-#pragma unroll
-    for (int k = 0; k < kLagFinBins; ++k) {
-        const int i = b0 + threadIdx.x + kLagFinThreads * k;
-        if (k >= bpt || i >= b1) continue;
-        const double v = rho[k] * it.factor;
-        if (it.out_fp64) static_cast<double *>(out)[(size_t)t * B.n_f + i] = v;
-        else static_cast<float *>(out)[(size_t)t * B.n_f + i] = (float)v;
-    }
+    const double v = rho * it.factor;
+    if (it.out_fp64) static_cast<double *>(out)[(size_t)t * B.n_f + i] = v;
+    else static_cast<float *>(out)[(size_t)t * B.n_f + i] = (float)v;
 }
 
 }  // namespace
 
 // ------------------------------------------------------------------ launchers
 
-template <typename T, int NS, int U>
+template <typename T, int NS>
 static void launch_lag_t(const LagKey &k, const BandDev *bands, const WorkItem *items, int n_items, int blocks,
                          size_t lds, const void *y, double *part, hipStream_t stream) {
-#define CCR_LAG(RM_, CR_, PS_)                                                                                        \
-    hipLaunchKernelGGL((k_lag<T, NS, U, RM_, CR_, PS_>), dim3(blocks), dim3(64 * k.waves), lds, stream, bands, items, \
-                       n_items, (const c2<T> *)y, part)
-    if (k.cross) {
-        if (k.ps) CCR_LAG(4, true, true);
-        else CCR_LAG(4, true, false);
-    } else if (k.ps) {
-        if (k.rm == 0) CCR_LAG(0, false, true);
-        else CCR_LAG(4, false, true);
+#define CCR_LAG(RM_, CR_, PS_, CM_)                                                                              \
+    hipLaunchKernelGGL((k_lag<T, NS, RM_, CR_, PS_, CM_>), dim3(blocks), dim3(64 * k.waves), lds, stream, bands, \
+                       items, n_items, (const c2<T> *)y, part)
+    // the weight is compiled in for pairs of both kinds with per-segment weights; the other forms
+    // run transforms of up to 512 points (the planner's choice)
+    if (k.cross || k.ps) {
+        if constexpr (NS <= 512) {
+            if (k.cross && k.ps) CCR_LAG(4, true, true, 2);
+            else if (k.cross) CCR_LAG(4, true, false, 2);
+            else if (k.rm == 0) CCR_LAG(0, false, true, 2);
+            else CCR_LAG(4, false, true, 2);
+        }
+    } else if (k.circ) {
+        if (k.rm == 0) CCR_LAG(0, false, false, 1);
+        else if (k.rm == 1) CCR_LAG(1, false, false, 1);
+        else CCR_LAG(4, false, false, 1);
     } else {
-        if (k.rm == 0) CCR_LAG(0, false, false);
-        else if (k.rm == 1) CCR_LAG(1, false, false);
-        else if (k.rm == 2) CCR_LAG(2, false, false);
-        else CCR_LAG(4, false, false);
+        if (k.rm == 0) CCR_LAG(0, false, false, 0);
+        else if (k.rm == 1) CCR_LAG(1, false, false, 0);
+        else if (k.rm == 2) CCR_LAG(2, false, false, 0);
+        else CCR_LAG(4, false, false, 0);
     }
 #undef CCR_LAG
 }
@@ -617,21 +689,23 @@ hipError_t launch_lag_m(const LagKey &k, const BandDev *bands, const WorkItem *i
                         bool fp64, size_t lds, const void *y, double *part, hipStream_t stream) {
     if (blocks == 0) return hipSuccess;
     if (fp64) {
-        if (k.ns == 512) launch_lag_t<double, 512, 1>(k, bands, items, n_items, blocks, lds, y, part, stream);
-        else if (k.ns == 256) launch_lag_t<double, 256, 1>(k, bands, items, n_items, blocks, lds, y, part, stream);
+        if (k.ns == 512) launch_lag_t<double, 512>(k, bands, items, n_items, blocks, lds, y, part, stream);
+        else if (k.ns == 256) launch_lag_t<double, 256>(k, bands, items, n_items, blocks, lds, y, part, stream);
         else return hipErrorInvalidValue;
     } else {
-        if (k.ns == 1024) launch_lag_t<float, 1024, 2>(k, bands, items, n_items, blocks, lds, y, part, stream);
-        else if (k.ns == 512) launch_lag_t<float, 512, 1>(k, bands, items, n_items, blocks, lds, y, part, stream);
-        else if (k.ns == 256) launch_lag_t<float, 256, 1>(k, bands, items, n_items, blocks, lds, y, part, stream);
+        if (k.ns == 1024) launch_lag_t<float, 1024>(k, bands, items, n_items, blocks, lds, y, part, stream);
+        else if (k.ns == 512) launch_lag_t<float, 512>(k, bands, items, n_items, blocks, lds, y, part, stream);
+        else if (k.ns == 256) launch_lag_t<float, 256>(k, bands, items, n_items, blocks, lds, y, part, stream);
         else return hipErrorInvalidValue;
     }
     return hipGetLastError();
 }
 
-hipError_t launch_lag_finish_m(const BandDev *bands, const WorkItem *items, int n_items, int blocks, size_t lds,
-                               const double *part, hipStream_t stream) {
+hipError_t launch_lag_finish_m(const BandDev *bands, const WorkItem *items, int n_items, int reduce_blocks,
+                               int blocks, size_t lds, double *part, hipStream_t stream) {
     if (blocks == 0) return hipSuccess;
+    if (reduce_blocks > 0)
+        hipLaunchKernelGGL(k_lag_reduce, dim3(reduce_blocks), dim3(kLagFinThreads), 0, stream, bands, items, n_items, part);
     hipLaunchKernelGGL(k_lag_finish, dim3(blocks), dim3(kLagFinThreads), lds, stream, bands, items, n_items, part);
     return hipGetLastError();
 }
