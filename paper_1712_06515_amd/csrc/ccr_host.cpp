@@ -1851,7 +1851,7 @@ ccr_status run_rounds(ccr_ctx *c, const CallPlan &cp, size_t r0, size_t r1, bool
         {
             LaunchTimer lt(c, 0, s, timing);
             HIP_OK(c, launch_resample_m(db, di, r.n, (int)r.blocks[kStResample], fp64, r.v.DT, r.v.window,
-                                        r.v.n_cheb, r.v.far, coef, ws.y, s));
+                                        r.v.n_cheb, r.v.far, r.v.wps, coef, ws.y, s));
         }
         if (r.v.fold) {
             LaunchTimer lt(c, 7, s, timing);
@@ -2150,7 +2150,7 @@ static ccr_status split_series_of(ccr_ctx *c, int band_id, int64_t template_inde
     HIP_OK(c, launch_zero(ws.y, r.y_bytes, s));
     HIP_OK(c, launch_timebase_m(db, di, r.n, (int)r.blocks[kStTimebase], r.v.n_cheb, r.v.ss, ws.coef, s));
     HIP_OK(c, launch_resample_m(db, di, r.n, (int)r.blocks[kStResample], false, r.v.DT, r.v.window, r.v.n_cheb,
-                                r.v.far, ws.coef, ws.y, s));
+                                r.v.far, false, ws.coef, ws.y, s));
     *y_dev = ws.y;
     return CCR_OK;
 }

@@ -224,9 +224,10 @@ hipError_t launch_timebase_m(const BandDev *bands, const WorkItem *items, int n_
                              bool short_series, double *coef,
                              hipStream_t stream);
 // farrow: the split-precision Farrow-form kernel (bands with a table; kFarTemplates templates a
-// workgroup); else one wavefront per kResTemplates templates.
+// workgroup; ps2: two weighted series a detector); else one wavefront per kResTemplates templates.
 hipError_t launch_resample_m(const BandDev *bands, const WorkItem *items, int n_items, int blocks, bool fp64, int D,
-                             int window, int n_cheb, bool farrow, const double *coef, void *y, hipStream_t stream);
+                             int window, int n_cheb, bool farrow, bool ps2, const double *coef, void *y,
+                             hipStream_t stream);
 // The Farrow table of a band (BandDev::farrow) from its input series x [Q][n] and the fitted
 // coefficients A [kFarDeg][2D + 1] (row k - 1 for the power dc^k).
 hipError_t launch_farrow_table(const float2 *x, int64_t n, int Q, int D, const double *A, int64_t far_len,

@@ -654,7 +654,7 @@ __device__ __forceinline__ float2 farrow_eval_global(const float2 *p, int64_t st
 // kFarCap (not met for physical delays) reads the table in global memory instead.  The gap
 // mask and the in-chunk test of each pass are wave-wide bit masks (ballots), applied as
 // execution masks.
-template <int NC>
+template <int NC, bool PS2>
 __device__ __forceinline__ void resample_far_body(const BandDev &B, const double *coef, float2 *y, int w, int t0,
                                                   int t1) {
     constexpr int kE = kFarDeg + 1;          // coefficients of an entry
@@ -668,8 +668,14 @@ __device__ __forceinline__ void resample_far_body(const BandDev &B, const double
     const uint8_t *mk_ = B.mask + (size_t)det * nr + (size_t)K * B.n_k;
     const float2 *tab = B.farrow + (size_t)det * (kFarDeg + 1) * B.far_len;
     const Anchor an = B.anchors[entry];
-    const double psi_b = __builtin_amdgcn_fract(fma(B.f_het, an.D_a, an.psi_a));
+    double psi_b = __builtin_amdgcn_fract(fma(B.f_het, an.D_a, an.psi_a));
     const double inv_nk = 1.0 / (double)B.n_k;
+    // uniform values of every pass, held in vector registers: as scalars they were spilled and read
+    // back lane by lane each pass (with the fallback's address arithmetic moved off the common path,
+    // 57 -> 40 vector instructions a pass; 4-6 % where the series stays in the caches.  A 12 GB
+    // series stays at 4.0 ms: its stores alone take 3.65 ms, the arithmetic alone 2.0)
+    double inv_dt = B.inv_dt, f_het = B.f_het;
+    asm("" : "+v"(inv_dt), "+v"(f_het), "+v"(psi_b));
     const int64_t r0 = (int64_t)K * B.n_k;
     // wave-uniform (readfirstlane), so that a template's time-base coefficients are scalar
     // loads: a vector load's wait would also wait for the previous pass's stores
@@ -689,7 +695,7 @@ __device__ __forceinline__ void resample_far_body(const BandDev &B, const double
                 cl[0] -= an.D_a;
                 const int s = lane < 32 ? c0 : c1 - 1;
                 float dc, psi;
-                sample_time_far<NC>(cl, (double)(2 * s - B.n_k) * inv_nk, B.inv_dt, B.f_het, psi_b, jr, dc, psi);
+                sample_time_far<NC>(cl, (double)(2 * s - B.n_k) * inv_nk, inv_dt, f_het, psi_b, jr, dc, psi);
                 jr += s;
             }
             int lo = INT_MAX, hi = INT_MIN;
@@ -747,17 +753,17 @@ __device__ __forceinline__ void resample_far_body(const BandDev &B, const double
         }
         __syncthreads();
         // STAGED (uniform per chunk): j* lies in the staged range (j* is nondecreasing over the
-        // chunk and the range spans its first and last samples), so every lane reads LDS at a
-        // clamped index; lanes outside the range, if a wave has any (a uniform test), take the
-        // global-memory form instead.  Otherwise every sample reads the table in global memory.
+        // chunk and the range spans its first and last samples), so every lane reads LDS; a pass
+        // with a lane outside the range, if there is any (a uniform test), takes the global-memory
+        // form instead.  Otherwise every sample reads the table in global memory.
         auto walk = [&](auto staged_c) {
             constexpr bool STAGED = decltype(staged_c)::value;
+#pragma unroll 1
             for (int i = 0; i < kFarPerWave; ++i) {
                 const int tb = tw0 + i;
                 if (tb >= t1) break;
                 // the series, or with per-sample weights its two streams y a_r and y b_r
-                const int ns2 = B.ps2 ? 2 : 1;
-                float2 *yo = y + ((size_t)tb * B.Q + det) * ns2 * nr + r0;
+                float2 *yo = y + ((size_t)tb * B.Q + det) * (PS2 ? 2 : 1) * nr + r0;
                 const double *cf = coef + ((size_t)tb * B.n_work + w) * kCheb;
                 double cl[NC];
 #pragma unroll
@@ -766,42 +772,42 @@ __device__ __forceinline__ void resample_far_body(const BandDev &B, const double
                 // buffer stores: a uniform resource per stream and the sample's byte offset (no
                 // 64-bit address arithmetic per pass); the range is the segment's n_k samples
                 const __amdgpu_buffer_rsrc_t yb0 = __builtin_amdgcn_make_buffer_rsrc(yo, (short)0, B.n_k * 8, 0x00020000);
-                const __amdgpu_buffer_rsrc_t yb1 = __builtin_amdgcn_make_buffer_rsrc(yo + nr, (short)0, B.n_k * 8, 0x00020000);
-                auto put = [](const __amdgpu_buffer_rsrc_t &rs, unsigned idx, float2 v) {
-                    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), rs, (int)(idx * 8u), 0, 0);
+                auto put = [](const __amdgpu_buffer_rsrc_t &rs, int off, float2 v) {
+                    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), rs, off, 0, 0);
                 };
 #pragma unroll
                 for (int p = 0; p < kPasses; ++p) {
                     if (c0 + 64 * p >= c1) break;
-                    const unsigned so = (unsigned)(c0 + 64 * p + lane);  // sample index (32-bit offset from yo)
+                    const int so = (c0 + 64 * p + lane) * 8;  // byte offset of the sample from yo
                     // samples in gaps: zero (their own execution mask)
-                    if (__builtin_amdgcn_inverse_ballot_w64(in_b[p] & ~m_b[p])) {
-                        put(yb0, so, make_float2(0.f, 0.f));
-                        if (B.ps2) put(yb1, so, make_float2(0.f, 0.f));
+                    if (in_b[p] & ~m_b[p]) {
+                        if (__builtin_amdgcn_inverse_ballot_w64(in_b[p] & ~m_b[p])) {
+                            put(yb0, so, make_float2(0.f, 0.f));
+                            if constexpr (PS2)
+                                put(__builtin_amdgcn_make_buffer_rsrc(yo + nr, (short)0, B.n_k * 8, 0x00020000), so,
+                                    make_float2(0.f, 0.f));
+                        }
                     }
                     if (__builtin_amdgcn_inverse_ballot_w64(m_b[p])) {
                         int jr;
                         float dc, psi;
-                        sample_time_far<NC>(cl, xs[p], B.inv_dt, B.f_het, psi_b, jr, dc, psi);
+                        sample_time_far<NC>(cl, xs[p], inv_dt, f_het, psi_b, jr, dc, psi);
                         jr += sj[p];  // j* - r0 - jlo
                         float2 a;
-                        bool far = true;
-                        if constexpr (STAGED) {
-                            const bool in_range = (unsigned)jr < (unsigned)span;
-                            a = farrow_eval_lds(sf + __umul24(min((unsigned)jr, (unsigned)span - 1u), kES), dc);
-                            far = __builtin_amdgcn_ballot_w64(!in_range) != 0 && !in_range;
-                        }
-                        if (far) {
+                        if (STAGED && __builtin_expect(__builtin_amdgcn_ballot_w64((unsigned)jr >= (unsigned)span) == 0, 1)) {
+                            a = farrow_eval_lds(sf + __umul24((unsigned)jr, kES), dc);
+                        } else {
                             const int64_t jj = r0 + jlo + jr + B.D;
                             a = (jj >= 0 && jj < B.far_len) ? farrow_eval_global(tab + jj, B.far_len, dc)
                                                              : make_float2(0.f, 0.f);
                         }
                         const float c = __builtin_amdgcn_cosf(psi), sn = __builtin_amdgcn_sinf(psi);
                         const float2 yv = make_float2(c * a.x - sn * a.y, sn * a.x + c * a.y);
-                        if (B.ps2) {
-                            const float2 wr = B.pwf[(size_t)det * nr + r0 + so];
+                        if constexpr (PS2) {
+                            const float2 wr = B.pwf[(size_t)det * nr + r0 + c0 + 64 * p + lane];
                             put(yb0, so, make_float2(yv.x * wr.x, yv.y * wr.x));
-                            put(yb1, so, make_float2(yv.x * wr.y, yv.y * wr.y));
+                            put(__builtin_amdgcn_make_buffer_rsrc(yo + nr, (short)0, B.n_k * 8, 0x00020000), so,
+                                make_float2(yv.x * wr.y, yv.y * wr.y));
                         } else {
                             put(yb0, so, yv);
                         }
@@ -817,7 +823,7 @@ __device__ __forceinline__ void resample_far_body(const BandDev &B, const double
 
 __global__ void __launch_bounds__(256) k_resample_far(BandDev B, const double *coef, float2 *y, int n_tmpl) {
     const int t0 = blockIdx.y * kFarTemplates;
-    resample_far_body<kCheb>(B, coef, y, blockIdx.x, t0, min(n_tmpl, t0 + kFarTemplates));
+    resample_far_body<kCheb, false>(B, coef, y, blockIdx.x, t0, min(n_tmpl, t0 + kFarTemplates));
 }
 
 // Time base samples of one detector's segments [k0, k0 + n) for one template (stage output).
@@ -2391,7 +2397,7 @@ k_resample_m(const BandDev *__restrict__ bands, const WorkItem *__restrict__ ite
                                   min(it.n_tmpl, t0 + kResTemplates));
 }
 
-template <int NC>
+template <int NC, bool PS2>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8)))
 k_resample_far_m(const BandDev *__restrict__ bands, const WorkItem *__restrict__ items, int n_items,
                  const double *__restrict__ coef, float2 *__restrict__ y) {
@@ -2407,7 +2413,7 @@ k_resample_far_m(const BandDev *__restrict__ bands, const WorkItem *__restrict__
     const int full = (B.n_work * tiles) & ~7;  // the item's blocks: n_work segment entries x tiles
     const int v = l < full ? (l & 7) * (full >> 3) + (l >> 3) : l;
     const int t0 = (v % tiles) * kFarTemplates;
-    resample_far_body<NC>(B, coef + it.coef_off, y + it.y_off, v / tiles, t0, min(it.n_tmpl, t0 + kFarTemplates));
+    resample_far_body<NC, PS2>(B, coef + it.coef_off, y + it.y_off, v / tiles, t0, min(it.n_tmpl, t0 + kFarTemplates));
 }
 
 template <int NR, bool Z4>
@@ -2798,21 +2804,24 @@ static void launch_resample_m_t(const BandDev *bands, const WorkItem *items, int
 }
 
 hipError_t launch_resample_m(const BandDev *bands, const WorkItem *items, int n_items, int blocks, bool fp64, int D,
-                             int window, int n_cheb, bool farrow, const double *coef, void *y, hipStream_t stream) {
+                             int window, int n_cheb, bool farrow, bool ps2, const double *coef, void *y,
+                             hipStream_t stream) {
     if (blocks == 0) return hipSuccess;
     if (farrow && !fp64) {
-        if (n_cheb == kChebSplitLow)
-            hipLaunchKernelGGL(k_resample_far_m<kChebSplitLow>, dim3(blocks), dim3(256), 0, stream, bands, items,
-                               n_items, coef, (float2 *)y);
-        else if (n_cheb == kChebSplitMin)
-            hipLaunchKernelGGL(k_resample_far_m<kChebSplitMin>, dim3(blocks), dim3(256), 0, stream, bands, items,
-                               n_items, coef, (float2 *)y);
-        else if (n_cheb == kChebSplit)
-            hipLaunchKernelGGL(k_resample_far_m<kChebSplit>, dim3(blocks), dim3(256), 0, stream, bands, items,
-                               n_items, coef, (float2 *)y);
-        else
-            hipLaunchKernelGGL(k_resample_far_m<kCheb>, dim3(blocks), dim3(256), 0, stream, bands, items, n_items,
-                               coef, (float2 *)y);
+#define CCR_FAR(NC_)                                                                                                  \
+    do {                                                                                                              \
+        if (ps2)                                                                                                      \
+            hipLaunchKernelGGL((k_resample_far_m<NC_, true>), dim3(blocks), dim3(256), 0, stream, bands, items,       \
+                               n_items, coef, (float2 *)y);                                                           \
+        else                                                                                                          \
+            hipLaunchKernelGGL((k_resample_far_m<NC_, false>), dim3(blocks), dim3(256), 0, stream, bands, items,      \
+                               n_items, coef, (float2 *)y);                                                           \
+    } while (0)
+        if (n_cheb == kChebSplitLow) CCR_FAR(kChebSplitLow);
+        else if (n_cheb == kChebSplitMin) CCR_FAR(kChebSplitMin);
+        else if (n_cheb == kChebSplit) CCR_FAR(kChebSplit);
+        else CCR_FAR(kCheb);
+#undef CCR_FAR
     } else if (fp64) {
         if (D == 8) launch_resample_m_t<double, 8, kCheb>(bands, items, n_items, blocks, window, coef, y, stream);
         else launch_resample_m_t<double, 0, kCheb>(bands, items, n_items, blocks, window, coef, y, stream);
