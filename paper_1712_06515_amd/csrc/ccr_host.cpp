@@ -1597,7 +1597,7 @@ constexpr int64_t kMaxBlocks = ((int64_t)1 << 31) - 1;
 int64_t stage_max_blocks(const Variant &v, int st) {
     int threads = 64;
     if (st == kStTimebase) threads = tb_entries(v.n_cheb) * v.n_cheb;
-    else if (st == kStResample) threads = v.far ? 256 : 64;
+    else if (st == kStResample) threads = v.far || (v.n_cheb == kCheb && resample64_ok(v.DT, v.window)) ? 256 : 64;
     else if (st == kStSpectra && v.fold) threads = kFoldThreads;
     else if (st == kStSpectra) threads = v.lag ? 64 * v.lk.waves : v.sp ? 64 : (v.wide ? 64 * v.wwv : (v.reg16 ? 128 : spectra_threads(v.n_s)));
     else if (st == kStPairs) threads = v.fold ? kFoldThreads : (v.lag ? kLagFinThreads : kPairsThreads);

@@ -184,6 +184,11 @@ constexpr int kSpec16Groups = 8;     // 256-point register FFT: segments per 128
 constexpr int kPairsThreads = 128;   // pair sum: bins per workgroup
 constexpr int kFinishThreads = 256;  // finish: bins per workgroup
 constexpr int kResTemplates = 4;     // resampling: templates per workgroup
+// FP64 resampling with 8 taps each side and the tap-indexed window (the default band): a
+// 256-thread workgroup stages a segment's input (at most kRes64Win entries; segments hold at most
+// 2048 samples) for kResTemplates templates; other taps and windows: a wavefront each
+constexpr int kRes64Win = 2176;
+inline bool resample64_ok(int D, int window) { return D == 8 && window == 0; }
 // Farrow-form resampling (split precision): tap weights as polynomials of degree kFarDeg in the
 // offset; a 256-thread workgroup (kFarWaves wavefronts, kFarPerWave templates each) stages the
 // table planes of chunks of kFarChunk samples of one segment in LDS (kFarCap entries a plane)

@@ -543,6 +543,143 @@ __device__ __forceinline__ void resample_body(const BandDev &B, const double *co
     }
 }
 
+// Windowed-sinc sum of the FP64 path with D = 8 taps each side and the tap-indexed window
+// (symmetric, centre weight 1): with s = sin(pi dc) / pi and cw_n = (-1)^n w_n,
+//   y = s sum_n cw_n x_n / (dc - n),   1 / (dc -+ n) = (dc +- n) / (dc^2 - n^2),
+// so the 17 divisions become one: the eight dc^2 - n^2 (in [-64, -3/4]) are inverted together from
+// the reciprocal of their product (prefix products, then back).  s / dc = sinc(dc) is its Taylor
+// series in dc^2 (through dc^20: 1e-18 at |dc| = 1/2), which also gives the centre tap without
+// dividing by dc.  Rounding: a few 1e-16 of the sum's terms, as for the divisions.
+__device__ __forceinline__ double2 interpolate64_d8(const double *cw, const float2 *xc, double dc) {
+    const double z = dc * dc;
+    // (-1)^k pi^(2k) / (2k + 1)!
+    constexpr double kSinc[11] = {1.0,
+                                  -1.6449340668482264365,
+                                  0.81174242528335364364,
+                                  -0.19075182412208421369,
+                                  0.026147847817654800505,
+                                  -0.0023460810354558236375,
+                                  0.00014842879303107100368,
+                                  -6.9758736616563804745e-06,
+                                  2.5312174041370276513e-07,
+                                  -7.3047118222177748e-09,
+                                  1.7165384749821433e-10};
+    double sinc = kSinc[10];
+#pragma unroll
+    for (int k = 9; k >= 0; --k) sinc = fma(sinc, z, kSinc[k]);
+    double P[9], pre[9];
+    pre[0] = 1.0;
+#pragma unroll
+    for (int n = 1; n <= 8; ++n) {
+        P[n] = z - (double)(n * n);
+        pre[n] = n == 1 ? P[1] : pre[n - 1] * P[n];
+    }
+    double inv = __builtin_amdgcn_rcp(pre[8]);
+    inv = fma(inv, fma(-pre[8], inv, 1.0), inv);
+    inv = fma(inv, fma(-pre[8], inv, 1.0), inv);
+    double re = 0.0, im = 0.0;
+#pragma unroll
+    for (int n = 8; n >= 1; --n) {
+        const double r = n > 1 ? inv * pre[n - 1] : inv;  // 1 / (dc^2 - n^2)
+        if (n > 1) inv *= P[n];
+        const double c = cw[n + 8] * r, cn = c * (double)n;
+        const double qp = fma(c, dc, cn), qm = fma(c, dc, -cn);  // cw_n / (dc - n), cw_n / (dc + n)
+        const float2 xp = xc[n], xm = xc[-n];
+        re = fma(qp, (double)xp.x, re);
+        im = fma(qp, (double)xp.y, im);
+        re = fma(qm, (double)xm.x, re);
+        im = fma(qm, (double)xm.y, im);
+    }
+    const float2 x0 = xc[0];
+    const double s = dc * sinc;
+    return make_double2(fma(s, re, sinc * (double)x0.x), fma(s, im, sinc * (double)x0.y));
+}
+
+// FP64 resampling for D = 8 and the tap-indexed window: one 256-thread workgroup per (active
+// segment, kResTemplates templates).  The segment's input, over the range of j* of its templates
+// (their delays differ by a few samples), and its gap mask are staged in LDS once; the wavefronts
+// then share the (template, 64-sample pass) pairs with no global reads but the coefficients.
+// Bound: VALU issue (FP64 arithmetic, ~250 instructions a pass).  Against one wavefront per segment
+// that loads each pass's window and divides per tap: 5 templates of 120 days at T_short 1440 s 1.61
+// -> 0.94 ms, 12 of the 120-day band at 200 Hz 0.79 -> 0.51 ms.  A range wider than the LDS window reads
+// each sample's taps from global memory.
+template <int NC>
+__device__ __forceinline__ void resample64_body(const BandDev &B, const double *coef, double2 *y, int w, int t0,
+                                                int t1) {
+    __shared__ float2 win[kRes64Win];
+    __shared__ uint8_t msk[kRes64Win];
+    constexpr int D = 8;
+    const int entry = B.work[w];
+    const int det = entry / B.n_seg;
+    const int K = entry - det * B.n_seg;
+    const int64_t nr = (int64_t)B.n_seg * B.n_k, r0 = (int64_t)K * B.n_k;
+    const uint8_t *mk_ = B.mask + (size_t)det * nr + r0;
+    const float2 *xd = B.x + (size_t)det * B.n;
+    const Anchor an = B.anchors[entry];
+    const double inv_nk = 1.0 / (double)B.n_k;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    double cw[2 * D + 1];
+    load_signed_window<double, D>(B, cw);
+    // range of j* - r0 over the templates: lanes i evaluate template t0 + i at the first sample
+    // (lanes 32 + i: at the last); every wavefront does the same
+    int lo = INT_MAX, hi = INT_MIN;
+    {
+        const int i = lane & 31;
+        int jr = 0;
+        if (i < kResTemplates && t0 + i < t1) {
+            const double *cf = coef + ((size_t)(t0 + i) * B.n_work + w) * kCheb;
+            double cl[NC];
+#pragma unroll
+            for (int k = 0; k < NC; ++k) cl[k] = cf[k];
+            const int s = lane < 32 ? 0 : B.n_k - 1;
+            int64_t js;
+            double dc, psi;
+            sample_time<NC>(cl, (double)(2 * s - B.n_k) * inv_nk, an, B.inv_dt, B.f_het, r0 + s, js, dc, psi);
+            jr = (int)(js - r0);
+        }
+#pragma unroll
+        for (int q = 0; q < kResTemplates; ++q)
+            if (t0 + q < t1) {
+                lo = min(lo, __builtin_amdgcn_readlane(jr, q));
+                hi = max(hi, __builtin_amdgcn_readlane(jr, 32 + q));
+            }
+    }
+    lo -= D;
+    hi += D;
+    const bool staged = hi - lo < kRes64Win;
+    if (staged)
+        for (int k = threadIdx.x; k <= hi - lo; k += 256) {
+            const int64_t j = r0 + lo + k;
+            win[k] = (j >= 0 && j < B.n) ? xd[j] : make_float2(0.f, 0.f);
+        }
+    for (int k = threadIdx.x; k < B.n_k; k += 256) msk[k] = mk_[k];
+    __syncthreads();
+    const int passes = (B.n_k + 63) >> 6, pairs = passes * (t1 - t0);
+#pragma unroll 1
+    for (int q = wave; q < pairs; q += 4) {
+        const int ti = q / passes, tb = t0 + ti, s = (q - ti * passes) * 64 + lane;
+        const double *cf = coef + ((size_t)tb * B.n_work + w) * kCheb;
+        double cl[NC];
+#pragma unroll
+        for (int k = 0; k < NC; ++k) cl[k] = cf[k];
+        if (s >= B.n_k) continue;
+        double2 out = make_double2(0.0, 0.0);
+        if (msk[s]) {
+            int64_t js;
+            double dc, psi;
+            sample_time<NC>(cl, (double)(2 * s - B.n_k) * inv_nk, an, B.inv_dt, B.f_het, r0 + s, js, dc, psi);
+            const int at = (int)(js - r0) - lo;  // j* is nondecreasing, so inside [D, hi - lo - D]
+            double2 a;
+            if (staged && at >= D && at + D <= hi - lo) a = interpolate64_d8(cw, win + at, dc);
+            else a = interpolate<double, D, 0>(B, xd, js, dc, cw);
+            double c, sn;
+            sincos_rev<double>(psi, sn, c);
+            out = make_double2(c * a.x - sn * a.y, sn * a.x + c * a.y);
+        }
+        y[((size_t)tb * B.Q + det) * nr + r0 + s] = out;
+    }
+}
+
 template <typename T, int DT, int WIN>
 __global__ void __launch_bounds__(64) k_resample(BandDev B, const double *coef, c2<T> *y) {
     resample_body<T, DT, WIN>(B, coef, y, blockIdx.x, blockIdx.y, blockIdx.y + 1);
@@ -2397,6 +2534,22 @@ k_resample_m(const BandDev *__restrict__ bands, const WorkItem *__restrict__ ite
                                   min(it.n_tmpl, t0 + kResTemplates));
 }
 
+__global__ void __launch_bounds__(256) k_resample64(BandDev B, const double *coef, double2 *y, int n_tmpl) {
+    const int t0 = blockIdx.y * kResTemplates;
+    resample64_body<kCheb>(B, coef, y, blockIdx.x, t0, min(n_tmpl, t0 + kResTemplates));
+}
+
+__global__ void __launch_bounds__(256)
+k_resample64_m(const BandDev *__restrict__ bands, const WorkItem *__restrict__ items, int n_items,
+               const double *__restrict__ coef, double2 *__restrict__ y) {
+    const WorkItem &it = items[find_item(items, n_items, kStResample, blockIdx.x)];
+    const BandDev B = global_view(bands[it.band], bands);
+    const int l = blockIdx.x - it.first[kStResample];
+    const int tiles = (it.n_tmpl + kResTemplates - 1) / kResTemplates;
+    const int t0 = (l % tiles) * kResTemplates;
+    resample64_body<kCheb>(B, coef + it.coef_off, y + it.y_off, l / tiles, t0, min(it.n_tmpl, t0 + kResTemplates));
+}
+
 template <int NC, bool PS2>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(8)))
 k_resample_far_m(const BandDev *__restrict__ bands, const WorkItem *__restrict__ items, int n_items,
@@ -2627,7 +2780,9 @@ hipError_t launch_resample(const BandDev &B, const double *coef, int n_tmpl, boo
         dim3 grid((unsigned)B.n_work, (n_tmpl + kFarTemplates - 1) / kFarTemplates);
         hipLaunchKernelGGL(k_resample_far, grid, dim3(256), 0, stream, B, coef, (float2 *)y, n_tmpl);
     } else if (fp64) {
-        if (B.D == 8) launch_resample_t<double, 8>(B, coef, n_tmpl, y, stream);
+        if (resample64_ok(B.D, B.window))
+            hipLaunchKernelGGL(k_resample64, dim3((unsigned)B.n_work, (n_tmpl + kResTemplates - 1) / kResTemplates),
+                               dim3(256), 0, stream, B, coef, (double2 *)y, n_tmpl);
         else launch_resample_t<double, 0>(B, coef, n_tmpl, y, stream);
     } else {
         if (B.D == 8) launch_resample_t<float, 8>(B, coef, n_tmpl, y, stream);
@@ -2823,7 +2978,8 @@ hipError_t launch_resample_m(const BandDev *bands, const WorkItem *items, int n_
         else CCR_FAR(kCheb);
 #undef CCR_FAR
     } else if (fp64) {
-        if (D == 8) launch_resample_m_t<double, 8, kCheb>(bands, items, n_items, blocks, window, coef, y, stream);
+        if (resample64_ok(D, window))
+            hipLaunchKernelGGL(k_resample64_m, dim3(blocks), dim3(256), 0, stream, bands, items, n_items, coef, (double2 *)y);
         else launch_resample_m_t<double, 0, kCheb>(bands, items, n_items, blocks, window, coef, y, stream);
     } else if (n_cheb == kChebSplit) {
         if (D == 8) launch_resample_m_t<float, 8, kChebSplit>(bands, items, n_items, blocks, window, coef, y, stream);
