@@ -156,6 +156,11 @@ struct ccr_ctx {
     std::vector<Timed> timed;
     double kt_ms[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
     int64_t kt_n[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};
+    // SFT front end: device buffers of the last call, and two pinned buffers through which results
+    // are copied to pageable host memory
+    DevBuf sft_dev;
+    void *pin[2] = {nullptr, nullptr};
+    hipEvent_t pin_done[2] = {nullptr, nullptr};
     // no-allocation entry point: host staging of its band and work-item tables (fixed size,
     // allocated with the context) and the event after which the staging may be rewritten
     std::vector<char> na_host;
@@ -203,6 +208,17 @@ bool finite_all(const double *v, int64_t n) {
     for (int64_t i = 0; i < n; ++i)
         if (!std::isfinite(v[i])) return false;
     return true;
+}
+
+// Whether n floats are all finite: the exponent bits alone, without a branch per value.
+bool finite_all_f32(const float *v, int64_t n) {
+    uint32_t bad = 0;
+    for (int64_t i = 0; i < n; ++i) {
+        uint32_t u;
+        std::memcpy(&u, v + i, sizeof u);
+        bad |= (uint32_t)((u & 0x7f800000u) == 0x7f800000u);
+    }
+    return bad == 0;
 }
 
 template <typename F> void parallel_for(int64_t n, F &&f) {
@@ -1615,6 +1631,45 @@ ccr_status grow(ccr_ctx *c, DevBuf &b, size_t bytes) {
     return CCR_OK;
 }
 
+// The same for a buffer that no captured launch sequence refers to.
+ccr_status grow_scratch(ccr_ctx *c, DevBuf &b, size_t bytes) {
+    if (bytes <= b.bytes && b.p) return CCR_OK;
+    HIP_OK(c, hipStreamSynchronize(c->stream));
+    HIP_OK(c, b.ensure(bytes));
+    return CCR_OK;
+}
+
+constexpr size_t kSftKeepBytes = (size_t)256 << 20;
+constexpr size_t kPinBytes = (size_t)2 << 20;
+
+// Device result to pageable host memory, complete on return: the copy engine fills one pinned
+// buffer while the host empties the other (12.5 MB: 0.71 ms by the runtime's pageable copy).
+ccr_status copy_out(ccr_ctx *c, void *dst, const void *src, size_t bytes, hipStream_t s) {
+    if (bytes <= kPinBytes / 8) {
+        HIP_OK(c, hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, s));
+        HIP_OK(c, hipStreamSynchronize(s));
+        return CCR_OK;
+    }
+    for (int i = 0; i < 2; ++i) {
+        if (!c->pin[i]) HIP_OK(c, hipHostMalloc(&c->pin[i], kPinBytes));
+        if (!c->pin_done[i]) HIP_OK(c, hipEventCreateWithFlags(&c->pin_done[i], hipEventDisableTiming));
+    }
+    const size_t n = (bytes + kPinBytes - 1) / kPinBytes;
+    auto len = [&](size_t k) { return std::min(kPinBytes, bytes - k * kPinBytes); };
+    auto fetch = [&](size_t k) -> ccr_status {
+        HIP_OK(c, hipMemcpyAsync(c->pin[k & 1], static_cast<const char *>(src) + k * kPinBytes, len(k), hipMemcpyDeviceToHost, s));
+        HIP_OK(c, hipEventRecord(c->pin_done[k & 1], s));
+        return CCR_OK;
+    };
+    ccr_status st = fetch(0);
+    for (size_t k = 0; k < n && !st; ++k) {
+        if (k + 1 < n && (st = fetch(k + 1))) break;
+        HIP_OK(c, hipEventSynchronize(c->pin_done[k & 1]));
+        std::memcpy(static_cast<char *>(dst) + k * kPinBytes, c->pin[k & 1], len(k));
+    }
+    return st;
+}
+
 // budget_override > 0: pack rounds to that many workspace bytes instead of the context's budget.
 ccr_status build_plan(ccr_ctx *c, bool fp64, int n_bands, const int *band_ids, void *const *rho_out,
                       int out_on_device, int out_fp64, const BatchParams &bp, CallPlan &cp, size_t budget_override = 0) {
@@ -2223,6 +2278,11 @@ void ccr_destroy(ccr_ctx *c) {
     if (c->h_tables) (void)hipHostFree(c->h_tables);
     if (c->tables_copied) (void)hipEventDestroy(c->tables_copied);
     if (c->na_copied) (void)hipEventDestroy(c->na_copied);
+    c->sft_dev.release();
+    for (int i = 0; i < 2; ++i) {
+        if (c->pin[i]) (void)hipHostFree(c->pin[i]);
+        if (c->pin_done[i]) (void)hipEventDestroy(c->pin_done[i]);
+    }
     if (c->stream) (void)hipStreamDestroy(c->stream);
     delete c;
 }
@@ -2347,8 +2407,9 @@ ccr_status ccr_set_data(ccr_ctx *c, int band_id, int det, const ccr_site *site, 
         if (B->det[X].t0 != t0 || B->det[X].dt != dt)
             return fail(c, CCR_EINVAL, "t0/dt differ from detector %d", X);
     }
-    for (int64_t i = 0; i < 2 * n; ++i)
-        if (!std::isfinite(x[i])) return fail(c, CCR_EINVAL, "non-finite sample at %lld", (long long)(i / 2));
+    if (!finite_all_f32(x, 2 * n))
+        for (int64_t i = 0; i < 2 * n; ++i)
+            if (!std::isfinite(x[i])) return fail(c, CCR_EINVAL, "non-finite sample at %lld", (long long)(i / 2));
     try {
         DetData &d = B->det[det];
         d.x.assign(x, x + 2 * n);
@@ -2660,41 +2721,48 @@ ccr_status ccr_sft_series(ccr_ctx *c, int64_t n_sft, double t_sft, double t0, in
     if (off < 0 || off + n_out > n_bins)
         return fail(c, CCR_ERANGE, "the SFTs hold bins %lld..%lld, the band needs %lld..%lld", (long long)k_first,
                     (long long)(k_first + n_bins - 1), (long long)(kh - h), (long long)(kh - h + n_out - 1));
-    for (int64_t i = 0; i < 2 * n_sft * n_bins; ++i)
-        if (!std::isfinite(z[i])) return fail(c, CCR_EINVAL, "non-finite SFT bin at %lld", (long long)(i / 2));
+    if (!finite_all_f32(z, 2 * n_sft * n_bins)) {
+        for (int64_t i = 0; i < 2 * n_sft * n_bins; ++i)
+            if (!std::isfinite(z[i])) return fail(c, CCR_EINVAL, "non-finite SFT bin at %lld", (long long)(i / 2));
+    }
     HIP_OK(c, hipSetDevice(c->device));
-    std::vector<double2> roots((size_t)n_out), ej((size_t)n_out), sk((size_t)n_sft);
-    for (int64_t m = 0; m < n_out; ++m) {
-        const long double a = 2.0L * kPiL * (long double)m / (long double)n_out;
-        roots[(size_t)m] = make_double2((double)cosl(a), (double)sinl(a));
-        const long double b = -2.0L * kPiL * nu * (long double)m / (long double)n_out;
-        ej[(size_t)m] = make_double2((double)(cosl(b) / ts), (double)(sinl(b) / ts));
+    // per SFT: the stitching phase (cycles, reduced in long double) and the presence flag, one copy
+    const size_t pb = (size_t)n_sft * (sizeof(double) + 1);
+    std::vector<char> small;
+    try {
+        small.resize(pb);
+    } catch (const std::bad_alloc &) {
+        return fail(c, CCR_ENOMEM, "out of host memory");
     }
     for (int64_t K = 0; K < n_sft; ++K) {
         long double ph = fh * ((long double)t0 + (long double)K * ts);
         ph -= floorl(ph);
-        const long double a = -2.0L * kPiL * ph;
-        sk[(size_t)K] = make_double2((double)cosl(a), (double)sinl(a));
+        const double p = (double)ph;
+        std::memcpy(small.data() + K * sizeof(double), &p, sizeof p);
+        small[(size_t)n_sft * sizeof(double) + K] = sft_valid ? (sft_valid[K] ? 1 : 0) : 1;
     }
-    DevBuf dz, dx, dr, de, ds, dv;
+    // device buffers in one allocation, kept by the context up to kSftKeepBytes
     const size_t zb = (size_t)n_sft * n_bins * sizeof(float2), xb = (size_t)n_sft * n_out * sizeof(float2);
-    HIP_OK(c, dz.ensure(zb));
-    HIP_OK(c, dx.ensure(xb));
     ccr_status st;
-    if ((st = upload(c, dr, roots)) || (st = upload(c, de, ej)) || (st = upload(c, ds, sk))) return st;
-    if (sft_valid) {
-        if ((st = upload(c, dv, std::vector<uint8_t>(sft_valid, sft_valid + n_sft)))) return st;
-    }
+    if ((st = grow_scratch(c, c->sft_dev, arena_al(zb) + arena_al(xb) + arena_al(pb)))) return st;
+    char *dz = c->sft_dev.as<char>(), *dx = dz + arena_al(zb), *dp = dx + arena_al(xb);
     hipStream_t s = c->stream;
-    HIP_OK(c, hipMemcpyAsync(dz.p, z, zb, hipMemcpyHostToDevice, s));
-    {
-        LaunchTimer lt(c, 8, s);
-        HIP_OK(c, launch_sft_series(dz.as<float2>(), n_sft, n_bins, off, (int)n_out, (int)h, dr.as<double2>(),
-                                    de.as<double2>(), ds.as<double2>(), sft_valid ? dv.as<uint8_t>() : nullptr,
-                                    dx.as<float2>(), s));
-    }
-    HIP_OK(c, hipMemcpyAsync(x_out, dx.p, xb, hipMemcpyDeviceToHost, s));
-    HIP_OK(c, hipStreamSynchronize(s));
+    // whatever fails from here on, nothing queued may outlive the call's host buffers
+    st = [&]() -> ccr_status {
+        HIP_OK(c, hipMemcpyAsync(dp, small.data(), pb, hipMemcpyHostToDevice, s));
+        HIP_OK(c, hipMemcpyAsync(dz, z, zb, hipMemcpyHostToDevice, s));
+        {
+            LaunchTimer lt(c, 8, s);
+            HIP_OK(c, launch_sft_series(reinterpret_cast<float2 *>(dz), n_sft, n_bins, off, (int)n_out, (int)h, (double)nu,
+                                        (double)(1.0L / ts), reinterpret_cast<double *>(dp),
+                                        reinterpret_cast<uint8_t *>(dp + n_sft * sizeof(double)),
+                                        reinterpret_cast<float2 *>(dx), s));
+        }
+        return copy_out(c, x_out, dx, xb, s);
+    }();
+    if (st) (void)hipStreamSynchronize(s);
+    if (c->sft_dev.bytes > kSftKeepBytes) c->sft_dev.release();
+    if (st) return st;
     if (valid_out)
         for (int64_t K = 0; K < n_sft; ++K)
             std::memset(valid_out + K * n_out, sft_valid ? (sft_valid[K] ? 1 : 0) : 1, (size_t)n_out);
