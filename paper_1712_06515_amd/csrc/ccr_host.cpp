@@ -353,6 +353,8 @@ bool lag_plan(const Plan &pl, const ccr_band &b, int Q, bool streams, bool fp64,
     for (int ns = 256; ns <= (big ? 1024 : 512); ns *= 2) {
         const int nf = (int)((pl.n_k + ns - 1) / ns);
         if (nf > 4) continue;
+        // four transforms a wavefront read at 32-bit offsets into a template's series
+        if (lag_quad(ns, fp64) && (uint64_t)Q * pl.n_seg * pl.n_k * 8 >= 0xffff0000ull) continue;
         const int64_t pmin = std::max<int64_t>(1, (int64_t)std::ceil(kLagSigmaMin * (double)(2 * pl.n_k - 1) / ns));
         std::vector<int64_t> cand{pmin, pmin + 1, pmin + 2};
         if (pl.n_fft % ns == 0) cand.push_back(pl.n_fft / ns);
@@ -364,7 +366,7 @@ bool lag_plan(const Plan &pl, const ccr_band &b, int Q, bool streams, bool fp64,
             const int w = direct ? 1 : lag_taps(pl.n_k, ng, fp64, &beta);
             const int64_t gmin = floor_div(k0 * ng, pl.n_fft) - (direct ? 0 : w / 2 - 1);
             const int64_t gmax = floor_div(k1 * ng, pl.n_fft) + (direct ? 0 : w / 2);
-            const int v = ns / 64;
+            const int v = lag_values(ns, fp64);
             int64_t m0 = floor_div(floor_div(gmin, P), v) * v;
             int64_t span = floor_div(gmax, P) - m0 + 1;
             const bool wrap = span >= ns;
@@ -372,8 +374,7 @@ bool lag_plan(const Plan &pl, const ccr_band &b, int Q, bool streams, bool fp64,
                 m0 = 0;
                 span = ns;
             }
-            const int exch = (ns + 64) * cs / 2;  // ns + ns / V = ns + 64 values of one component
-            const int slot = (int)std::max<int64_t>(exch, (span + 63) / 64 * 64 * cs);
+            const int slot = lag_slot(ns, fp64, span);
             if ((size_t)kLagSegs * lag_dets(Q, R, b.pairs) * (streams ? 2 : 1) * slot + lag_tw_lds(ns, fp64) > kLagMaxLds)
                 continue;
             const double fft = ns == 1024 ? 570.0 : (ns == 512 ? 255.0 : 115.0);
@@ -408,11 +409,11 @@ void lag_tables(const Plan &pl, bool fp64, LagGrid &L, LagTables &t) {
     };
     t.tw64.resize((size_t)ng);
     for (int64_t j = 0; j < ng; ++j) t.tw64[(size_t)j] = root(j);
-    const int v = d.ns / 64;
+    const int v = lag_values(d.ns, fp64);
     t.step64.resize((size_t)d.P * v * d.nfold);
     for (int64_t p = 0; p < d.P; ++p)
         for (int64_t r = 0; r < (int64_t)v * d.nfold; ++r)
-            t.step64[(size_t)(p * v * d.nfold + r)] = t.tw64[(size_t)(((p + (int64_t)d.P * d.m0) * 64 * r) % ng)];
+            t.step64[(size_t)(p * v * d.nfold + r)] = t.tw64[(size_t)(((p + (int64_t)d.P * d.m0) * (d.ns / v) * r) % ng)];
     auto narrow = [](const std::vector<double2> &a, std::vector<float2> &o) {
         o.resize(a.size());
         for (size_t i = 0; i < a.size(); ++i) o[i] = make_float2((float)a[i].x, (float)a[i].y);
@@ -1524,13 +1525,14 @@ struct BatchParams {
 };
 
 // LDS of a workgroup of the grid's kernel: the twiddles and a step's transforms.
-size_t lag_lds(const BandDev &bd, bool fp64) {
+size_t lag_lds(const BandDev &bd, const LagKey &k, bool fp64) {
+    if (k.same > 0) return lag_tw_lds(256, false) + 4 * 4 * kLagQuadSlot;
     return (size_t)kLagSegs * lag_dets(bd.Q, bd.R, bd.pairs) * (bd.pw ? 2 : 1) * bd.lag.slot_bytes +
            lag_tw_lds(bd.lag.ns, fp64);
 }
 
 // Whether a band runs on the lag-resolved grid, and the kernel variant that takes it.
-bool lag_fits(const BandDev &bd, LagKey &k) {
+bool lag_fits(const BandDev &bd, bool fp64, LagKey &k) {
     if (!bd.lag.on) return false;
     if (bd.pairs == CCR_PAIRS_CROSS && bd.Q < 2) return false;
     k.ns = bd.lag.ns;
@@ -1540,6 +1542,13 @@ bool lag_fits(const BandDev &bd, LagKey &k) {
     k.rm = bd.R == 0 ? 0 : (k.cross || k.ps || bd.R > 2 || (k.circ && bd.R > 1) ? 4 : bd.R);
     k.waves = 2;
     while (64 * k.waves < bd.lag.span) k.waves *= 2;
+    if (bd.R == 0 && !k.ps && lag_quad(k.ns, fp64) && bd.lag.nfold == 1) {
+        k.same = bd.lag.span <= 96 ? 6 : 16;
+        k.rows = bd.n_k <= 128 ? 8 : (bd.n_k <= 192 ? 12 : 16);
+        k.dets = bd.Q == 2 || bd.Q == 3 ? bd.Q : 0;
+        k.circ = false;  // the weight is read at run time
+        k.waves = 4;
+    }
     return true;
 }
 
@@ -1560,10 +1569,10 @@ Variant variant_of(const BandDev &bd, bool fp64, bool short_series, bool farrow,
     const bool wide_ok = (bd.pw == nullptr || (streams && v.far && bd.pwf != nullptr)) && spectra_wide_ok(bw, fp64, kMaxLds);
     v.sp = plain && spectra_pairs_ok(bd, fp64, kMaxLds) && !(prefer_wide && wide_ok);
     v.timer = v.sp ? 6 : 7;
-    // same-time pairs on 256-point segments stay on their own kernel: N_FFT is then 2 to 4
-    // transforms too, and only the decimated bins are summed (120-day band, 512 templates: 7.4 ms
-    // there, 10 ms on the grid)
-    if (!(v.sp && bd.R == 0) && lag_fits(bd, v.lk)) {
+    // the grid is the faster one wherever it applies (lags up to 4): band after band 1.5 to 12 times,
+    // and for same-time pairs of 256 points 7.2 -> 4.06 ms (120-day band, 512 templates); the kernels
+    // below take the rest
+    if (lag_fits(bd, fp64, v.lk)) {
         v.lag = true;
         v.sp = false;
     }
@@ -1595,16 +1604,19 @@ Variant variant_of(const BandDev &bd, bool fp64, bool short_series, bool farrow,
 // Segments per chunk when the caller and the tuner leave it open: 256, or fewer (not below 16) so
 // that a call of few templates or short series still gives the GPU about 4096 workgroups (4-8
 // wavefronts each on the grid; 8192 of the 256-point kernel's single wavefronts).  Shorter chunks
-// repeat more halo segments (R per chunk), so full calls keep 256.  In FP64 the rule looks at the
+// repeat more halo segments (R per chunk), so full calls keep 256; same-time pairs in registers have
+// no halo and no LDS to share out, a workgroup takes 16 segments a step, and up to 1024 segments a
+// chunk pay (512 templates: 128, 256, 512, 1024, 2048 segments 4.62, 4.66, 4.21, 4.06, 4.38 ms).  In FP64 the rule looks at the
 // band alone, never at the template count, which keeps results bitwise independent of how templates
 // are split over calls: 64 chunks a band.
 int64_t default_chunk(const Band &B, const Variant &v, const BandDev &bd, bool fp64) {
     const int64_t M = B.plan.n_seg;
     int64_t chunks = 0;
-    if (v.lag) chunks = fp64 ? 64 : 4096 / ((int64_t)B.n_tmpl * bd.lag.P * bd.lag.n_sub);
+    const int64_t most = v.lag && v.lk.same > 0 ? 1024 : 256;
+    if (v.lag) chunks = fp64 ? 64 : (v.lk.same > 0 ? 16384 : 4096) / ((int64_t)B.n_tmpl * bd.lag.P * bd.lag.n_sub);
     else if (v.sp) chunks = 8192 / B.n_tmpl;
-    const int64_t kc = chunks > 0 ? std::max<int64_t>(16, M / chunks) : 256;
-    return std::min<int64_t>({kc, (int64_t)256, M});
+    const int64_t kc = chunks > 0 ? std::max<int64_t>(16, M / chunks) : most;
+    return std::min<int64_t>({kc, most, M});
 }
 
 constexpr int64_t kMaxBlocks = ((int64_t)1 << 31) - 1;
@@ -1785,7 +1797,7 @@ ccr_status build_plan(ccr_ctx *c, bool fp64, int n_bands, const int *band_ids, v
             q.part = part1 * nb;
             q.coef = coef1 * nb;
             q.fin_lds = v.lag ? B.lag[fp64 ? 1 : 0].fin_lds : 0;
-            q.lds = v.fold ? (size_t)pl.n_s : v.lag ? lag_lds(bd, fp64) : v.sp ? spectra_pairs_lds(cp.bands.back()) : (v.wide ? spectra_wide_lds(cp.bands.back()) : 0);
+            q.lds = v.fold ? (size_t)pl.n_s : v.lag ? lag_lds(bd, v.lk, fp64) : v.sp ? spectra_pairs_lds(cp.bands.back()) : (v.wide ? spectra_wide_lds(cp.bands.back()) : 0);
             for (int st = 0; st < kStages; ++st) q.blk[st] = per_t[st] * nb;
             q.blk[kStResample] = per_t[kStResample] * ((nb + res_t - 1) / res_t);
             pend.push_back(q);

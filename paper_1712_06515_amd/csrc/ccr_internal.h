@@ -60,7 +60,7 @@ struct LagDev {
     int on;          // 1 when the band runs on the grid
     int ns, P, ng;   // transform length, classes, N_G = P ns
     int nfold;       // rows of ns samples that a segment's N_K samples fold onto
-    int m0, span;    // first transform output kept (mod ns, a multiple of ns / 64), outputs kept per class
+    int m0, span;    // first transform output kept (mod ns, a multiple of lag_values()), outputs kept per class
     int wrap;        // 1: every grid point is kept (span = ns), indices taken mod N_G
     int n_sub;       // problems per chunk: 1, or one per detector (pairs within a detector only) or
                      // per pair of detectors (pairs across detectors only, with lags)
@@ -68,7 +68,8 @@ struct LagDev {
     int taps;        // interpolation taps from the grid to an output bin (1: the bins are grid points)
     const float2 *tw32;    // [ng] exp(-2 pi i j / ng)
     const double2 *tw64;
-    const float2 *step32;  // [P][nfold ns / 64] class input twiddle W^(64 (p + P m0) r)
+    // [P][nfold v] class input twiddle W^((ns / v) (p + P m0) r), v = lag_values(ns, precision)
+    const float2 *step32;
     const double2 *step64;
     // [Q][n_seg + 2 kLagSegs] pair weights (hat a scale, hat b scale), zero for absent segments
     const float2 *segwf;
@@ -271,14 +272,35 @@ constexpr int kLagMaxR = 4;           // largest lag of the kernel
 constexpr int kLagFinThreads = 256;
 struct LagKey {
     int ns = 0, rm = 0, waves = 0;
+    // same-time pairs of 256 points in FP32: outputs (6 or 16) and input rows (8, 12 or 16) a lane,
+    // detectors (2, 3, or 0: any number); same = 0: the other kernel
+    int same = 0, rows = 0, dets = 0;
     bool cross = false, ps = false, circ = false;
     bool operator==(const LagKey &o) const {
-        return ns == o.ns && rm == o.rm && waves == o.waves && cross == o.cross && ps == o.ps && circ == o.circ;
+        return ns == o.ns && rm == o.rm && waves == o.waves && same == o.same && rows == o.rows && dets == o.dets &&
+               cross == o.cross && ps == o.ps && circ == o.circ;
     }
 };
 // Most threads of a workgroup (a lane per kept column), and the LDS of its twiddle table.
 constexpr int lag_max_threads(int ns, bool fp64) { return ns < 512 ? 256 : (ns == 512 || fp64 ? 512 : 1024); }
-constexpr int lag_tw_lds(int ns, bool fp64) { return ns == 1024 && !fp64 ? 32 * 64 * 8 : 0; }
+// 256-point transforms in FP32 run four to a wavefront, 16 lanes and 16 values a lane each; the
+// others take a wavefront, ns / 64 values a lane.
+constexpr bool lag_quad(int ns, bool fp64) { return ns == 256 && !fp64; }
+constexpr int lag_values(int ns, bool fp64) { return lag_quad(ns, fp64) ? 16 : ns / 64; }
+constexpr int lag_tw_lds(int ns, bool fp64) { return fp64 ? 0 : (ns == 1024 ? 32 * 64 * 8 : (ns == 256 ? 256 * 8 : 0)); }
+// A quad's exchange, 16 rows of 17 values; consecutive slots start 16 banks apart.
+constexpr int kLagQuadSlot = 1088;
+// LDS of one transform: its exchange (one component; 17 x 16 entries of a quad, else at most
+// ns + 64), then its kept outputs; a quad's slots start 16 banks apart.
+inline int lag_slot(int ns, bool fp64, int64_t span) {
+    const int cs = fp64 ? 16 : 8;
+    if (!lag_quad(ns, fp64)) {
+        const int out = (int)((span + 63) / 64 * 64) * cs;
+        return out > (ns + 64) * cs / 2 ? out : (ns + 64) * cs / 2;
+    }
+    const int out = (int)((span + 15) / 16 * 16) * cs;
+    return out <= kLagQuadSlot ? kLagQuadSlot : (out + 127) / 128 * 128 + 64;
+}
 hipError_t launch_lag_m(const LagKey &k, const BandDev *bands, const WorkItem *items, int n_items, int blocks,
                         bool fp64, size_t lds, const void *y, double *part, hipStream_t stream);
 // reduce_blocks: pair stage, 0 when every item has a single partial a template; blocks: finish stage.

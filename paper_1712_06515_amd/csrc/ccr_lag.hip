@@ -15,6 +15,8 @@
 //                 interpolation margin, per (template, chunk of segments, residue class)
 //   k_lag_reduce  chunk sums
 //   k_lag_finish  interpolation to the output bins, lag phases, sqrt(2) / N
+#include <type_traits>
+
 #include "ccr_device.h"
 #include "ccr_internal.h"
 
@@ -118,6 +120,46 @@ template <typename T, int NS> struct LagTw<T, NS, true> {
     __device__ __forceinline__ c2<T> c(int) const { return l[0]; }
 };
 
+// 256 points, FP32: four transforms a wavefront, 16 lanes each (lane t of a group holds x[t + 16 r]
+// in v[r]): passes of radix 16 and 16 with one exchange where the 64-lane form takes three, at the
+// same arithmetic a transform and a quarter of the per-unit overhead (six bands of 3 detectors with
+// lag 1, whole call: 8.5 -> 8.3 ms; same-time pairs: see k_lag_same).  l: the factors
+// W256^(k t) W^(q t) of the first pass's output k, q as above (16 x 16, LDS, one copy a workgroup;
+// the groups' reads coincide).
+struct LagTwQuad {
+    const float2 *l;
+    __device__ __forceinline__ void load(const float2 *tw, float2 *lds, int P, int q, int lane) {
+        for (int e = threadIdx.x; e < 256; e += blockDim.x)
+            lds[e] = tw[((unsigned)(P * (e >> 4) + q) * (unsigned)(e & 15)) % (unsigned)(P * 256)];
+        l = lds + (lane & 15);
+        __syncthreads();
+    }
+    __device__ __forceinline__ float2 a(int k) const { return l[16 * k]; }
+};
+
+// One group's transform through `ex` (16 rows of 17); on return X[t + 16 k] is in v[4 (k % 4) + k / 4].
+// Groups without a unit (on = false) leave LDS alone.  Z4: the inputs v[12..15] are zero (not read).
+template <bool Z4 = false>
+__device__ __forceinline__ void lag_fft_quad(float2 *v, float *ex, const LagTwQuad &tw, int t, bool on) {
+    dft16<float, Z4>(v);
+#pragma unroll
+    for (int k = 0; k < 16; ++k) v[4 * (k & 3) + (k >> 2)] = cmul<float>(v[4 * (k & 3) + (k >> 2)], tw.a(k));
+    if (on) {
+#pragma unroll
+        for (int k = 0; k < 16; ++k) ex[17 * k + t] = v[4 * (k & 3) + (k >> 2)].x;
+        wave_sync();
+#pragma unroll
+        for (int r = 0; r < 16; ++r) v[r].x = ex[17 * t + r];
+        wave_sync();
+#pragma unroll
+        for (int k = 0; k < 16; ++k) ex[17 * k + t] = v[4 * (k & 3) + (k >> 2)].y;
+        wave_sync();
+#pragma unroll
+        for (int r = 0; r < 16; ++r) v[r].y = ex[17 * t + r];
+    }
+    dft16<float>(v);
+}
+
 // NS-point forward FFT of one wavefront (V = NS / 64 values a lane, x[l + 64 r] in v[r] on
 // entry, X[l + 64 J] in v[J] on return), self-sorting passes of radix 16, 16, 4 (1024), 8, 8, 8
 // (512) or 4, 4, 4, 4 (256): a pass of radix V with stride Ns has butterfly l read a[l + 64 r],
@@ -214,6 +256,9 @@ template <> __device__ __forceinline__ double2 ld_uniform_c2<double>(const doubl
     const double *d = reinterpret_cast<const double *>(p);
     return make_double2(ld_uniform(d, 2 * i), ld_uniform(d, 2 * i + 1));
 }
+
+// Byte offset past any series (with room for a row's offset): reads there give zero.
+constexpr unsigned kLagNone = 0xffff0000u;
 
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 // Value at byte offset `lane` + 64 r values (`lane`: the lane's own byte offset, opaque to the
@@ -326,7 +371,10 @@ template <typename T, int NS, int RM, bool CR, bool PS, int CM>
 __device__ __forceinline__ void lag_body(const BandDev &B, const c2<T> *__restrict__ y, double *__restrict__ part,
                                          int k_chunk, int n_chunks, int c, int sub, int p, int tb) {
     extern __shared__ __align__(16) char smem[];
-    constexpr int V = NS / 64;
+    constexpr bool QUAD = lag_quad(NS, sizeof(T) == 8);
+    constexpr int V = lag_values(NS, sizeof(T) == 8);  // values a lane
+    constexpr int RL = NS / V;                          // input row: lanes of one transform
+    constexpr int GR = 64 / RL;                         // transforms a wavefront takes at once
     constexpr int S = PS ? 2 : 1;
     constexpr int NST = CR ? 4 : 2;
     constexpr bool LTW = lag_tw_lds(NS, sizeof(T) == 8) > 0;
@@ -353,7 +401,7 @@ __device__ __forceinline__ void lag_body(const BandDev &B, const c2<T> *__restri
     const int slot_bytes = G.slot_bytes;
     const int nunit = kLagSegs * nd;  // units of a step (times the streams)
 
-    LagTw<T, NS, LTW> tw;
+    std::conditional_t<QUAD, LagTwQuad, LagTw<T, NS, LTW>> tw;
     tw.load(LagTab<T>::tw(G), reinterpret_cast<c2<T> *>(smem), P, (p + P * G.m0) % G.ng, lane);
     char *slots = smem + lag_tw_lds(NS, sizeof(T) == 8);
     const c2<T> *step = LagTab<T>::step(G) + (size_t)p * V * nf;
@@ -373,37 +421,85 @@ __device__ __forceinline__ void lag_body(const BandDev &B, const c2<T> *__restri
         if (Kb + kLagSegs > K1) m &= (1u << ((K1 - Kb) * nd)) - 1u;
         return m;
     };
-    // n-th set bit of m (from 0), -1 if there is none
     const unsigned all = nunit >= 32 ? ~0u : (1u << nunit) - 1u;
+    // n-th set bit of m (from 0), n < popcount(m)
     auto nth = [&](unsigned m, int n) -> int {
-        if (m == all) return n < nunit ? n : -1;
-        for (int k = 0; k < n && m; ++k) m &= m - 1;
-        return m ? __builtin_ctz(m) : -1;
+        if (m == all) return n;
+        if constexpr (GR == 1) {  // uniform
+            for (int k = 0; k < n; ++k) m &= m - 1;
+            return __builtin_ctz(m);
+        } else {  // a lane each: by halves
+            int pos = 0;
+#pragma unroll
+            for (int w = 16; w > 0; w >>= 1) {
+                const int low = __builtin_popcount((m >> pos) & ((1u << w) - 1u));
+                if (n >= low) {
+                    n -= low;
+                    pos += w;
+                }
+            }
+            return pos;
+        }
     };
     const unsigned rnd = (65536u + nd - 1) / nd;  // u / nd = u rnd >> 16 for u < 32, nd <= 8
-    int lo = lane * (int)sizeof(c2<T>);
+    const int tl = lane & (RL - 1);               // lane within the transform's row
+    int lo = tl * (int)sizeof(c2<T>);
     asm("" : "+v"(lo));
     // input of segment K of detector det; reads past its N_K samples give zero (on = false: all)
     auto src = [&](const c2<T> *base, int det, int K, bool on) {
         return __builtin_amdgcn_make_buffer_rsrc((void *)(base + (size_t)det * nr + (size_t)K * n_k), (short)0,
                                                  on ? n_k * (int)sizeof(c2<T>) : 0, 0x00020000);
     };
-    // this wavefront's units in order: (step iK, unit iu, stream in % S); nxt holds that unit's input
+    // four transforms a wavefront: every lane reads at its own group's byte offset `at` into the
+    // template's series (or its weights, laid out alike); rows past N_K and groups without a unit
+    // read past the range, which gives zero
+    auto ld_quad = [&](__amdgpu_buffer_rsrc_t rs, unsigned at, unsigned at_last, int n, int r) -> float2 {
+        const int s0 = RL * r;
+        const unsigned o = s0 + RL <= n ? at : (s0 < n ? at_last : kLagNone);
+        return __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(rs, (int)(o + (unsigned)(s0 * 8)), 0, 0));
+    };
+    // n_k, opaque: a row's comparison with it is redone (two scalar instructions) instead of held
+    auto fresh = [](int n) {
+        asm volatile("" : "+s"(n));
+        return n;
+    };
+    auto last_of = [&](unsigned at) { return tl < n_k % RL ? at : kLagNone; };
+    auto whole = [&](const c2<T> *base) {
+        return __builtin_amdgcn_make_buffer_rsrc((void *)base, (short)0, (int)(unsigned)(B.Q * nr * 8), 0x00020000);
+    };
+    // this wavefront's (unit, stream) pairs in order: number GR in + group of the step at iK; nxt holds
+    // their input, ip their place (unit S + stream, -1: none; of this lane's group), iat its offset
     c2<T> nxt[V];
-    int iK = Ks, in = wv;
+    int iK = Ks, in = wv, ip = -1;
+    unsigned iat = kLagNone;
+    bool have = false;
     unsigned im = step_mask(Ks);
-    int iu = nth(im, in / S);
-    auto seek = [&]() {  // to the first unit at or after the iterator's place
-        while (iu < 0 && iK + kLagSegs < K1) {
+    auto seek = [&]() {  // to the first pairs at or after the iterator's place
+        int cnt = __builtin_popcount(im) * S;
+        while (GR * in >= cnt && iK + kLagSegs < K1) {
             iK += kLagSegs;
             im = step_mask(iK);
             in = wv;
-            iu = nth(im, in / S);
+            cnt = __builtin_popcount(im) * S;
         }
-        const int t = (int)((unsigned)max(iu, 0) * rnd >> 16), i = max(iu, 0) - t * nd;
-        const __amdgpu_buffer_rsrc_t rs = src(yb, D.at(i), iu >= 0 ? iK + t : 0, iu >= 0);
+        have = GR * in < cnt;
+        if constexpr (QUAD) {
+            const int n = GR * in + (lane >> 4);
+            ip = n < cnt ? nth(im, n / S) * S + n % S : -1;
+            const int u = max(ip, 0) / S, t = (int)((unsigned)u * rnd >> 16), i = u - t * nd;
+            iat = ip < 0 ? kLagNone : (unsigned)(D.at(i) * nr + (int64_t)(iK + t) * n_k) * 8u + (unsigned)lo;
+            const __amdgpu_buffer_rsrc_t rs = whole(yb);
+            const unsigned last = last_of(iat);
+            const int nk = fresh(n_k);
 #pragma unroll
-        for (int r = 0; r < V; ++r) nxt[r] = ld_buf<T>(rs, lo, r);
+            for (int r = 0; r < V; ++r) nxt[r] = ld_quad(rs, iat, last, nk, r);
+        } else {
+            ip = have ? nth(im, in / S) * S + in % S : -1;
+            const int u = max(ip, 0) / S, t = (int)((unsigned)u * rnd >> 16), i = u - t * nd;
+            const __amdgpu_buffer_rsrc_t rs = src(yb, D.at(i), have ? iK + t : 0, have);
+#pragma unroll
+            for (int r = 0; r < V; ++r) nxt[r] = ld_buf<T>(rs, lo, r);
+        }
     };
     seek();
 
@@ -427,18 +523,23 @@ __device__ __forceinline__ void lag_body(const BandDev &B, const c2<T> *__restri
                 for (int j = 0; j < NST; ++j) hist[d][j] = mk<T>((T)0, (T)0);
             continue;
         }
-        // transforms: this wavefront takes active (unit, stream) numbers wv, wv + W, ...
+        // transforms of this wavefront's pairs
 #pragma unroll 1
-        while (iu >= 0 && iK == Kb) {
-            const int s = PS ? in % S : 0;
-            const int t = (int)((unsigned)iu * rnd >> 16), i = iu - t * nd;
-            char *slot = slots + (size_t)(iu * S + s) * slot_bytes;
+        while (have && iK == Kb) {
+            const int pl = ip, s = PS ? max(pl, 0) % S : 0;
+            const unsigned at = iat;
+            const int u = max(pl, 0) / S, t = (int)((unsigned)u * rnd >> 16), i = u - t * nd;
+            char *slot = slots + (size_t)max(pl, 0) * slot_bytes;
+            // input row r + V j (j > 0: rows past N_S) and its weight
+            auto row = [&](const c2<T> *base, int r) -> c2<T> {
+                if constexpr (QUAD) return ld_quad(whole(base), at, last_of(at), n_k, r);
+                else return ld_buf<T>(src(base, D.at(i), Kb + t, true), lo, r);
+            };
             c2<T> v[V];
             if constexpr (PS) {
-                const __amdgpu_buffer_rsrc_t rw = src(LagTab<T>::pw(B), D.at(i), Kb + t, true);
 #pragma unroll
                 for (int r = 0; r < V; ++r) {
-                    const c2<T> w = ld_buf<T>(rw, lo, r);
+                    const c2<T> w = row(LagTab<T>::pw(B), r);
                     v[r] = cscale<T>(nxt[r], s ? w.y : w.x);
                 }
                 if (p > 0) {
@@ -452,29 +553,36 @@ __device__ __forceinline__ void lag_body(const BandDev &B, const c2<T> *__restri
 #pragma unroll
                 for (int r = 0; r < V; ++r) v[r] = nxt[r];
             }
-            // the next unit's input is loaded while this one is transformed
+            // the next input is loaded while this one is transformed
             in += W;
-            iu = nth(im, in / S);
             seek();
             for (int j = 1; j < nf; ++j) {
-                const __amdgpu_buffer_rsrc_t rs = src(yb, D.at(i), Kb + t, true);
-                const __amdgpu_buffer_rsrc_t rw = src(PS ? LagTab<T>::pw(B) : yb, D.at(i), Kb + t, true);
 #pragma unroll
                 for (int r = 0; r < V; ++r) {
-                    if (64 * r + NS * j >= n_k) continue;  // uniform
-                    c2<T> z = ld_buf<T>(rs, lo, r + V * j);
+                    if (RL * r + NS * j >= n_k) continue;  // uniform
+                    c2<T> z = row(yb, r + V * j);
                     if constexpr (PS) {
-                        const c2<T> w = ld_buf<T>(rw, lo, r + V * j);
+                        const c2<T> w = row(LagTab<T>::pw(B), r + V * j);
                         z = cscale<T>(z, s ? w.y : w.x);
                     }
                     v[r] = cadd<T>(v[r], cmul<T>(z, ld_uniform_c2<T>(step, r + V * j)));
                 }
             }
-            lag_fft<T>(v, reinterpret_cast<T *>(slot), tw, lane);
-            wave_sync();
+            if constexpr (QUAD) {
+                lag_fft_quad(v, reinterpret_cast<float *>(slot), tw, tl, pl >= 0);
+                if (pl >= 0) {
+                    wave_sync();
 #pragma unroll
-            for (int J = 0; J < V; ++J)
-                if (64 * J < span) reinterpret_cast<c2<T> *>(slot)[lane + 64 * J] = v[J];
+                    for (int k = 0; k < 16; ++k)
+                        if (16 * k < span) reinterpret_cast<c2<T> *>(slot)[tl + 16 * k] = v[4 * (k & 3) + (k >> 2)];
+                }
+            } else {
+                lag_fft<T>(v, reinterpret_cast<T *>(slot), tw, lane);
+                wave_sync();
+#pragma unroll
+                for (int J = 0; J < V; ++J)
+                    if (64 * J < span) reinterpret_cast<c2<T> *>(slot)[lane + 64 * J] = v[J];
+            }
         }
         // zeros for the units without a spectrum
         {
@@ -554,17 +662,201 @@ __device__ __forceinline__ void lag_body(const BandDev &B, const c2<T> *__restri
     }
 }
 
+// ------------------------------------------------------------------ same-time pairs, 256 points
+
+// First index of the ascending list x[0 .. n) with x >= key, by the whole wavefront (64 probes a round).
+__device__ __forceinline__ int lower_wave(const int *x, int n, int key, int lane) {
+    int a = 0;
+    while (n > 0) {
+        const int step = (n + 63) >> 6, i = lane * step;
+        const int below = __builtin_popcountll(__ballot(i < n && x[i] < key));
+        if (below == 0) return a;
+        // x[a + (below - 1) step] < key <= x[a + below step], where that exists
+        const int lo = (below - 1) * step + 1, hi = min(n, below * step);
+        a += lo;
+        x += lo;
+        n = hi - lo;
+    }
+    return a;
+}
+
+// Same-time pair sums (R = 0) of a 256-point grid without LDS slots or barriers: a wavefront takes
+// four segments at once, a 16-lane group each, and transforms one detector after the other, so that
+// every detector's spectrum of a segment lies in the same registers of the same lanes and the
+// products are formed there.  The groups take consecutive entries of seg_any, the segments with a
+// pair (gaps cost nothing); the workgroup's four wavefronts take the chunk's quadruples in turn and
+// add up at the end.  A lane keeps outputs t + 16 k, k < NO (16 NO >= span; the second pass is
+// pruned to them at compile time).  NR: input rows of 16 that hold samples, 8, 12 or 16 for N_K up to
+// 128, 192 or 256; of 12 and 16 all but the last four are full, and only these need their ends looked at.
+// The pairs of detector Y with those before it add F_Y . sum_X (wa_Y u_X + wb_Y v_X) G_X (a product
+// of 2-vectors) with weights wa, wb = hat a, hat b times the scale, u = wa, v = wb and G = F; for
+// Gamma^circ u = wb, v = -wa and G = i F.  QK = 2 or 3 detectors: the G_X are kept as they are; any
+// other number (QK = 0): as the sums of u_X G_X and of v_X G_X.
+//
+// Bound: VALU issue (busy in every cycle, ~112 instructions a transform of which ~95 are its passes
+// and twiddles; four wavefronts a SIMD).  512 templates of the 120-day band (2 detectors, 30 % gaps,
+// two classes of 179-sample segments, 137 bins): the 256-point spectra + pairs kernel, which runs
+// every step through an LDS ring, 7.2 ms; k_lag with four transforms a wavefront 6.5 ms; this kernel
+// 4.8 ms, with chunks of up to 1024 segments (a wavefront gets ~35 steps, not 9) 4.25 ms, with one
+// weight a pair in place of the two sums for 2 and 3 detectors 4.06 ms.
+template <int NO, int NR, int QK>
+__device__ __forceinline__ void lag_same_body(const BandDev &B, const float2 *__restrict__ y, double *__restrict__ part,
+                                              int k_chunk, int n_chunks, int c, int sub, int p, int tb) {
+    extern __shared__ __align__(16) char smem[];
+    constexpr int NF = NR == 8 ? 0 : NR - 4;  // full rows
+    const LagDev &G = B.lag;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const int g = lane >> 4, t = lane & 15;
+    const int n_k = B.n_k, Q = QK > 0 ? QK : B.Q, P = G.P, span = G.span;
+    const bool circ = B.weight != 0;
+    LagTwQuad tw;
+    tw.load(G.tw32, reinterpret_cast<float2 *>(smem), P, (p + P * G.m0) % G.ng, lane);
+    char *ex = smem + lag_tw_lds(256, false) + wv * 4 * kLagQuadSlot;
+    const float2 *step = G.step32 + (size_t)p * 16;
+
+    // entries [lo, hi) of seg_any; pairs within a detector only: none
+    const int K0 = c * k_chunk, K1 = min(B.n_seg, K0 + k_chunk);
+    const int lo = lower_wave(B.seg_any, B.n_seg_any, K0, lane);
+    const int hi = (B.pairs & 1) ? lower_wave(B.seg_any, B.n_seg_any, K1, lane) : lo;
+    const unsigned nr = (unsigned)(B.n_seg * n_k);
+    const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+        (void *)(y + (size_t)tb * Q * nr), (short)0, (int)((unsigned)Q * nr * 8u), 0x00020000);
+    const int nlast = n_k & 15;
+
+    auto seg = [&](int e) { return e < hi ? B.seg_any[e] : -1; };
+    auto det_bits = [&](int K) { return K >= 0 ? B.seg_bits[K] : 0u; };
+    float2 nxt[NR], wn;
+    // input and weights of detector i of this group's segment K; on: it has a spectrum.  Rows past
+    // N_K and segments without one read past the buffer's range, which gives zero.
+    auto load = [&](int K, bool on, int i) {
+        const unsigned at = on ? ((unsigned)i * nr + (unsigned)(K * n_k + t)) * 8u : kLagNone;
+        const unsigned last = t < nlast ? at : kLagNone;
+        int n = n_k;
+        asm volatile("" : "+s"(n));  // the rows' comparisons are redone (two scalar instructions each), not held
+#pragma unroll
+        for (int r = 0; r < NR; ++r) {
+            const unsigned o = r < NF || 16 * r + 16 <= n ? at : (16 * r < n ? last : kLagNone);
+            nxt[r] = __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(rs, (int)(o + 128u * r), 0, 0));
+        }
+        wn = make_float2(0.0f, 0.0f);
+        if (on) wn = G.segwf[i * (B.n_seg + 2 * kLagSegs) + kLagSegs + K];
+    };
+
+    double acc[NO];
+#pragma unroll
+    for (int k = 0; k < NO; ++k) acc[k] = 0.0;
+    // the input is loaded one transform ahead, a step's activity bits one step and its segment two
+    int eb = lo + 4 * wv;
+    int Ka = seg(eb + g), Kb = seg(eb + 16 + g);
+    unsigned ba = det_bits(Ka);
+    load(Ka, ba & 1u, 0);
+#pragma unroll 1
+    for (; eb < hi; eb += 16) {
+        const unsigned bb = det_bits(Kb);
+        const int Kc = seg(eb + 32 + g);
+        // spectra of detector i, while the next input is loaded (a step without the detector costs
+        // its transform all the same: a branch round it took a quarter of the registers)
+        auto spectra = [&](float2 *v, int i) {
+            if (p > 0) {
+#pragma unroll
+                for (int r = 0; r < NR; ++r) v[r] = cmul<float>(nxt[r], ld_uniform_c2<float>(step, r));
+            } else {
+#pragma unroll
+                for (int r = 0; r < NR; ++r) v[r] = nxt[r];
+            }
+            if (i + 1 < Q) load(Ka, (ba >> (i + 1)) & 1u, i + 1);
+            else load(Kb, bb & 1u, 0);
+            if constexpr (NR == 8) {
+#pragma unroll
+                for (int r = 8; r < 12; ++r) v[r] = make_float2(0.0f, 0.0f);
+            }
+            lag_fft_quad<(NR <= 12)>(v, reinterpret_cast<float *>(ex + g * kLagQuadSlot), tw, t, true);
+            wave_sync();
+        };
+        auto turned = [&](float2 f) { return circ ? make_float2(-f.y, f.x) : f; };
+        if constexpr (QK > 0) {
+            float2 G_[QK - 1][NO];
+            float2 uv[QK - 1];
+#pragma unroll
+            for (int i = 0; i < QK; ++i) {
+                const float2 w = wn;
+                float2 v[16];
+                spectra(v, i);
+                float pw[QK];
+#pragma unroll
+                for (int X = 0; X < i; ++X) pw[X] = fma(w.x, uv[X].x, w.y * uv[X].y);
+#pragma unroll
+                for (int k = 0; k < NO; ++k) {
+                    const float2 f = v[4 * (k & 3) + (k >> 2)];
+                    if (i == 1) {
+                        acc[k] += (double)(pw[0] * fma(f.x, G_[0][k].x, f.y * G_[0][k].y));
+                    } else if (i == 2) {
+                        const float cx = fma(pw[0], G_[0][k].x, pw[1] * G_[QK - 2][k].x);
+                        const float cy = fma(pw[0], G_[0][k].y, pw[1] * G_[QK - 2][k].y);
+                        acc[k] += (double)fma(f.x, cx, f.y * cy);
+                    }
+                    if (i + 1 < QK) G_[i][k] = turned(f);
+                }
+                if (i + 1 < QK) uv[i] = circ ? make_float2(w.y, -w.x) : w;
+            }
+        } else {
+            float2 A[NO], Bs[NO];
+#pragma unroll 1
+            for (int i = 0; i < Q; ++i) {
+                const float2 w = wn, uv = circ ? make_float2(w.y, -w.x) : w;
+                float2 v[16];
+                spectra(v, i);
+                if (i == 0) {
+#pragma unroll
+                    for (int k = 0; k < NO; ++k) {
+                        const float2 f = turned(v[4 * (k & 3) + (k >> 2)]);
+                        A[k] = cscale<float>(f, uv.x);
+                        Bs[k] = cscale<float>(f, uv.y);
+                    }
+                } else {
+#pragma unroll
+                    for (int k = 0; k < NO; ++k) {
+                        const float2 f = v[4 * (k & 3) + (k >> 2)], h = turned(f);
+                        const float cx = fma(w.x, A[k].x, w.y * Bs[k].x), cy = fma(w.x, A[k].y, w.y * Bs[k].y);
+                        acc[k] += (double)fma(f.x, cx, f.y * cy);
+                        A[k] = make_float2(fma(uv.x, h.x, A[k].x), fma(uv.x, h.y, A[k].y));
+                        Bs[k] = make_float2(fma(uv.y, h.x, Bs[k].x), fma(uv.y, h.y, Bs[k].y));
+                    }
+                }
+            }
+        }
+        Ka = Kb;
+        ba = bb;
+        Kb = Kc;
+    }
+    // the groups, then the wavefronts (each through its own exchange area)
+    double *red = reinterpret_cast<double *>(ex);
+#pragma unroll
+    for (int k = 0; k < NO; ++k) {
+        double v = acc[k];
+        v += __shfl_xor(v, 16);
+        v += __shfl_xor(v, 32);
+        if (g == 0) red[16 * k + t] = v;
+    }
+    __syncthreads();
+    const int x = threadIdx.x;
+    if (x >= span) return;
+    const char *r0 = smem + lag_tw_lds(256, false) + 8 * x;
+    double v = 0.0;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) v += *reinterpret_cast<const double *>(r0 + w * 4 * kLagQuadSlot);
+    part[(((size_t)tb * n_chunks + c) * G.n_sub + sub) * P * span + (size_t)p * span + x] = v;
+}
+
 // Blocks of an item: G = n_tmpl n_chunks n_sub groups of P class workgroups; the dispatcher
 // hands workgroups to the 8 XCDs in turn, so a group's classes get indices with equal value mod
 // 8 and read the group's resampled series through one XCD's L2.
-template <typename T, int NS, int RM, bool CR, bool PS, int CM>
-__global__ void __launch_bounds__(lag_max_threads(NS, sizeof(T) == 8))
-k_lag(const BandDev *__restrict__ bands, const WorkItem *__restrict__ items, int n_items,
-      const c2<T> *__restrict__ y, double *__restrict__ part) {
-    const WorkItem &it = items[find_item(items, n_items, kStSpectra, blockIdx.x)];
-    const BandDev B = global_view(bands[it.band], bands);
+struct LagPlace {
+    int c, sub, p, t;  // chunk, problem, class, template
+};
+__device__ __forceinline__ LagPlace lag_place(const WorkItem &it, const LagDev &L) {
     const int l = blockIdx.x - it.first[kStSpectra];
-    const int P = B.lag.P, G = it.n_tmpl * it.n_chunks * B.lag.n_sub;
+    const int P = L.P, G = it.n_tmpl * it.n_chunks * L.n_sub;
     const int full = (G >> 3) * 8 * P;
     int g, p;
     if (l < full) {
@@ -575,9 +867,28 @@ k_lag(const BandDev *__restrict__ bands, const WorkItem *__restrict__ items, int
         g = (G >> 3) * 8 + (l - full) / P;
         p = (l - full) % P;
     }
-    const int per = it.n_chunks * B.lag.n_sub;
-    lag_body<T, NS, RM, CR, PS, CM>(B, y + it.y_off, part + it.part_off, it.k_chunk, it.n_chunks,
-                                   (g % per) / B.lag.n_sub, g % B.lag.n_sub, p, g / per);
+    const int per = it.n_chunks * L.n_sub;
+    return {(g % per) / L.n_sub, g % L.n_sub, p, g / per};
+}
+
+template <typename T, int NS, int RM, bool CR, bool PS, int CM>
+__global__ void __launch_bounds__(lag_max_threads(NS, sizeof(T) == 8))
+k_lag(const BandDev *__restrict__ bands, const WorkItem *__restrict__ items, int n_items,
+      const c2<T> *__restrict__ y, double *__restrict__ part) {
+    const WorkItem &it = items[find_item(items, n_items, kStSpectra, blockIdx.x)];
+    const BandDev B = global_view(bands[it.band], bands);
+    const LagPlace w = lag_place(it, B.lag);
+    lag_body<T, NS, RM, CR, PS, CM>(B, y + it.y_off, part + it.part_off, it.k_chunk, it.n_chunks, w.c, w.sub, w.p, w.t);
+}
+
+template <int NO, int NR, int QK>
+__global__ void __launch_bounds__(256, NO > 6 ? 2 : (QK == 2 && NR <= 12 ? 4 : 3))
+k_lag_same(const BandDev *__restrict__ bands, const WorkItem *__restrict__ items, int n_items,
+           const float2 *__restrict__ y, double *__restrict__ part) {
+    const WorkItem &it = items[find_item(items, n_items, kStSpectra, blockIdx.x)];
+    const BandDev B = global_view(bands[it.band], bands);
+    const LagPlace w = lag_place(it, B.lag);
+    lag_same_body<NO, NR, QK>(B, y + it.y_off, part + it.part_off, it.k_chunk, it.n_chunks, w.c, w.sub, w.p, w.t);
 }
 
 // ------------------------------------------------------------------ interpolation to the output bins
@@ -688,6 +999,27 @@ static void launch_lag_t(const LagKey &k, const BandDev *bands, const WorkItem *
 hipError_t launch_lag_m(const LagKey &k, const BandDev *bands, const WorkItem *items, int n_items, int blocks,
                         bool fp64, size_t lds, const void *y, double *part, hipStream_t stream) {
     if (blocks == 0) return hipSuccess;
+    if (k.same > 0) {
+#define CCR_SAME(NO_, NR_, QK_)                                                                            \
+    hipLaunchKernelGGL((k_lag_same<NO_, NR_, QK_>), dim3(blocks), dim3(256), lds, stream, bands, items, n_items, \
+                       (const float2 *)y, part)
+#define CCR_SAME_Q(NO_, NR_)                   \
+    if (k.dets == 2) CCR_SAME(NO_, NR_, 2);    \
+    else if (k.dets == 3) CCR_SAME(NO_, NR_, 3); \
+    else CCR_SAME(NO_, NR_, 0)
+        switch (k.same + k.rows) {
+            case 6 + 8: CCR_SAME_Q(6, 8); break;
+            case 6 + 12: CCR_SAME_Q(6, 12); break;
+            case 6 + 16: CCR_SAME_Q(6, 16); break;
+            case 16 + 8: CCR_SAME_Q(16, 8); break;
+            case 16 + 12: CCR_SAME_Q(16, 12); break;
+            case 16 + 16: CCR_SAME_Q(16, 16); break;
+            default: return hipErrorInvalidValue;
+        }
+#undef CCR_SAME_Q
+#undef CCR_SAME
+        return hipGetLastError();
+    }
     if (fp64) {
         if (k.ns == 512) launch_lag_t<double, 512>(k, bands, items, n_items, blocks, lds, y, part, stream);
         else if (k.ns == 256) launch_lag_t<double, 256>(k, bands, items, n_items, blocks, lds, y, part, stream);
