@@ -531,15 +531,20 @@ __device__ __forceinline__ void lag_body(const BandDev &B, const c2<T> *__restri
             const int u = max(pl, 0) / S, t = (int)((unsigned)u * rnd >> 16), i = u - t * nd;
             char *slot = slots + (size_t)max(pl, 0) * slot_bytes;
             // input row r + V j (j > 0: rows past N_S) and its weight
-            auto row = [&](const c2<T> *base, int r) -> c2<T> {
-                if constexpr (QUAD) return ld_quad(whole(base), at, last_of(at), n_k, r);
-                else return ld_buf<T>(src(base, D.at(i), Kb + t, true), lo, r);
+            auto from = [&](const c2<T> *base) {
+                if constexpr (QUAD) return whole(base);
+                else return src(base, D.at(i), Kb + t, true);
+            };
+            auto row = [&](__amdgpu_buffer_rsrc_t rs, int r) -> c2<T> {
+                if constexpr (QUAD) return ld_quad(rs, at, last_of(at), n_k, r);
+                else return ld_buf<T>(rs, lo, r);
             };
             c2<T> v[V];
             if constexpr (PS) {
+                const __amdgpu_buffer_rsrc_t rw = from(LagTab<T>::pw(B));
 #pragma unroll
                 for (int r = 0; r < V; ++r) {
-                    const c2<T> w = row(LagTab<T>::pw(B), r);
+                    const c2<T> w = row(rw, r);
                     v[r] = cscale<T>(nxt[r], s ? w.y : w.x);
                 }
                 if (p > 0) {
@@ -557,12 +562,13 @@ __device__ __forceinline__ void lag_body(const BandDev &B, const c2<T> *__restri
             in += W;
             seek();
             for (int j = 1; j < nf; ++j) {
+                const __amdgpu_buffer_rsrc_t rs = from(yb), rw = from(PS ? LagTab<T>::pw(B) : yb);
 #pragma unroll
                 for (int r = 0; r < V; ++r) {
                     if (RL * r + NS * j >= n_k) continue;  // uniform
-                    c2<T> z = row(yb, r + V * j);
+                    c2<T> z = row(rs, r + V * j);
                     if constexpr (PS) {
-                        const c2<T> w = row(LagTab<T>::pw(B), r + V * j);
+                        const c2<T> w = row(rw, r + V * j);
                         z = cscale<T>(z, s ? w.y : w.x);
                     }
                     v[r] = cadd<T>(v[r], cmul<T>(z, ld_uniform_c2<T>(step, r + V * j)));
