@@ -1557,8 +1557,6 @@ Variant variant_of(const BandDev &bd, bool fp64, bool short_series, bool farrow,
     Variant v;
     v.ss = short_series;
     v.far = farrow && !fp64 && bd.farrow != nullptr;
-    // the spectra + pair-sum kernels take the Gamma^ave weight over lagged pairs with per-segment
-    // weights; the other forms run on the general path
     // the 256-point spectra + pair-sum kernel takes the Gamma^ave weight over lagged pairs with
     // per-segment weights, the 1024-point one either weight and every ordered pair as well; the
     // other forms (per-sample antenna functions: two spectra streams) run on the general path

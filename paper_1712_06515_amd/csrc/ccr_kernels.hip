@@ -2783,6 +2783,9 @@ hipError_t launch_resample(const BandDev &B, const double *coef, int n_tmpl, boo
         if (resample64_ok(B.D, B.window))
             hipLaunchKernelGGL(k_resample64, dim3((unsigned)B.n_work, (n_tmpl + kResTemplates - 1) / kResTemplates),
                                dim3(256), 0, stream, B, coef, (double2 *)y, n_tmpl);
+        else if (B.D == 8)
+            hipLaunchKernelGGL((k_resample<double, 8, 1>), dim3((unsigned)B.n_work, n_tmpl), dim3(64), 0, stream, B, coef,
+                               (double2 *)y);
         else launch_resample_t<double, 0>(B, coef, n_tmpl, y, stream);
     } else {
         if (B.D == 8) launch_resample_t<float, 8>(B, coef, n_tmpl, y, stream);
@@ -2980,6 +2983,9 @@ hipError_t launch_resample_m(const BandDev *bands, const WorkItem *items, int n_
     } else if (fp64) {
         if (resample64_ok(D, window))
             hipLaunchKernelGGL(k_resample64_m, dim3(blocks), dim3(256), 0, stream, bands, items, n_items, coef, (double2 *)y);
+        else if (D == 8)
+            hipLaunchKernelGGL((k_resample_m<double, 8, 1, kCheb>), dim3(blocks), dim3(64), 0, stream, bands, items,
+                               n_items, coef, (double2 *)y);
         else launch_resample_m_t<double, 0, kCheb>(bands, items, n_items, blocks, window, coef, y, stream);
     } else if (n_cheb == kChebSplit) {
         if (D == 8) launch_resample_m_t<float, 8, kChebSplit>(bands, items, n_items, blocks, window, coef, y, stream);
