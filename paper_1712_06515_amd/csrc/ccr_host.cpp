@@ -1750,6 +1750,18 @@ ccr_status build_plan(ccr_ctx *c, bool fp64, int n_bands, const int *band_ids, v
         while (v.lag && budget_override > 0 && kc < pl.n_seg &&
                arena_bytes_of(coef1, y1, F1, (size_t)((pl.n_seg + kc - 1) / kc) * lag1) > budget)
             kc = std::min<int64_t>(2 * kc, pl.n_seg);
+        if (budget_override > 0 && (v.lag || v.fold)) {
+            // What fits the fixed workspace does not depend on the kernels: its limit stays that of the
+            // forms for any lag (spectra in memory in FP64), and such a band is refused here too.
+            BandDev b0 = bd;
+            b0.lag.on = 0;
+            const Variant v0 = variant_of(b0, fp64, B.short_series, c->opt_farrow != 0, bp.spectra != 0, !bp.no_streams, false);
+            const int64_t kc0 = std::min<int64_t>(bp.k_chunk > 0 ? bp.k_chunk : 256, pl.n_seg);
+            const size_t nb = (size_t)std::min<int64_t>(std::max<int64_t>(bp.template_batch, 1), B.n_tmpl);
+            const size_t F0 = v0.sp || v0.wide ? 0 : (size_t)B.Q * pl.n_seg * pl.n_f * cs * (bd.pw ? 2 : 1);
+            const size_t part0 = (size_t)((pl.n_seg + kc0 - 1) / kc0) * pl.n_f * sizeof(double) * (bd.allp ? 4 : 1);
+            cp.arena_bytes = std::max(cp.arena_bytes, arena_bytes_of(nb * coef1, nb * ser1 * (v0.wps ? 2 : 1), nb * F0, nb * part0));
+        }
         if (v.fold) kc = pl.n_seg;  // one partial a bin
         const int nch = (int)((pl.n_seg + kc - 1) / kc);
         const size_t part1 = v.lag ? (size_t)nch * lag1

@@ -88,3 +88,30 @@ def test_lag_grid(ccr, case):
             print(f"  error {e:.2e}, max|rho| {np.abs(ref).max():.2f}", flush=True)
             assert kt["spectra"][1] == 0 and kt["pairs"][1] == 0, kt  # not the general path
             assert e < (1e-10 if prec == ccr.PREC_FP64 else 1e-4)
+
+
+def test_fixed_workspace_limit(ccr):
+    """The call without allocations refuses the same bands whichever kernel they would take: 14 days
+    in FP64 with 7413 bins, whose spectra (2 x 840 x 7413 complex, 199 MB) and series (23 MB) fit
+    one template's fixed workspace, are taken, 21 days (298 MB and 35 MB) are not."""
+    import torch
+    for n_seg, fits in ((840, True), (1260, False)):
+        cfg = small_config(q=2, n_seg=n_seg, t_short=1440.0, f_min=399.875, f_band=0.25, max_lag=4, pairs=3, a_p_max=2.0,
+                           gap_fraction=0.0, templates=dict(a_p=(1.0, 1.0, 1), t_asc=(0.0, 0.0, 1), period=[68023.70]),
+                           injections=[])
+        ds = synth.make_dataset(cfg)
+        with ccr.Context(ds.sky, device=0) as ctx:
+            bid = ctx.load(ds)
+            info = ctx.band_info(bid)
+            need = 16 * 2 * n_seg * (info["n_f"] + info["n_k"])
+            assert (need < 240 << 20) == fits and (need > 260 << 20) == (not fits), need
+            out = torch.zeros((len(ds.templates), info["n_f"]), dtype=torch.float64, device="cuda")
+            if fits:
+                ctx.compute_rho_noalloc(bid, prec=ccr.PREC_FP64, out_fp64=True, outputs=[out.data_ptr()])
+                torch.cuda.synchronize()
+                ref = ctx.compute_rho(bid, prec=ccr.PREC_FP64, out_fp64=True)
+                # the same kernels with other chunks: FP64 sums in another order
+                assert float(np.max(np.abs(out.cpu().numpy() - ref))) < 1e-10 * max(1.0, float(np.abs(ref).max()))
+            else:
+                with pytest.raises(ccr.CcrError):
+                    ctx.compute_rho_noalloc(bid, prec=ccr.PREC_FP64, out_fp64=True, outputs=[out.data_ptr()])
