@@ -139,6 +139,13 @@ def roofline(name, avg_ms, tb, info, workload, streams=1):
                 "avg_launch_ms": avg_ms, "algorithmic_bytes_per_launch": byts,
                 "per_unit": f"{8.0 + 8.0 / T_b:g} B per resampled sample (8 B written, 8 B input "
                             f"per tile of {T_b} templates)"}
+    if name == "spectra_wide" and info.get("folded"):
+        # every ordered pair: one pass over the resampled series, folded onto N_FFT samples
+        byts = streams * n_active * info["n_k"] * tb * 8.0
+        ach = byts / (avg_ms * 1e-3) / 1e9
+        return {"kernel": "k_fold + k_fold_dft", "bound": "hbm", "achieved": ach, "peak": HBM_PEAK_GBS, "unit": "GB/s",
+                "frac": ach / HBM_PEAK_GBS, "traffic": read_traffic("fold", workload), "avg_launch_ms": avg_ms,
+                "algorithmic_bytes_per_launch": byts, "per_unit": "8 B read per resampled sample"}
     flops = streams * n_active * tb * P * (5.0 * ns * np.log2(ns) + 6.0 * ns)
     per_unit = f"P (5 n_s log2 n_s + 6 n_s) FP32 flop per (template, detector, segment), n_s={ns}, P={P}"
     if streams != 1:
@@ -154,7 +161,7 @@ def roofline(name, avg_ms, tb, info, workload, streams=1):
     kern = {"spectra": "k_spectra16_m" if ns == 256 else "k_spectra_m", "spectra_pairs": "k_spectra_pairs_m",
             "fused": "k_fused", "spectra_wide": "k_spectra_wide_m"}[name]
     if grid and name in ("spectra_pairs", "spectra_wide"):
-        kern = "k_lag"
+        kern = "k_lag_same" if info.get("max_lag") == 0 and ns == 256 else "k_lag"
     return {"kernel": kern, "bound": "alu", "achieved": ach, "peak": FP32_PEAK_TFLOPS, "unit": "TFLOP/s",
             "frac": ach / FP32_PEAK_TFLOPS, "traffic": read_traffic(name, workload),
             "avg_launch_ms": avg_ms, "algorithmic_flops_per_launch": flops, "per_unit": per_unit}
@@ -343,6 +350,7 @@ def main():
     kt = ctx.kernel_times(reset=True)
     ctx.set_option("timing", 0)
     info["grid_ns"], info["grid_classes"] = ctx.get_option("grid_ns"), ctx.get_option("grid_classes")
+    info["max_lag"] = cfg["band"]["max_lag"]
 
     # plain FP64 path: one template per launch sequence, no graph, on a bounded subset
     nsub = min(args.fp64_templates, n_t)
@@ -439,6 +447,7 @@ def form_lines(args, ds, info0):
             step()
             kt = ctx.kernel_times(reset=True)
             inf["grid_ns"], inf["grid_classes"] = ctx.get_option("grid_ns"), ctx.get_option("grid_classes")
+            inf["max_lag"], inf["folded"] = dsf.band["max_lag"], dsf.band.get("pairs", 3) == 4
         dom = max((k for k in kt if kt[k][1]), key=lambda k: kt[k][0])
         line = {"value": len(tm) * inf["n_f"] / sec, "unit": "rho-evals/s", "ms_per_step": 1e3 * sec,
                 "templates": len(tm), "kernels_ms_per_step": {k: v[0] for k, v in kt.items() if v[1]},
