@@ -180,10 +180,10 @@ const char *ccr_last_error(const ccr_ctx *ctx);
  *                     applies to device outputs only;
  *   "round_templates" at most this many templates in one launch round (0, the default: as
  *                     many as the workspace budget holds);
- *   "spectra_kernel"  0 (default): bands of same-time pairs on 256-point segments run the
- *                     256-point spectra + pair-sum kernel; 1: they run the kernel of the other
- *                     bands.  (With lags up to 4 both values run the lag-resolved grid; the value
- *                     then only says which slot of ccr_kernel_time, 6 or 7, counts it.);
+ *   "spectra_kernel"  0 (default): 256-point bands with lags above 4 run the 256-point spectra +
+ *                     pair-sum kernel; 1: they run the kernel of the other bands.  (With lags up
+ *                     to 4 both values run the lag-resolved grid; the value then only says which
+ *                     slot of ccr_kernel_time, 6 or 7, counts it.);
  *   "autotune"        1: on the first call for a given band list and precision, time the
  *                     first launch round of each candidate launch shape and keep the fastest
  *                     per template: the spectra kernel (where a band can take either) and

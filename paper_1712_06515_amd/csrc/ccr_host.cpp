@@ -1540,8 +1540,10 @@ bool lag_fits(const BandDev &bd, bool fp64, LagKey &k) {
     k.ps = bd.pw != nullptr;
     k.circ = bd.weight == CCR_WEIGHT_CIRC && !k.cross && !k.ps;
     k.rm = bd.R == 0 ? 0 : (k.cross || k.ps || bd.R > 2 || (k.circ && bd.R > 1) ? 4 : bd.R);
-    k.waves = 2;
-    while (64 * k.waves < bd.lag.span) k.waves *= 2;
+    // a lane per column; a third or fourth wavefront that only transforms costs more than it takes off
+    // the others (six bands, 3 detectors, lag 1, 256 points: 2 for spans up to 128, then 3, against 2
+    // or 4: 5.72 -> 5.19 ms; 3 at least 5.44; 1 for spans up to 64 5.44)
+    k.waves = std::max(2, (bd.lag.span + 63) / 64);
     if (bd.R == 0 && !k.ps && lag_quad(k.ns, fp64) && bd.lag.nfold == 1) {
         k.same = bd.lag.span <= 96 ? 6 : 16;
         k.rows = bd.n_k <= 128 ? 8 : (bd.n_k <= 192 ? 12 : 16);
