@@ -169,7 +169,8 @@ const char *ccr_last_error(const ccr_ctx *ctx);
  *                     at least 64; 0 (the default) = 3/4 of the device memory that is free,
  *                     plus what the context's workspace already holds, at the context's first
  *                     compute call (fixed from then on; fewer, larger launch rounds);
- *   "k_chunk"         segments per pair-sum chunk, 0 = min(M, 256) or the tuned value;
+ *   "k_chunk"         segments per pair-sum chunk, 0 = chosen per band (at most 256 segments, 1024
+ *                     for same-time pairs of 256-point segments) or the tuned value;
  *   "fused"           1: fused resample + FFT + pair kernel where a band fits it, 0: staged;
  *   "items_per_launch" work items per launch, 0 = as many as the workspace holds (1 with
  *                     template_batch 1: one template per launch sequence, no batching);
@@ -290,13 +291,17 @@ ccr_status ccr_compute_rho(ccr_ctx *ctx, ccr_precision prec, int n_bands, const 
  *     CCR_ESTATE.
  *   - rho_out[b]: device memory, n_templates * n_f values (double if out_fp64, else float), valid
  *     until the work completes.  Templates are processed in as many launch rounds as the fixed
- *     array requires; a band whose single-template workspace exceeds it (e.g. 240 days at
- *     T_short 1440 s in FP64) gives CCR_ERANGE, as do band and work-item tables over 1 MiB.
+ *     array requires; a band whose single-template workspace on the kernels for any lag exceeds
+ *     it (series, coefficients, chunk partials and, where those kernels keep them in memory, as
+ *     always in FP64, the spectra at the output bins; e.g. 240 days at T_short 1440 s in FP64)
+ *     gives CCR_ERANGE, as do band and work-item tables over 1 MiB.
  *   - Options "template_batch" and "k_chunk" apply; "graph", "autotune" and "timing" do not.
  *   - The array is shared by every call on the device and keeps the last call's contents; no
  *     part of it needs to start at zero.  Calls that overlap on one device (different
  *     contexts or streams) race: order them on one stream or synchronise between them.
- * Results equal ccr_compute_rho's for the same options. */
+ * Results equal ccr_compute_rho's for the same options: both take a band through the same kernels
+ * and chunks.  (A band that the array holds runs on the lag-resolved grid, or as a folded series,
+ * only where that fits the array too, in either call.) */
 ccr_status ccr_compute_rho_noalloc(ccr_ctx *ctx, ccr_precision prec, int n_bands, const int *band_ids,
                                    void *const *rho_out, int out_fp64, void *hip_stream);
 

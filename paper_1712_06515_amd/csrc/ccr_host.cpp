@@ -1490,10 +1490,12 @@ struct Variant {
 // of the last segment), segment spectra (general path), chunk partials; 256-byte aligned.
 constexpr size_t kArenaAlign = 256;
 constexpr size_t kYTailPad = 256 * sizeof(double2);
-inline size_t arena_al(size_t v) { return (v + kArenaAlign - 1) & ~(kArenaAlign - 1); }
+constexpr size_t arena_al(size_t v) { return (v + kArenaAlign - 1) & ~(kArenaAlign - 1); }
 inline size_t arena_bytes_of(size_t coef, size_t y, size_t F, size_t part) {
     return arena_al(coef) + arena_al(y + kYTailPad) + arena_al(F) + arena_al(part);
 }
+// The fixed array of the call without allocations: its tables, then this much workspace.
+constexpr size_t kNoAllocArena = kScratchBytes - arena_al(kNoAllocTableBytes);
 
 struct Round {
     int i0 = 0, n = 0;  // items [i0, i0 + n) of the call's item table
@@ -1731,9 +1733,35 @@ ccr_status build_plan(ccr_ctx *c, bool fp64, int n_bands, const int *band_ids, v
         const size_t fold_part = (size_t)pl.n_f * 4 * sizeof(double);
         const size_t coef1 = (size_t)std::max(B.n_work, 1) * kCheb * sizeof(double);
         const size_t ser1 = (size_t)B.Q * pl.n_seg * pl.n_k * cs;
-        // (a fixed workspace that cannot hold one template's folded series keeps the other kernels)
-        const bool fold = budget_override == 0 || arena_bytes_of(coef1, ser1, fold1, fold_part) <= budget;
-        const Variant v = variant_of(bd, fp64, B.short_series, c->opt_farrow != 0, bp.spectra != 0, !bp.no_streams, fold);
+        // Route of the band, the same in both entry points so that they give the same sums: a band whose
+        // template fits the fixed array on the kernels for any lag (v0) takes the grid or the folded
+        // series only where these fit it too, the grid with longer chunks if the chunk length is its own.
+        BandDev b0 = bd;
+        b0.lag.on = 0;
+        auto variant = [&](const BandDev &d, bool fold) {
+            return variant_of(d, fp64, B.short_series, c->opt_farrow != 0, bp.spectra != 0, !bp.no_streams, fold);
+        };
+        const Variant v0 = variant(b0, false);
+        const int64_t kc0 = std::min<int64_t>(bp.k_chunk > 0 ? bp.k_chunk : 256, pl.n_seg);
+        const size_t y0 = ser1 * (v0.wps ? 2 : 1);
+        const size_t F0 = v0.sp || v0.wide ? 0 : (size_t)B.Q * pl.n_seg * pl.n_f * cs * (bd.pw ? 2 : 1);
+        const size_t part0 = (size_t)((pl.n_seg + kc0 - 1) / kc0) * pl.n_f * sizeof(double) * (bd.allp ? 4 : 1);
+        const bool fixed0 = arena_bytes_of(coef1, y0, F0, part0) <= kNoAllocArena;
+        Variant v = variant(bd, !fixed0 || arena_bytes_of(coef1, ser1, fold1, fold_part) <= kNoAllocArena);
+        const size_t lag1 = (size_t)bd.lag.n_sub * (2 * bd.R + 1) * bd.lag.P * bd.lag.span * sizeof(double);
+        int64_t kc = bp.k_chunk > 0 ? bp.k_chunk : default_chunk(B, v, bd, fp64);
+        kc = std::max<int64_t>(1, std::min<int64_t>(kc, pl.n_seg));
+        if (v.lag && fixed0) {
+            auto fits = [&]() {
+                return arena_bytes_of(coef1, ser1, 0, (size_t)((pl.n_seg + kc - 1) / kc) * lag1) <= kNoAllocArena;
+            };
+            while (bp.k_chunk == 0 && kc < pl.n_seg && !fits()) kc = std::min<int64_t>(2 * kc, pl.n_seg);
+            if (!fits()) {
+                bd = cp.bands.back() = b0;
+                v = v0;
+                kc = kc0;
+            }
+        }
         if (v.wps) cp.bands.back().ps2 = 1;
         if (bi == 0) {
             c->last_grid_ns = v.lag ? bd.lag.ns : 0;
@@ -1741,28 +1769,14 @@ ccr_status build_plan(ccr_ctx *c, bool fp64, int n_bands, const int *band_ids, v
         }
         const int res_t = v.far ? kFarTemplates : kResTemplates;  // templates per resampler workgroup
         if (std::find(variants.begin(), variants.end(), v) == variants.end()) variants.push_back(v);
-        int64_t kc = bp.k_chunk > 0 ? bp.k_chunk : default_chunk(B, v, bd, fp64);
-        kc = std::max<int64_t>(1, std::min<int64_t>(kc, pl.n_seg));
         const size_t y1 = ser1 * (v.wps ? 2 : 1);
         // two spectra streams per segment with per-sample weights; four partials per bin (the
         // stream sums) for every ordered pair
         const size_t F1 = v.fold ? fold1 : (v.sp || v.wide || v.lag) ? 0 : (size_t)B.Q * pl.n_seg * pl.n_f * cs * (bd.pw ? 2 : 1);
-        const size_t lag1 = (size_t)bd.lag.n_sub * (2 * bd.R + 1) * bd.lag.P * bd.lag.span * sizeof(double);
-        // a fixed workspace that one template's chunk partials would overflow: longer chunks
-        while (v.lag && budget_override > 0 && kc < pl.n_seg &&
-               arena_bytes_of(coef1, y1, F1, (size_t)((pl.n_seg + kc - 1) / kc) * lag1) > budget)
-            kc = std::min<int64_t>(2 * kc, pl.n_seg);
         if (budget_override > 0 && (v.lag || v.fold)) {
-            // What fits the fixed workspace does not depend on the kernels: its limit stays that of the
-            // forms for any lag (spectra in memory in FP64), and such a band is refused here too.
-            BandDev b0 = bd;
-            b0.lag.on = 0;
-            const Variant v0 = variant_of(b0, fp64, B.short_series, c->opt_farrow != 0, bp.spectra != 0, !bp.no_streams, false);
-            const int64_t kc0 = std::min<int64_t>(bp.k_chunk > 0 ? bp.k_chunk : 256, pl.n_seg);
+            // what fits the fixed array does not depend on the kernels: its limit stays that of v0
             const size_t nb = (size_t)std::min<int64_t>(std::max<int64_t>(bp.template_batch, 1), B.n_tmpl);
-            const size_t F0 = v0.sp || v0.wide ? 0 : (size_t)B.Q * pl.n_seg * pl.n_f * cs * (bd.pw ? 2 : 1);
-            const size_t part0 = (size_t)((pl.n_seg + kc0 - 1) / kc0) * pl.n_f * sizeof(double) * (bd.allp ? 4 : 1);
-            cp.arena_bytes = std::max(cp.arena_bytes, arena_bytes_of(nb * coef1, nb * ser1 * (v0.wps ? 2 : 1), nb * F0, nb * part0));
+            cp.arena_bytes = std::max(cp.arena_bytes, arena_bytes_of(nb * coef1, nb * y0, nb * F0, nb * part0));
         }
         if (v.fold) kc = pl.n_seg;  // one partial a bin
         const int nch = (int)((pl.n_seg + kc - 1) / kc);
@@ -1794,6 +1808,10 @@ ccr_status build_plan(ccr_ctx *c, bool fp64, int n_bands, const int *band_ids, v
             tb = std::min<int64_t>(tb, st == kStResample ? mb * res_t : mb);
         }
         tb = std::max<int64_t>(1, std::min<int64_t>(tb, B.n_tmpl));
+        // (a batch that v0 fits into the fixed array is split where the grid's does not)
+        while (budget_override > 0 && (v.lag || v.fold) && tb > 1 &&
+               arena_bytes_of(tb * coef1, tb * y1, tb * F1, tb * part1) > budget)
+            --tb;
         char *dst = out_on_device ? static_cast<char *>(rho_out[bi]) : c->ws_out.as<char>() + cp.out_off[bi];
         const int64_t n_t = bp.max_templates > 0 ? std::min<int64_t>(B.n_tmpl, bp.max_templates) : B.n_tmpl;
         for (int64_t t = 0; t < n_t; t += tb) {
@@ -2669,8 +2687,7 @@ ccr_status ccr_compute_rho_noalloc(ccr_ctx *c, ccr_precision prec, int n_bands, 
     hipStream_t s = hip_stream ? (hipStream_t)hip_stream : c->stream;
     const bool fp64 = prec == CCR_PREC_FP64;
     // the scratch holds the band and work-item tables, then the workspace of the largest round
-    const size_t tables_cap = arena_al(kNoAllocTableBytes);
-    const size_t budget = kScratchBytes - tables_cap;
+    const size_t tables_cap = arena_al(kNoAllocTableBytes), budget = kNoAllocArena;
     BatchParams bp;
     bp.k_chunk = c->opt_k_chunk;
     bp.template_batch = c->opt_template_batch;
