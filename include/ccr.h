@@ -283,7 +283,7 @@ ccr_status ccr_compute_rho(ccr_ctx *ctx, ccr_precision prec, int n_bands, const 
 /* For callers that cannot allocate device memory (code under HIP graph capture, tight serving
  * loops, harnesses that forbid hipMalloc): ccr_compute_rho with device outputs whose workspace
  * (band and work-item tables, time-base coefficients, resampled series, spectra, chunk
- * partials) lives in a fixed device array of 256 MiB per device instead of the context's
+ * partials) lives in a fixed device array of 256.3 MiB per device instead of the context's
  * workspace.  The call makes no hipMalloc, hipFree or other allocating call; it queues a table
  * copy and the kernels on hip_stream (NULL: the context's stream) and returns.
  *   - Every band must be prepared beforehand (set-up that allocates): after its data, weights
@@ -294,7 +294,7 @@ ccr_status ccr_compute_rho(ccr_ctx *ctx, ccr_precision prec, int n_bands, const 
  *     array requires; a band whose single-template workspace on the kernels for any lag exceeds
  *     it (series, coefficients, chunk partials and, where those kernels keep them in memory, as
  *     always in FP64, the spectra at the output bins; e.g. 240 days at T_short 1440 s in FP64)
- *     gives CCR_ERANGE, as do band and work-item tables over 1 MiB.
+ *     gives CCR_ERANGE, as do tables of more than 2016 bands with a work item each (1.28 MiB).
  *   - Options "template_batch" and "k_chunk" apply; "graph", "autotune" and "timing" do not.
  *   - The array is shared by every call on the device and keeps the last call's contents; no
  *     part of it needs to start at zero.  Calls that overlap on one device (different

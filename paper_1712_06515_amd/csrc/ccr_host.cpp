@@ -1396,9 +1396,6 @@ void collect_times(ccr_ctx *c) {
     c->timed.clear();
 }
 
-// host staging (and scratch region) of the no-allocation entry point's tables
-constexpr size_t kNoAllocTableBytes = (size_t)1 << 20;
-
 ccr_status grow(ccr_ctx *c, DevBuf &b, size_t bytes);
 
 // Fused path: one launch per template batch computes partial rho per (template, segment chunk)
@@ -1494,8 +1491,6 @@ constexpr size_t arena_al(size_t v) { return (v + kArenaAlign - 1) & ~(kArenaAli
 inline size_t arena_bytes_of(size_t coef, size_t y, size_t F, size_t part) {
     return arena_al(coef) + arena_al(y + kYTailPad) + arena_al(F) + arena_al(part);
 }
-// The fixed array of the call without allocations: its tables, then this much workspace.
-constexpr size_t kNoAllocArena = kScratchBytes - arena_al(kNoAllocTableBytes);
 
 struct Round {
     int i0 = 0, n = 0;  // items [i0, i0 + n) of the call's item table
@@ -2687,7 +2682,7 @@ ccr_status ccr_compute_rho_noalloc(ccr_ctx *c, ccr_precision prec, int n_bands, 
     hipStream_t s = hip_stream ? (hipStream_t)hip_stream : c->stream;
     const bool fp64 = prec == CCR_PREC_FP64;
     // the scratch holds the band and work-item tables, then the workspace of the largest round
-    const size_t tables_cap = arena_al(kNoAllocTableBytes), budget = kNoAllocArena;
+    const size_t tables_cap = kScratchBytes - kNoAllocArena, budget = kNoAllocArena;
     BatchParams bp;
     bp.k_chunk = c->opt_k_chunk;
     bp.template_batch = c->opt_template_batch;

@@ -324,7 +324,14 @@ hipError_t launch_sft_series(const float2 *z, int64_t n_sft, int64_t n_bins, int
 // kScratchBytes per device).  scratch_init(device) looks up the array's device address on
 // `device` once (hipGetSymbolAddress with that device current) and keeps it; scratch_device_ptr
 // returns it (null before scratch_init succeeded).
-constexpr size_t kScratchBytes = (size_t)256 << 20;
+//
+// It holds the band and work-item tables, for 2016 bands of one item each (what 1 MiB held when an
+// entry of either table took 520 bytes together: the entries grew, the calls that fit did not
+// shrink), then 255 MiB of workspace.
+constexpr size_t kNoAllocBands = 2016;
+constexpr size_t kNoAllocTableBytes = kNoAllocBands * (sizeof(BandDev) + sizeof(WorkItem)) + 256;
+constexpr size_t kNoAllocArena = (size_t)255 << 20;
+constexpr size_t kScratchBytes = (kNoAllocTableBytes + 255) / 256 * 256 + kNoAllocArena;
 constexpr int kScratchMaxDevices = 64;
 hipError_t scratch_init(int device);
 void *scratch_device_ptr(int device);
