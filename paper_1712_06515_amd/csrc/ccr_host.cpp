@@ -111,6 +111,11 @@ struct Band {
 
 }  // namespace
 
+// Lag-resolved grid that a band runs on, as ccr_get_option reports it (zeros: none).
+struct GridInfo {
+    int64_t ns = 0, classes = 0;
+};
+
 struct ccr_ctx {
     int device = 0;
     ccr_sky sky{};
@@ -148,7 +153,7 @@ struct ccr_ctx {
     };
     std::vector<Tuned> tuned;
     int64_t last_tuned_k_chunk = 0, last_tuned_template_batch = 0, last_tuned_spectra = -1, last_tuned_round_templates = 0;
-    int64_t last_grid_ns = 0, last_grid_classes = 0;  // first band of the last planned call
+    GridInfo last_grid;  // first band of the last compute call
     struct Timed {
         int kind;
         hipEvent_t a, b;
@@ -174,6 +179,7 @@ struct ccr_ctx::GraphEntry {
     std::vector<void *> outs;
     int prec = 0, out_fp64 = 0;
     uint64_t gen = 0;
+    GridInfo grid;
     void *tables = nullptr;  // device copy of the band and work-item tables
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
@@ -1508,6 +1514,7 @@ struct CallPlan {
     std::vector<WorkItem> items;
     std::vector<Round> rounds;
     size_t arena_bytes = 0;       // largest round's workspace (rounds run in turn and share the arena)
+    GridInfo grid;                // of the first band
     std::vector<size_t> out_off;  // host outputs: byte offset of each band's rho in ws_out
     size_t out_bytes = 0;
 };
@@ -1758,10 +1765,7 @@ ccr_status build_plan(ccr_ctx *c, bool fp64, int n_bands, const int *band_ids, v
             }
         }
         if (v.wps) cp.bands.back().ps2 = 1;
-        if (bi == 0) {
-            c->last_grid_ns = v.lag ? bd.lag.ns : 0;
-            c->last_grid_classes = v.lag ? bd.lag.P : 0;
-        }
+        if (bi == 0 && v.lag) cp.grid = {bd.lag.ns, bd.lag.P};
         const int res_t = v.far ? kFarTemplates : kResTemplates;  // templates per resampler workgroup
         if (std::find(variants.begin(), variants.end(), v) == variants.end()) variants.push_back(v);
         const size_t y1 = ser1 * (v.wps ? 2 : 1);
@@ -2156,11 +2160,13 @@ ccr_status compute_batched(ccr_ctx *c, ccr_precision prec, int n_bands, const in
             if (g->band_ids == ids && g->outs == outs && g->prec == (int)prec && g->out_fp64 == out_fp64 &&
                 g->gen == c->gen) {
                 HIP_OK(c, hipGraphLaunch(g->exec, s));
+                c->last_grid = g->grid;
                 return CCR_OK;
             }
     }
     CallPlan cp;
     if ((st = build_plan(c, fp64, n_bands, band_ids, rho_out, out_on_device, out_fp64, bp, cp))) return st;
+    c->last_grid = cp.grid;
     if ((st = ensure_workspace(c, cp))) return st;
     if (graph) {
         // capture on the context's own stream (the caller's may be the null stream), replay on `s`
@@ -2169,6 +2175,7 @@ ccr_status compute_batched(ccr_ctx *c, ccr_precision prec, int n_bands, const in
         g->outs.assign(rho_out, rho_out + n_bands);
         g->prec = (int)prec;
         g->out_fp64 = out_fp64;
+        g->grid = cp.grid;
         size_t items_off = 0;
         const size_t bytes = tables_bytes(cp, &items_off);
         std::vector<char> host(bytes);
@@ -2368,8 +2375,8 @@ ccr_status ccr_get_option(ccr_ctx *c, const char *name, int64_t *value) {
     else if (k == "spectra_kernel") *value = c->opt_spectra_kernel;
     else if (k == "round_templates") *value = c->opt_round_templates;
     else if (k == "tuned_round_templates") *value = c->last_tuned_round_templates;
-    else if (k == "grid_ns") *value = c->last_grid_ns;
-    else if (k == "grid_classes") *value = c->last_grid_classes;
+    else if (k == "grid_ns") *value = c->last_grid.ns;
+    else if (k == "grid_classes") *value = c->last_grid.classes;
     else if (k == "resample_templates") *value = kResTemplates;
     else if (k == "farrow") *value = c->opt_farrow;
     else if (k == "farrow_stage") *value = c->opt_farrow_stage;
@@ -2653,8 +2660,11 @@ ccr_status ccr_compute_rho(ccr_ctx *c, ccr_precision prec, int n_bands, const in
                 rest_out.push_back(rho_out[bi]);
             }
         }
-        if (rest.empty()) return CCR_OK;
-        return compute_batched(c, prec, (int)rest.size(), rest.data(), rest_out.data(), out_on_device, out_fp64, s);
+        if (!rest.empty() &&
+            (st = compute_batched(c, prec, (int)rest.size(), rest.data(), rest_out.data(), out_on_device, out_fp64, s)))
+            return st;
+        if (rest.empty() || rest[0] != band_ids[0]) c->last_grid = GridInfo();  // the first band ran fused
+        return CCR_OK;
     }
     return compute_batched(c, prec, n_bands, band_ids, rho_out, out_on_device, out_fp64, s);
 }
@@ -2694,6 +2704,7 @@ ccr_status ccr_compute_rho_noalloc(ccr_ctx *c, ccr_precision prec, int n_bands, 
     if (cp.arena_bytes > budget)
         return fail(c, CCR_ERANGE, "one template's workspace (%zu MiB) exceeds the fixed scratch of %zu MiB",
                     cp.arena_bytes >> 20, budget >> 20);
+    c->last_grid = cp.grid;
     size_t items_off = 0;
     const size_t tbytes = tables_bytes(cp, &items_off);
     if (tbytes > kNoAllocTableBytes)

@@ -1,0 +1,48 @@
+"""What a context reports about its last call."""
+
+import pytest
+
+import synth
+from conftest import small_config
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ccr():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1712_06515_amd import ccr as mod
+    mod.load_library()
+    return mod
+
+
+def test_grid_after_replay(ccr):
+    """grid_ns and grid_classes name the last call's grid also when that call replayed a graph."""
+    import torch
+    a = synth.make_dataset(small_config(n_seg=12, t_short=400.0, f_min=100.0, f_band=0.1, max_lag=1))
+    b = synth.make_dataset(small_config(n_seg=9, t_short=1440.0, f_min=399.875, f_band=0.25, max_lag=4, a_p_max=2.0))
+    with ccr.Context(a.sky, device=0) as ctx:
+        ids = [ctx.load(a), ctx.load(b)]
+        outs = [torch.empty((ctx.band_info(i)["n_templates"], ctx.band_info(i)["n_f"]), dtype=torch.float32, device="cuda")
+                for i in ids]
+        ctx.set_option("graph", 1)
+        grids = {}
+        for rep in range(3):
+            for k in (0, 1):
+                ctx.compute_rho(ids[k], prec=ccr.PREC_SPLIT, out_fp64=False, outputs=[outs[k].data_ptr()])
+                ctx.sync()
+                g = ctx.get_option("grid_ns"), ctx.get_option("grid_classes")
+                assert grids.setdefault(k, g) == g
+        assert grids[0][0] == 256 and grids[1][0] == 1024
+        # the stage outputs plan a call of their own, which is no compute call
+        ctx.resample_series(ids[0], 0, 0, prec=ccr.PREC_SPLIT)
+        assert (ctx.get_option("grid_ns"), ctx.get_option("grid_classes")) == grids[1]
+        # fused: not on the grid
+        ctx.set_option("graph", 0)
+        ctx.set_option("fused", 1)
+        ctx.set_option("timing", 1)
+        ctx.compute_rho(ids[0], prec=ccr.PREC_SPLIT)
+        assert ctx.kernel_times()["fused"][1] > 0
+        assert ctx.get_option("grid_ns") == 0 and ctx.get_option("grid_classes") == 0
