@@ -335,8 +335,9 @@ ccr_status ccr_sync(ccr_ctx *ctx);
  * launch).  kernel: 0 resampling, 1 segment spectra, 2 pair sum, 3 final scaling,
  * 4 fused resampling + spectra + pair sum, 5 FP64 time base (per-segment interpolating polynomial),
  * 6 spectra + pair sum in one kernel (split precision, 256-point segments with per-segment
- * Gamma^ave weights), 7 the same for every other band that has such a kernel, 8 the SFT front end
- * (ccr_sft_series).
+ * Gamma^ave weights and LDS for their bins), 7 the same for every other band that has such a kernel,
+ * 8 the SFT front end (ccr_sft_series).  Bands of both slots 6 and 7 run on the lag-resolved grid at
+ * lags up to 4; a timed call launches them apart.
  * Waits for the recorded launches to finish. */
 ccr_status ccr_kernel_time(ccr_ctx *ctx, int kernel, double *ms, int64_t *launches);
 ccr_status ccr_reset_kernel_times(ccr_ctx *ctx);

@@ -1476,7 +1476,7 @@ struct Variant {
     bool fold = false;   // every ordered pair: folded series
     bool lag = false;    // spectra + pair sum on the lag-resolved grid
     LagKey lk;
-    int timer = 0;       // kernel-time slot of the spectra stage (not part of the kernel choice)
+    int timer = 0;       // kernel-time slot of the spectra stage: bands of one round share it
     int DT = 0, window = 0, n_s = 0, nr = 0, n_cheb = kCheb;
     int wcols = 0, wqm = 0, wts = 0, wwv = 0;  // wide: bins of a class per lane, detector count,
                                                // segments a step, wavefronts a workgroup
@@ -1484,7 +1484,7 @@ struct Variant {
         return sp == o.sp && reg16 == o.reg16 && z4 == o.z4 && ss == o.ss && far == o.far && wide == o.wide &&
                DT == o.DT && window == o.window && n_s == o.n_s && nr == o.nr && n_cheb == o.n_cheb &&
                wcols == o.wcols && wqm == o.wqm && wts == o.wts && wwv == o.wwv && wallp == o.wallp && wns == o.wns && wps == o.wps &&
-               lag == o.lag && lk == o.lk && fold == o.fold;
+               lag == o.lag && lk == o.lk && fold == o.fold && timer == o.timer;
     }
 };
 
@@ -1766,6 +1766,8 @@ ccr_status build_plan(ccr_ctx *c, bool fp64, int n_bands, const int *band_ids, v
         }
         if (v.wps) cp.bands.back().ps2 = 1;
         if (bi == 0 && v.lag) cp.grid = {bd.lag.ns, bd.lag.P};
+        // bands that share a kernel but not its time slot share launches unless these are timed
+        if (!c->opt_timing) v.timer = 0;
         const int res_t = v.far ? kFarTemplates : kResTemplates;  // templates per resampler workgroup
         if (std::find(variants.begin(), variants.end(), v) == variants.end()) variants.push_back(v);
         const size_t y1 = ser1 * (v.wps ? 2 : 1);
@@ -2040,7 +2042,8 @@ ccr_status choose_params(ccr_ctx *c, ccr_precision prec, int n_bands, const int 
         max_seg = std::max<int64_t>(max_seg, B.plan.n_seg);
         const BandDev bd = band_dev(B, fp64);
         const Variant v0 = variant_of(bd, fp64, B.short_series, c->opt_farrow != 0, false);
-        const Variant v1 = variant_of(bd, fp64, B.short_series, c->opt_farrow != 0, true);
+        Variant v1 = variant_of(bd, fp64, B.short_series, c->opt_farrow != 0, true);
+        v1.timer = v0.timer;  // (the same kernel in another time slot is no choice)
         both = both || !(v0 == v1);
     }
     hipEvent_t e0 = nullptr, e1 = nullptr;

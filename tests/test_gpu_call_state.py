@@ -46,3 +46,27 @@ def test_grid_after_replay(ccr):
         ctx.compute_rho(ids[0], prec=ccr.PREC_SPLIT)
         assert ctx.kernel_times()["fused"][1] > 0
         assert ctx.get_option("grid_ns") == 0 and ctx.get_option("grid_classes") == 0
+
+
+def test_time_slots_of_bands_sharing_a_kernel(ccr):
+    """Slot 6 counts 256-point bands with the Gamma^ave weight that the 256-point kernel of higher lags
+    holds (up to 4 detectors), slot 7 every other band, also where one call's bands run on the same grid
+    kernel."""
+    kw = dict(n_seg=12, t_short=400.0, f_min=400.0, f_band=0.06, max_lag=1, a_p_max=2.0)
+    dss = [synth.make_dataset(small_config(q=q, **kw)) for q in (2, 5)]
+    with ccr.Context(dss[0].sky, device=0) as ctx:
+        ctx.set_option("timing", 1)
+        ids = [ctx.load(ds) for ds in dss]
+        alone, grids = [], []
+        for i in ids:
+            ctx.kernel_times(reset=True)
+            ctx.compute_rho(i, prec=ccr.PREC_SPLIT)
+            kt = ctx.kernel_times(reset=True)
+            alone.append((kt["spectra_pairs"][1], kt["spectra_wide"][1]))
+            grids.append((ctx.get_option("grid_ns"), ctx.get_option("grid_classes")))
+        assert alone == [(1, 0), (0, 1)] and grids[0] == grids[1] and grids[0][0] == 256
+        for order in (ids, ids[::-1]):
+            ctx.kernel_times(reset=True)
+            ctx.compute_rho(order, prec=ccr.PREC_SPLIT)
+            kt = ctx.kernel_times(reset=True)
+            assert kt["spectra_pairs"][1] == 1 and kt["spectra_wide"][1] == 1, kt
