@@ -188,7 +188,8 @@ const char *ccr_last_error(const ccr_ctx *ctx);
  *   "autotune"        1: on the first call for a given band list and precision, time the
  *                     first launch round of each candidate launch shape and keep the fastest
  *                     per template: the spectra kernel (where a band can take either) and
- *                     k_chunk = 32 ... 1024 on a round of at most 64 templates a band, then
+ *                     the chunks, every band's own (as with k_chunk 0, untuned) or k_chunk =
+ *                     32 ... 1024 for all bands, on a round of at most 64 templates a band, then
  *                     the templates per launch round (the workspace budget's batch, its half
  *                     and quarter) where timing those rounds stays below about 12 s (an
  *                     explicit "k_chunk" disables tuning);
@@ -205,7 +206,8 @@ ccr_status ccr_set_option(ccr_ctx *ctx, const char *name, int64_t value);
 
 /* Read an option set with ccr_set_option, or "tuned_k_chunk" / "tuned_template_batch" /
  * "tuned_round_templates" / "tuned_spectra_kernel": the launch shape the autotuner chose last
- * (0, or -1 for the kernel, before any tuning), or "resample_templates": the
+ * (0, or -1 for the kernel, before any tuning), "tuned_own_chunks": 1 where the bands' own chunks
+ * were faster still than the best common length, which tuned_k_chunk gives, and are used, or "resample_templates": the
  * templates one resampling workgroup handles from one staged input window (a constant of the
  * build), "farrow_templates" / "farrow_degree": the same for the Farrow-form kernel and its
  * polynomial degree, or "grid_ns" / "grid_classes": transform length and transforms per segment

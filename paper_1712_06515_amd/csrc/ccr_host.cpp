@@ -152,7 +152,7 @@ struct ccr_ctx {
         int spectra;
     };
     std::vector<Tuned> tuned;
-    int64_t last_tuned_k_chunk = 0, last_tuned_template_batch = 0, last_tuned_spectra = -1, last_tuned_round_templates = 0;
+    int64_t last_tuned_k_chunk = 0, last_tuned_own = 0, last_tuned_template_batch = 0, last_tuned_spectra = -1, last_tuned_round_templates = 0;
     GridInfo last_grid;  // first band of the last compute call
     struct Timed {
         int kind;
@@ -2012,8 +2012,9 @@ ccr_status upload_tables(ccr_ctx *c, const CallPlan &cp, hipStream_t s, size_t *
 // Launch shapes for a call: the tuned ones when autotuning is on.  Tuning on first use for a
 // band list and precision times the call for each candidate and keeps the fastest per template:
 //   1. the spectra kernel (where a band can take both the 256-point and the wide spectra +
-//      pair-sum kernel) and k_chunk = 32 ... 1024, on the first (at most) 64 templates of
-//      every band, in rounds of at most 64 templates;
+//      pair-sum kernel) and the chunks: every band's own (k_chunk 0, the untuned call's, which
+//      differ from band to band and go down to 16 segments), then k_chunk = 32 ... 1024 for all
+//      bands, on the first (at most) 64 templates of every band, in rounds of at most 64 templates;
 //   2. the templates per launch round: the workspace budget's batch (the largest) and its half
 //      and quarter, when the whole call is cheap enough to time (the estimate from step 1 for
 //      all candidates below about 12 s).
@@ -2085,10 +2086,10 @@ ccr_status choose_params(ccr_ctx *c, ccr_precision prec, int n_bands, const int 
     }
     {
         const int64_t t_tune = bp.template_batch > 0 ? bp.template_batch : std::min<int64_t>(t_auto, 64);
-        float best = -1.0f, best_round_ms = 0.0f;
+        float best = -1.0f, best_kc = -1.0f, best_round_ms = 0.0f;
         BatchParams bestp = bp;
         for (int sk = both ? 0 : bp.spectra; sk <= (both ? 1 : bp.spectra); ++sk)
-            for (int64_t kc = 32; kc <= 1024; kc *= 2) {
+            for (int64_t kc = 0; kc <= 1024; kc = kc == 0 ? 32 : 2 * kc) {
                 if (kc > 2 * max_seg && kc > 32) break;
                 BatchParams cand = bp;
                 cand.k_chunk = kc;
@@ -2099,6 +2100,10 @@ ccr_status choose_params(ccr_ctx *c, ccr_precision prec, int n_bands, const int 
                 float per = 0.0f;
                 int64_t nr = 0;
                 if ((st = trial(cand, per, nr))) goto done;
+                if (kc > 0 && (best_kc < 0.0f || per < best_kc)) {
+                    best_kc = per;
+                    c->last_tuned_k_chunk = kc;
+                }
                 if (best < 0.0f || per < best) {
                     best = per;
                     bestp = cand;
@@ -2142,7 +2147,7 @@ done:
     (void)hipEventDestroy(e1);
     if (st) return st;
     c->tuned.push_back({ids, (int)prec, bp.k_chunk, bp.template_batch, bp.round_templates, bp.spectra});
-    c->last_tuned_k_chunk = bp.k_chunk;
+    c->last_tuned_own = bp.k_chunk == 0;
     c->last_tuned_template_batch = bp.template_batch;
     c->last_tuned_spectra = bp.spectra;
     c->last_tuned_round_templates = bp.round_templates;
@@ -2378,6 +2383,7 @@ ccr_status ccr_get_option(ccr_ctx *c, const char *name, int64_t *value) {
     else if (k == "spectra_kernel") *value = c->opt_spectra_kernel;
     else if (k == "round_templates") *value = c->opt_round_templates;
     else if (k == "tuned_round_templates") *value = c->last_tuned_round_templates;
+    else if (k == "tuned_own_chunks") *value = c->last_tuned_own;
     else if (k == "grid_ns") *value = c->last_grid.ns;
     else if (k == "grid_classes") *value = c->last_grid.classes;
     else if (k == "resample_templates") *value = kResTemplates;

@@ -1,5 +1,6 @@
 """What a context reports about its last call."""
 
+import numpy as np
 import pytest
 
 import synth
@@ -70,3 +71,21 @@ def test_time_slots_of_bands_sharing_a_kernel(ccr):
             ctx.compute_rho(order, prec=ccr.PREC_SPLIT)
             kt = ctx.kernel_times(reset=True)
             assert kt["spectra_pairs"][1] == 1 and kt["spectra_wide"][1] == 1, kt
+
+
+def test_tuner_tries_the_bands_own_chunks(ccr):
+    """Few templates of a short series: the untuned call takes chunks of 16 segments, below every
+    length of the tuner's ladder, so the tuner times that shape too and reports when it keeps it."""
+    ds = synth.make_dataset(small_config(n_seg=480, t_short=360.0, f_min=99.875, f_band=0.25, max_lag=1))
+    with ccr.Context(ds.sky, device=0) as ctx:
+        bid = ctx.load(ds, templates=ds.templates[:1])
+        base = ctx.compute_rho(bid, prec=ccr.PREC_FP64)
+        assert ctx.get_option("tuned_own_chunks") == 0
+        ctx.set_option("autotune", 1)
+        tuned = ctx.compute_rho(bid, prec=ccr.PREC_FP64)
+        assert ctx.get_option("tuned_k_chunk") in (32, 64, 128, 256, 512, 1024)
+        assert np.max(np.abs(tuned - base)) < 1e-12 * max(1.0, np.abs(base).max())
+        # 16-segment chunks against the shortest of the ladder: twice the workgroups, half the steps a
+        # workgroup, on a GPU that neither fills
+        assert ctx.get_option("tuned_own_chunks") == 1
+        assert np.array_equal(tuned, base)
