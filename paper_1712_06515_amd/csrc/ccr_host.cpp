@@ -1605,20 +1605,19 @@ Variant variant_of(const BandDev &bd, bool fp64, bool short_series, bool farrow,
     return v;
 }
 
-// Segments per chunk when the caller and the tuner leave it open: 256, or fewer (not below 16) so
-// that a call of few templates or short series still gives the GPU about 4096 workgroups (4-8
-// wavefronts each on the grid; 8192 of the 256-point kernel's single wavefronts).  Shorter chunks
-// repeat more halo segments (R per chunk), so full calls keep 256; same-time pairs in registers have
-// no halo and no LDS to share out, a workgroup takes 16 segments a step, and up to 1024 segments a
-// chunk pay (512 templates: 128, 256, 512, 1024, 2048 segments 4.62, 4.66, 4.21, 4.06, 4.38 ms).  In FP64 the rule looks at the
-// band alone, never at the template count, which keeps results bitwise independent of how templates
-// are split over calls: 64 chunks a band.
+// Segments per chunk when the caller and the tuner leave it open: 256, or on the grid fewer (not below
+// 16) so that a call of few templates or short series still gives the GPU about 4096 workgroups of 4-8
+// wavefronts.  Shorter chunks repeat more halo segments (R per chunk), so full calls keep 256;
+// same-time pairs in registers have no halo and no LDS to share out, a workgroup takes 16 segments a
+// step, and up to 1024 segments a chunk pay (512 templates: 128, 256, 512, 1024, 2048 segments 4.62,
+// 4.66, 4.21, 4.06, 4.38 ms).  In FP64 the rule looks at the band alone, never at the template count,
+// which keeps results bitwise independent of how templates are split over calls: 64 chunks a band.
+// The kernels for any lag keep 256: where their chunks start decides which products they sum in FP32.
 int64_t default_chunk(const Band &B, const Variant &v, const BandDev &bd, bool fp64) {
     const int64_t M = B.plan.n_seg;
     int64_t chunks = 0;
     const int64_t most = v.lag && v.lk.same > 0 ? 1024 : 256;
     if (v.lag) chunks = fp64 ? 64 : (v.lk.same > 0 ? 16384 : 4096) / ((int64_t)B.n_tmpl * bd.lag.P * bd.lag.n_sub);
-    else if (v.sp) chunks = 8192 / B.n_tmpl;
     const int64_t kc = chunks > 0 ? std::max<int64_t>(16, M / chunks) : most;
     return std::min<int64_t>({kc, most, M});
 }

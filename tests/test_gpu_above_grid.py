@@ -89,3 +89,22 @@ def test_lags_above_the_grid(ccr, case):
     print(f"  split {err(r32):.2e} fp64 {err(r64):.2e} max|rho| {np.abs(ref).max():.2f}", flush=True)
     assert err(r32) < 1e-4 and err(r64) < 1e-10
     assert np.array_equal(r32, r32b)
+
+
+@pytest.mark.parametrize("q,pairs", [(1, 2), (2, 3)])
+def test_one_template_alone_and_in_a_list(ccr, q, pairs):
+    """The 256-point kernel sums the pair terms of up to 4 / Q segments in FP32; which segments share a
+    sum follows from where chunks start, so the chunks do not depend on the number of templates."""
+    cfg = small_config(q=q, n_seg=1500, t_short=400.0, f_min=400.0, f_band=0.03, max_lag=5, pairs=pairs, a_p_max=2.0,
+                       gap_fraction=0.2, templates=dict(a_p=(1.0, 2.0, 16), t_asc=(-200.0, 200.0, 16), period=[68023.70]))
+    ds = synth.make_dataset(cfg)
+    with ccr.Context(ds.sky, device=0) as ctx:
+        ctx.set_option("timing", 1)
+        bid = ctx.load(ds)
+        many = ctx.compute_rho(bid, prec=ccr.PREC_SPLIT)
+        assert ctx.kernel_times()["spectra_pairs"][1] > 0 and ctx.get_option("grid_ns") == 0
+        for t in (0, 200):
+            ctx.set_templates(bid, ds.templates[t:t + 1])
+            alone = ctx.compute_rho(bid, prec=ccr.PREC_SPLIT)[0]
+            differ = int(np.count_nonzero(alone != many[t]))
+            assert differ == 0
