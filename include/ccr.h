@@ -210,8 +210,9 @@ ccr_status ccr_set_option(ccr_ctx *ctx, const char *name, int64_t value);
  * were faster still than the best common length, which tuned_k_chunk gives, and are used, or "resample_templates": the
  * templates one resampling workgroup handles from one staged input window (a constant of the
  * build), "farrow_templates" / "farrow_degree": the same for the Farrow-form kernel and its
- * polynomial degree, or "grid_ns" / "grid_classes": transform length and transforms per segment
- * of the lag-resolved grid, for the first band of the last call (0: not on the grid).
+ * polynomial degree, or, of the lag-resolved grid that the first band of the last call ran on (0:
+ * none), "grid_ns" / "grid_classes": transform length and transforms per segment, "grid_wrap": 1 where
+ * every grid point is kept, "grid_taps": interpolation taps of an output bin.
  * CCR_EUNSUP for an unknown name. */
 ccr_status ccr_get_option(ccr_ctx *ctx, const char *name, int64_t *value);
 

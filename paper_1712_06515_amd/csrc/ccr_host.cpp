@@ -113,7 +113,7 @@ struct Band {
 
 // Lag-resolved grid that a band runs on, as ccr_get_option reports it (zeros: none).
 struct GridInfo {
-    int64_t ns = 0, classes = 0;
+    int64_t ns = 0, classes = 0, wrap = 0, taps = 0;
 };
 
 struct ccr_ctx {
@@ -1764,7 +1764,7 @@ ccr_status build_plan(ccr_ctx *c, bool fp64, int n_bands, const int *band_ids, v
             }
         }
         if (v.wps) cp.bands.back().ps2 = 1;
-        if (bi == 0 && v.lag) cp.grid = {bd.lag.ns, bd.lag.P};
+        if (bi == 0 && v.lag) cp.grid = {bd.lag.ns, bd.lag.P, bd.lag.wrap, bd.lag.taps};
         // bands that share a kernel but not its time slot share launches unless these are timed
         if (!c->opt_timing) v.timer = 0;
         const int res_t = v.far ? kFarTemplates : kResTemplates;  // templates per resampler workgroup
@@ -2385,6 +2385,8 @@ ccr_status ccr_get_option(ccr_ctx *c, const char *name, int64_t *value) {
     else if (k == "tuned_own_chunks") *value = c->last_tuned_own;
     else if (k == "grid_ns") *value = c->last_grid.ns;
     else if (k == "grid_classes") *value = c->last_grid.classes;
+    else if (k == "grid_wrap") *value = c->last_grid.wrap;
+    else if (k == "grid_taps") *value = c->last_grid.taps;
     else if (k == "resample_templates") *value = kResTemplates;
     else if (k == "farrow") *value = c->opt_farrow;
     else if (k == "farrow_stage") *value = c->opt_farrow_stage;
