@@ -297,18 +297,19 @@ struct LagDets {
 
 // Streams of one grid column at the step's kLagSegs segments from the spectra in LDS: NST = 2:
 // the sums over the detectors of hat a_X F_X and hat b_X F_X (n[t] = {A, B}); NST = 4 (two
-// detectors, pairs across them only): {a_0, a_1, b_0, b_1}.  s0: the same-time products of the
+// detectors, pairs across them only): {a_0, a_1, b_0, b_1}.  s0[t]: the same-time products of the
 // pairs X < Y, Re[conj(a_X) a_Y + conj(b_X) b_Y], or for Gamma^circ Im[conj(b_X) a_Y - conj(a_X) b_Y]
 // (a workgroup with more than one detector always sums pairs across them).  PS (per-sample
 // antenna functions): the two streams are transforms of their own.
 template <typename T, int ND, int NST, bool PS>
 __device__ __forceinline__ void lag_gather(const BandDev &B, const LagDets &D, const char *slots, int slot_bytes,
-                                           int col, int Kb, int nd, bool circ, T &s0, c2<T> (&n)[kLagSegs][NST]) {
+                                           int col, int Kb, int nd, bool circ, T (&s0)[kLagSegs], c2<T> (&n)[kLagSegs][NST]) {
     const int NDr = ND > 0 ? ND : nd;
     constexpr int NM = ND > 0 ? ND : CCR_MAX_DET_K;
 #pragma unroll
     for (int t = 0; t < kLagSegs; ++t) {
         c2<T> A = mk<T>((T)0, (T)0), Bs = A;
+        T z = sizeof(T) == 8 && t > 0 ? s0[t > 0 ? t - 1 : 0] : (T)0;
 #pragma unroll
         for (int i = 0; i < NM; ++i) {
             if (ND == 0 && i >= nd) continue;  // uniform
@@ -325,11 +326,11 @@ __device__ __forceinline__ void lag_gather(const BandDev &B, const LagDets &D, c
             }
             if (i > 0) {
                 if (circ) {
-                    s0 = fma(Bs.x, a.y, fma(-Bs.y, a.x, s0));
-                    s0 = fma(-A.x, b.y, fma(A.y, b.x, s0));
+                    z = fma(Bs.x, a.y, fma(-Bs.y, a.x, z));
+                    z = fma(-A.x, b.y, fma(A.y, b.x, z));
                 } else {
-                    s0 = fma(A.x, a.x, fma(A.y, a.y, s0));
-                    s0 = fma(Bs.x, b.x, fma(Bs.y, b.y, s0));
+                    z = fma(A.x, a.x, fma(A.y, a.y, z));
+                    z = fma(Bs.x, b.x, fma(Bs.y, b.y, z));
                 }
             }
             if constexpr (NST == 4) {
@@ -343,6 +344,7 @@ __device__ __forceinline__ void lag_gather(const BandDev &B, const LagDets &D, c
             n[t][0] = A;
             n[t][1] = Bs;
         }
+        s0[t] = z;
     }
 }
 
@@ -356,7 +358,7 @@ __device__ __forceinline__ void lag_gather(const BandDev &B, const LagDets &D, c
 //   buffer.  Units of absent segments write zeros.  The next unit's input is loaded meanwhile.
 //   Pair sums.  Lane j of the workgroup owns column j: it forms the step's streams, multiplies each segment's with those of the RM segments before it -- the step's own
 //   or the last step's, kept in registers -- and adds them to S_1 .. S_RM (lags above R are
-//   computed and dropped).  FP32 products of a step are summed in FP32, steps in FP64.
+//   computed and dropped).  FP32 products of a segment are summed in FP32, segments in FP64.
 // Two barriers a step.  Partials: [comp][P][span], comp 0: S_0 (same-time pairs across
 // detectors), 2 d - 1 and 2 d: Re and Im of S_d.
 //
@@ -378,6 +380,7 @@ __device__ __forceinline__ void lag_body(const BandDev &B, const c2<T> *__restri
     constexpr int S = PS ? 2 : 1;
     constexpr int NST = CR ? 4 : 2;
     constexpr bool LTW = lag_tw_lds(NS, sizeof(T) == 8) > 0;
+    constexpr bool ALL64 = sizeof(T) == 8;  // a step's products have one sum
     const LagDev &G = B.lag;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int W = blockDim.x >> 6;
@@ -602,7 +605,7 @@ __device__ __forceinline__ void lag_body(const BandDev &B, const c2<T> *__restri
         __syncthreads();
         if (wv * 64 < span) {  // uniform: some lane of this wavefront has a column
             c2<T> n[kLagSegs][NST];
-            T s0 = (T)0;
+            T s0[kLagSegs];
             if constexpr (CR) {
                 lag_gather<T, 2, NST, PS>(B, D, slots, slot_bytes, col, Kb, nd, circ, s0, n);
             } else {
@@ -614,7 +617,8 @@ __device__ __forceinline__ void lag_body(const BandDev &B, const c2<T> *__restri
                 }
             }
             if (Kb >= K0) {  // uniform; halo segments only enter the history
-                acc0 += (double)s0;
+#pragma unroll
+                for (int t = ALL64 ? kLagSegs - 1 : 0; t < kLagSegs; ++t) acc0 += (double)s0[t];
                 if constexpr (RM > 0) {
                     T st[2 * RM];
 #pragma unroll
@@ -635,16 +639,26 @@ __device__ __forceinline__ void lag_body(const BandDev &B, const c2<T> *__restri
                         }
 #pragma unroll
                         for (int d = 1; d <= RM; ++d) {
+                            T re = ALL64 ? st[2 * d - 2] : (T)0, im = ALL64 ? st[2 * d - 1] : (T)0;
 #pragma unroll
                             for (int j = 0; j < NST; ++j) {
                                 const c2<T> h = t >= d ? n[t >= d ? t - d : 0][j] : hist[d > t ? d - t - 1 : 0][j];
-                                st[2 * d - 2] = fma(x[j].x, h.x, fma(x[j].y, h.y, st[2 * d - 2]));
-                                st[2 * d - 1] = fma(x[j].x, h.y, fma(-x[j].y, h.x, st[2 * d - 1]));
+                                re = fma(x[j].x, h.x, fma(x[j].y, h.y, re));
+                                im = fma(x[j].x, h.y, fma(-x[j].y, h.x, im));
+                            }
+                            if constexpr (ALL64) {
+                                st[2 * d - 2] = re;
+                                st[2 * d - 1] = im;
+                            } else {
+                                acc[2 * d - 2] += (double)re;
+                                acc[2 * d - 1] += (double)im;
                             }
                         }
                     }
+                    if constexpr (ALL64) {
 #pragma unroll
-                    for (int k = 0; k < 2 * RM; ++k) acc[k] += (double)st[k];
+                        for (int k = 0; k < 2 * RM; ++k) acc[k] += (double)st[k];
+                    }
                 }
             }
             // the step's last RM segments become the history (kLagSegs >= RM)

@@ -1,0 +1,92 @@
+"""What the sums of the lag-resolved grid keep of the kernels before it, in split precision.
+
+- Products of a segment are summed in FP32, segments in FP64: the sum over all segments is the sum of the
+  parts, each with every other segment's weights set to zero, to FP64 rounding; so a template's rho
+  (FP32 output) has the same bits alone and in a list, whatever chunks of segments the list gives."""
+
+import numpy as np
+import pytest
+
+import synth
+from conftest import small_config
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ccr():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_1712_06515_amd import ccr as mod
+    mod.load_library()
+    return mod
+
+
+def dataset(n_k, ts=400.0, fb=0.1, weight=0, **kw):
+    cfg = small_config(t_short=ts, f_min=100.0, f_band=fb, a_p_max=2.0, **kw)
+    cfg["n_k"] = n_k
+    cfg["band"]["weight"] = weight
+    return synth.make_dataset(cfg, sigma_wander=0.2)
+
+
+LISTS = {
+    # (detectors, lag, N_K, T_short): same-time pairs in registers, 256-, 512- and 1024-point classes
+    "q2_lag0_nk179": (2, 0, 179, 400.0),
+    "q3_lag1_nk179": (3, 1, 179, 400.0),
+    "q2_lag3_nk500": (2, 3, 500, 900.0),
+    "q2_lag4_nk870": (2, 4, 870, 1440.0),
+}
+
+
+@pytest.mark.parametrize("case", sorted(LISTS))
+def test_one_template_alone_and_in_a_list(ccr, case):
+    q, R, n_k, ts = LISTS[case]
+    ds = dataset(n_k, ts=ts, q=q, n_seg=1500, max_lag=R, gap_fraction=0.2,
+                 templates=dict(a_p=(1.0, 2.0, 8), t_asc=(-200.0, 200.0, 8), period=[68023.70]))
+    with ccr.Context(ds.sky, device=0) as ctx:
+        bid = ctx.load(ds)
+        print(case, flush=True)
+        many = ctx.compute_rho(bid, prec=ccr.PREC_SPLIT, out_fp64=False)
+        assert ctx.get_option("grid_ns") > 0
+        for t in (0, 51):
+            ctx.set_templates(bid, ds.templates[t:t + 1])
+            alone = ctx.compute_rho(bid, prec=ccr.PREC_SPLIT, out_fp64=False)[0]
+            differ = int(np.count_nonzero(alone != many[t]))
+            assert differ == 0
+
+
+ADDITIVE = {
+    # (detectors, lag, pair kinds, weight, N_K, T_short)
+    "q2_lag0_nk500": (2, 0, 1, 0, 500, 900.0),
+    "q2_lag1_nk179": (2, 1, 3, 0, 179, 400.0),
+    "q3_lag1_nk179_circ": (3, 1, 3, 1, 179, 400.0),
+    "q2_lag4_nk870": (2, 4, 3, 0, 870, 1440.0),
+    "q3_lag2_nk500_cross": (3, 2, 1, 0, 500, 900.0),
+}
+
+
+@pytest.mark.parametrize("case", sorted(ADDITIVE))
+def test_segments_add_in_fp64(ccr, case):
+    q, R, pairs, weight, n_k, ts = ADDITIVE[case]
+    n_seg = 12
+    ds = dataset(n_k, ts=ts, weight=weight, q=q, n_seg=n_seg, max_lag=R, pairs=pairs)
+    with ccr.Context(ds.sky, device=0) as ctx:
+        bid = ctx.load(ds)
+
+        def total(keep):
+            for X in range(q):
+                k = np.isin(np.arange(n_seg), keep)
+                ctx.set_weights(bid, X, np.where(k, ds.a[X], 0.0), np.where(k, ds.b[X], 0.0), ds.noise_var[X])
+            ctx.set_templates(bid, ds.templates)
+            norm = ctx.band_info(bid)["norm"]
+            return norm * ctx.compute_rho(bid, prec=ccr.PREC_SPLIT) if norm > 0 else 0.0
+
+        print(case, flush=True)
+        whole = total(range(n_seg))
+        # pairs of later segment K: those of the segments K - R .. K less those of K - R .. K - 1
+        parts = 0.0
+        for K in range(n_seg):
+            parts = parts + total(range(max(0, K - R), K + 1)) - total(range(max(0, K - R), K))
+    # FP64 rounding of at most 2 n_seg sums of these magnitudes, and of the interpolation's ~400 taps
+    assert np.abs(whole - parts).max() <= 1e-13 * np.abs(whole).max()
