@@ -172,6 +172,7 @@ __device__ __forceinline__ BandDev global_view(const BandDev &b, const void *bas
         g.lag.g0 = as_global(b.lag.g0, base);
         g.lag.frac = as_global(b.lag.frac, base);
         g.lag.wt = as_global(b.lag.wt, base);
+        if (b.lag.pairw) g.lag.pairw = as_global(b.lag.pairw, base);
     }
     return g;
 }

@@ -328,6 +328,11 @@ int lag_dets(int Q, int R, int pairs) {
     return pairs == CCR_PAIRS_SAME ? 1 : 2;
 }
 
+// Whether a planned grid's pairs are same-time pairs formed in registers (k_lag_same).
+bool lag_same(const LagDev &d, int R, int64_t n_k, bool streams, bool fp64) {
+    return R == 0 && !streams && lag_quad(d.ns, fp64) && d.nfold == 1 && n_k <= 256;
+}
+
 // Host tables of a band's grid.
 struct LagTables {
     std::vector<float2> tw32, step32;
@@ -981,7 +986,7 @@ ccr_status prepare(ccr_ctx *c, Band &B) {
                 if (seg_work[(size_t)X * M + K] >= 0) bits[(size_t)K] |= 1u << X;
         B.off_segwd = put(segwd);
         B.off_seg_bits = put(bits);
-        size_t off[2][7] = {};
+        size_t off[2][8] = {};
         for (int f = 0; f < 2; ++f) {
             LagGrid &L = B.lag[f];
             if (!lag_plan(pl, B.p, Q, per_sample, f == 1, L.d)) continue;
@@ -1007,6 +1012,16 @@ ccr_status prepare(ccr_ctx *c, Band &B) {
                 std::vector<float2> wf(wd.size());
                 for (size_t e = 0; e < wd.size(); ++e) wf[e] = make_float2((float)wd[e].x, (float)wd[e].y);
                 off[f][5] = put(wf);
+            }
+            if (lag_same(L.d, R, nk, per_sample, f == 1) && Q >= 2 && Q <= 4) {
+                std::vector<float> pw;
+                for (int64_t K = 0; K < M; ++K)
+                    for (int Y = 1; Y < Q; ++Y)
+                        for (int X = 0; X < Y; ++X) {
+                            const double2 wx = segwd[(size_t)X * M + K], wy = segwd[(size_t)Y * M + K];
+                            pw.push_back((float)(circ ? wy.x * wx.y - wy.y * wx.x : wx.x * wy.x + wx.y * wy.y));
+                        }
+                off[f][7] = put(pw);
             }
             const int nd = lag_dets(Q, R, B.p.pairs);
             std::vector<uint32_t> sb((size_t)L.d.n_sub * row, 0);
@@ -1039,6 +1054,7 @@ ccr_status prepare(ccr_ctx *c, Band &B) {
                 d.segwf = reinterpret_cast<const float2 *>(base + off[f][5]);
                 d.tw32 = reinterpret_cast<const float2 *>(base + off[f][0]);
                 d.step32 = reinterpret_cast<const float2 *>(base + off[f][1]);
+                if (off[f][7]) d.pairw = reinterpret_cast<const float *>(base + off[f][7]);
             }
             d.g0 = reinterpret_cast<const int *>(base + off[f][2]);
             d.frac = reinterpret_cast<const int *>(base + off[f][3]);
@@ -1548,10 +1564,10 @@ bool lag_fits(const BandDev &bd, bool fp64, LagKey &k) {
     // the others (six bands, 3 detectors, lag 1, 256 points: 2 for spans up to 128, then 3, against 2
     // or 4: 5.72 -> 5.19 ms; 3 at least 5.44; 1 for spans up to 64 5.44)
     k.waves = std::max(2, (bd.lag.span + 63) / 64);
-    if (bd.R == 0 && !k.ps && lag_quad(k.ns, fp64) && bd.lag.nfold == 1) {
+    if (lag_same(bd.lag, bd.R, bd.n_k, k.ps, fp64)) {
         k.same = bd.lag.span <= 96 ? 6 : 16;
         k.rows = bd.n_k <= 128 ? 8 : (bd.n_k <= 192 ? 12 : 16);
-        k.dets = bd.Q == 2 || bd.Q == 3 ? bd.Q : 0;
+        k.dets = bd.lag.pairw ? bd.Q : 0;
         k.circ = false;  // the weight is read at run time
         k.waves = 4;
     }

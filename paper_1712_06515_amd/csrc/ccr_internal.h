@@ -74,6 +74,9 @@ struct LagDev {
     // [Q][n_seg + 2 kLagSegs] pair weights (hat a scale, hat b scale), zero for absent segments
     const float2 *segwf;
     const double2 *segwd;
+    // same-time pairs of 2 to 4 detectors in FP32, 256 points: [n_seg][Q (Q - 1) / 2] weight of the pair
+    // X < Y at Y (Y - 1) / 2 + X, formed in FP64 and rounded once (null: other forms)
+    const float *pairw;
     // [n_sub][n_seg + 2 kLagSegs] entry kLagSegs + K, K >= -kLagSegs: bit t n + i set when segment
     // K + t of the problem's i-th of n detectors has a spectrum, t < kLagSegs
     const uint32_t *step_bits;
@@ -273,7 +276,7 @@ constexpr int kLagFinThreads = 256;
 struct LagKey {
     int ns = 0, rm = 0, waves = 0;
     // same-time pairs of 256 points in FP32: outputs (6 or 16) and input rows (8, 12 or 16) a lane,
-    // detectors (2, 3, or 0: any number); same = 0: the other kernel
+    // detectors (2, 3, 4, or 0: any number); same = 0: the other kernel
     int same = 0, rows = 0, dets = 0;
     bool cross = false, ps = false, circ = false;
     bool operator==(const LagKey &o) const {

@@ -710,8 +710,10 @@ __device__ __forceinline__ int lower_wave(const int *x, int n, int key, int lane
 // 128, 192 or 256; of 12 and 16 all but the last four are full, and only these need their ends looked at.
 // The pairs of detector Y with those before it add F_Y . sum_X (wa_Y u_X + wb_Y v_X) G_X (a product
 // of 2-vectors) with weights wa, wb = hat a, hat b times the scale, u = wa, v = wb and G = F; for
-// Gamma^circ u = wb, v = -wa and G = i F.  QK = 2 or 3 detectors: the G_X are kept as they are; any
-// other number (QK = 0): as the sums of u_X G_X and of v_X G_X.
+// Gamma^circ u = wb, v = -wa and G = i F.  QK = 2 to 4 detectors: the G_X are kept as they are and the
+// pair weights wa_Y u_X + wb_Y v_X come from the band's table (formed in FP64, rounded once: as
+// products of FP32 factors they were off by up to three roundings); any other number (QK = 0): as the
+// sums of u_X G_X and of v_X G_X.
 //
 // (One workgroup for both classes, in step so that they read the segments together: 4.33 ms instead
 // of 4.06, though the two read the series 1.9 times over: that traffic does not set the time.)
@@ -747,9 +749,12 @@ __device__ __forceinline__ void lag_same_body(const BandDev &B, const float2 *__
 
     auto seg = [&](int e) { return e < hi ? B.seg_any[e] : -1; };
     auto det_bits = [&](int K) { return K >= 0 ? B.seg_bits[K] : 0u; };
-    float2 nxt[NR], wn;
-    // input and weights of detector i of this group's segment K; on: it has a spectrum.  Rows past
-    // N_K and segments without one read past the buffer's range, which gives zero.
+    constexpr int NPW = QK > 0 ? QK * (QK - 1) / 2 : 1;
+    float2 nxt[NR], wn = make_float2(0.0f, 0.0f);
+    float pwn[QK > 1 ? QK - 1 : 1];
+    // input of detector i of this group's segment K and its weights, or those of its pairs with the
+    // detectors before it; on: it has a spectrum.  Rows past N_K and segments without one read past the
+    // buffer's range, which gives zero.
     auto load = [&](int K, bool on, int i) {
         const unsigned at = on ? ((unsigned)i * nr + (unsigned)(K * n_k + t)) * 8u : kLagNone;
         const unsigned last = t < nlast ? at : kLagNone;
@@ -760,8 +765,14 @@ __device__ __forceinline__ void lag_same_body(const BandDev &B, const float2 *__
             const unsigned o = r < NF || 16 * r + 16 <= n ? at : (16 * r < n ? last : kLagNone);
             nxt[r] = __builtin_bit_cast(float2, __builtin_amdgcn_raw_buffer_load_b64(rs, (int)(o + 128u * r), 0, 0));
         }
-        wn = make_float2(0.0f, 0.0f);
-        if (on) wn = G.segwf[i * (B.n_seg + 2 * kLagSegs) + kLagSegs + K];
+        if constexpr (QK > 0) {
+#pragma unroll
+            for (int X = 0; X < QK - 1; ++X)
+                if (X < i) pwn[X] = on ? G.pairw[K * NPW + i * (i - 1) / 2 + X] : 0.0f;
+        } else {
+            wn = make_float2(0.0f, 0.0f);
+            if (on) wn = G.segwf[i * (B.n_seg + 2 * kLagSegs) + kLagSegs + K];
+        }
     };
 
     double acc[NO];
@@ -798,28 +809,29 @@ __device__ __forceinline__ void lag_same_body(const BandDev &B, const float2 *__
         auto turned = [&](float2 f) { return circ ? make_float2(-f.y, f.x) : f; };
         if constexpr (QK > 0) {
             float2 G_[QK - 1][NO];
-            float2 uv[QK - 1];
 #pragma unroll
             for (int i = 0; i < QK; ++i) {
-                const float2 w = wn;
+                float pw[QK - 1];
+#pragma unroll
+                for (int X = 0; X < QK - 1; ++X) pw[X] = pwn[X];
                 float2 v[16];
                 spectra(v, i);
-                float pw[QK];
-#pragma unroll
-                for (int X = 0; X < i; ++X) pw[X] = fma(w.x, uv[X].x, w.y * uv[X].y);
 #pragma unroll
                 for (int k = 0; k < NO; ++k) {
                     const float2 f = v[4 * (k & 3) + (k >> 2)];
                     if (i == 1) {
                         acc[k] += (double)(pw[0] * fma(f.x, G_[0][k].x, f.y * G_[0][k].y));
-                    } else if (i == 2) {
-                        const float cx = fma(pw[0], G_[0][k].x, pw[1] * G_[QK - 2][k].x);
-                        const float cy = fma(pw[0], G_[0][k].y, pw[1] * G_[QK - 2][k].y);
+                    } else if (i > 1) {
+                        float cx = pw[i - 1] * G_[i - 1][k].x, cy = pw[i - 1] * G_[i - 1][k].y;
+#pragma unroll
+                        for (int X = i - 2; X >= 0; --X) {
+                            cx = fma(pw[X], G_[X][k].x, cx);
+                            cy = fma(pw[X], G_[X][k].y, cy);
+                        }
                         acc[k] += (double)fma(f.x, cx, f.y * cy);
                     }
                     if (i + 1 < QK) G_[i][k] = turned(f);
                 }
-                if (i + 1 < QK) uv[i] = circ ? make_float2(w.y, -w.x) : w;
             }
         } else {
             float2 A[NO], Bs[NO];
@@ -1028,6 +1040,7 @@ hipError_t launch_lag_m(const LagKey &k, const BandDev *bands, const WorkItem *i
 #define CCR_SAME_Q(NO_, NR_)                   \
     if (k.dets == 2) CCR_SAME(NO_, NR_, 2);    \
     else if (k.dets == 3) CCR_SAME(NO_, NR_, 3); \
+    else if (k.dets == 4) CCR_SAME(NO_, NR_, 4); \
     else CCR_SAME(NO_, NR_, 0)
         switch (k.same + k.rows) {
             case 6 + 8: CCR_SAME_Q(6, 8); break;

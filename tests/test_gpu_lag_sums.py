@@ -2,7 +2,9 @@
 
 - Products of a segment are summed in FP32, segments in FP64: the sum over all segments is the sum of the
   parts, each with every other segment's weights set to zero, to FP64 rounding; so a template's rho
-  (FP32 output) has the same bits alone and in a list, whatever chunks of segments the list gives."""
+  (FP32 output) has the same bits alone and in a list, whatever chunks of segments the list gives.
+- 256-point bands, Gamma^ave: a pair's weight enters rounded to FP32 once (2^-24), not as products of
+  rounded factors."""
 
 import numpy as np
 import pytest
@@ -90,3 +92,56 @@ def test_segments_add_in_fp64(ccr, case):
             parts = parts + total(range(max(0, K - R), K + 1)) - total(range(max(0, K - R), K))
     # FP64 rounding of at most 2 n_seg sums of these magnitudes, and of the interpolation's ~400 taps
     assert np.abs(whole - parts).max() <= 1e-13 * np.abs(whole).max()
+
+
+def weights_rounded_badly(n_k):
+    """(hat a_K, hat a_L) with sigma = 1, b = 0 whose FP32 factors' FP32 product is furthest from the pair
+    weight among 20000 draws, and that distance (relative)."""
+    rng = np.random.default_rng(3)
+    a = rng.uniform(0.5, 1.0, (20000, 2))
+    f = (a / np.sqrt(n_k)).astype(np.float32)
+    w = a[:, 0] * a[:, 1] / n_k
+    e = np.abs((f[:, 0] * f[:, 1]).astype(np.float64) / w - 1.0)
+    i = int(np.argmax(e))
+    return a[i], float(e[i])
+
+
+PAIR_WEIGHT = {
+    # (detectors, lag, the two (detector, segment) entries of the one pair, N_K); away from the ends,
+    # whose segments the Earth's orbit moves out of the data
+    "q2_lag0": (2, 0, (0, 4), (1, 4), 179),
+    "q3_lag0_first_third": (3, 0, (0, 3), (2, 3), 256),
+    "q4_lag0_second_fourth": (4, 0, (1, 4), (3, 4), 100),
+}
+
+
+@pytest.mark.parametrize("case", sorted(PAIR_WEIGHT))
+def test_pair_weight_rounded_once(ccr, case):
+    """One pair carries all the weight, so the unnormalised sum is its weight times a product of spectra
+    that no weight enters: two sets of weights differ by the ratio of the pair weights, up to one rounding
+    (2^-24; the reference weight and its factors are powers of two) and, averaged over ~1e4 bins and
+    templates, 1e-9 of the products' own rounding."""
+    q, R, (X, K), (Y, L), n_k = PAIR_WEIGHT[case]
+    n_seg = 9
+    ds = dataset(n_k, fb=0.05 if n_k < 150 else 0.1, q=q, n_seg=n_seg, max_lag=R, pairs=2 if q == 1 else 3,
+                 templates=dict(a_p=(1.0, 2.0, 16), t_asc=(-900.0, 900.0, 16), period=[68023.70]))
+    bad, off = weights_rounded_badly(n_k)
+    assert off > 1.1e-7
+    with ccr.Context(ds.sky, device=0) as ctx:
+        bid = ctx.load(ds)
+
+        def unnormalised(ak, al):
+            a = np.zeros((q, n_seg))
+            a[X, K], a[Y, L] = ak, al
+            for d in range(q):
+                ctx.set_weights(bid, d, a[d], np.zeros(n_seg), np.ones(n_seg))
+            ctx.set_templates(bid, ds.templates)
+            return ctx.band_info(bid)["norm"] * ctx.compute_rho(bid, prec=ccr.PREC_SPLIT)
+
+        print(case, flush=True)
+        s_ref = unnormalised(np.sqrt(n_k) / 16.0, np.sqrt(n_k) / 16.0)
+        s_bad = unnormalised(bad[0], bad[1])
+        assert ctx.get_option("grid_ns") == 256
+    ratio = float((s_bad * s_ref).sum() / (s_ref * s_ref).sum()) / (bad[0] * bad[1] / n_k * 256.0) - 1.0
+    print(f"  pair weight off by {ratio:.2e}, products of rounded factors by {off:.2e}", flush=True)
+    assert abs(ratio) <= 2.0**-24 + 2e-9
