@@ -1001,11 +1001,22 @@ ccr_status prepare(ccr_ctx *c, Band &B) {
             off[f][2] = put(t.g0);
             off[f][3] = put(t.frac);
             off[f][4] = put(t.wt);
+            // products of spectra that no weight has entered yet are brought near 1 / sigma, as weighted
+            // ones are: the weights have the scale of 1 / sigma^2
+            const bool same_time = lag_same(L.d, R, nk, per_sample, f == 1);
+            int e2 = 0;
+            if (same_time) {
+                double most = 0.0;
+                for (const double2 &w : segwd) most = std::max({most, std::fabs(w.x), std::fabs(w.y)});
+                if (most > 0.0) e2 = std::min(126, std::max(-126, std::ilogb(most)));
+            }
+            L.d.scale = (float)std::ldexp(1.0, e2);
             // per-detector weights and per-problem activity with a step of zeros at either end
             const size_t row = (size_t)M + 2 * kLagSegs;
             std::vector<double2> wd((size_t)Q * row, make_double2(0.0, 0.0));
             for (int X = 0; X < Q; ++X)
                 for (int64_t K = 0; K < M; ++K) wd[X * row + kLagSegs + K] = segwd[(size_t)X * M + K];
+            for (double2 &w : wd) w = make_double2(std::ldexp(w.x, -e2), std::ldexp(w.y, -e2));
             if (f == 1) {
                 off[f][5] = put(wd);
             } else {
@@ -1013,12 +1024,12 @@ ccr_status prepare(ccr_ctx *c, Band &B) {
                 for (size_t e = 0; e < wd.size(); ++e) wf[e] = make_float2((float)wd[e].x, (float)wd[e].y);
                 off[f][5] = put(wf);
             }
-            if (lag_same(L.d, R, nk, per_sample, f == 1) && Q >= 2 && Q <= 4) {
+            if (same_time && Q >= 2 && Q <= 4) {
                 std::vector<float> pw;
                 for (int64_t K = 0; K < M; ++K)
                     for (int Y = 1; Y < Q; ++Y)
                         for (int X = 0; X < Y; ++X) {
-                            const double2 wx = segwd[(size_t)X * M + K], wy = segwd[(size_t)Y * M + K];
+                            const double2 wx = wd[X * row + kLagSegs + K], wy = wd[Y * row + kLagSegs + K];
                             pw.push_back((float)(circ ? wy.x * wx.y - wy.y * wx.x : wx.x * wy.x + wx.y * wy.y));
                         }
                 off[f][7] = put(pw);

@@ -74,7 +74,10 @@ struct LagDev {
     // [Q][n_seg + 2 kLagSegs] pair weights (hat a scale, hat b scale), zero for absent segments
     const float2 *segwf;
     const double2 *segwd;
-    // same-time pairs of 2 to 4 detectors in FP32, 256 points: [n_seg][Q (Q - 1) / 2] weight of the pair
+    // same-time pairs in FP32, 256 points: power of two that the spectra are multiplied with, about the
+    // largest weight, and that segwf and pairw (by its square) are divided by
+    float scale;
+    // the same, 2 to 4 detectors: [n_seg][Q (Q - 1) / 2] weight of the pair
     // X < Y at Y (Y - 1) / 2 + X, formed in FP64 and rounded once (null: other forms)
     const float *pairw;
     // [n_sub][n_seg + 2 kLagSegs] entry kLagSegs + K, K >= -kLagSegs: bit t n + i set when segment

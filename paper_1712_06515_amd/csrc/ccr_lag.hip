@@ -125,12 +125,12 @@ template <typename T, int NS> struct LagTw<T, NS, true> {
 // same arithmetic a transform and a quarter of the per-unit overhead (six bands of 3 detectors with
 // lag 1, whole call: 8.5 -> 8.3 ms; same-time pairs: see k_lag_same).  l: the factors
 // W256^(k t) W^(q t) of the first pass's output k, q as above (16 x 16, LDS, one copy a workgroup;
-// the groups' reads coincide).
+// the groups' reads coincide), times `scale`, which multiplies the spectra.
 struct LagTwQuad {
     const float2 *l;
-    __device__ __forceinline__ void load(const float2 *tw, float2 *lds, int P, int q, int lane) {
+    __device__ __forceinline__ void load(const float2 *tw, float2 *lds, int P, int q, int lane, float scale = 1.0f) {
         for (int e = threadIdx.x; e < 256; e += blockDim.x)
-            lds[e] = tw[((unsigned)(P * (e >> 4) + q) * (unsigned)(e & 15)) % (unsigned)(P * 256)];
+            lds[e] = cscale<float>(tw[((unsigned)(P * (e >> 4) + q) * (unsigned)(e & 15)) % (unsigned)(P * 256)], scale);
         l = lds + (lane & 15);
         __syncthreads();
     }
@@ -713,7 +713,8 @@ __device__ __forceinline__ int lower_wave(const int *x, int n, int key, int lane
 // Gamma^circ u = wb, v = -wa and G = i F.  QK = 2 to 4 detectors: the G_X are kept as they are and the
 // pair weights wa_Y u_X + wb_Y v_X come from the band's table (formed in FP64, rounded once: as
 // products of FP32 factors they were off by up to three roundings); any other number (QK = 0): as the
-// sums of u_X G_X and of v_X G_X.
+// sums of u_X G_X and of v_X G_X.  The twiddles carry a power of two (G.scale) that keeps unweighted
+// products of spectra as far from FP32's ends as weighted ones, whatever the data's unit.
 //
 // (One workgroup for both classes, in step so that they read the segments together: 4.33 ms instead
 // of 4.06, though the two read the series 1.9 times over: that traffic does not set the time.)
@@ -734,7 +735,7 @@ __device__ __forceinline__ void lag_same_body(const BandDev &B, const float2 *__
     const int n_k = B.n_k, Q = QK > 0 ? QK : B.Q, P = G.P, span = G.span;
     const bool circ = B.weight != 0;
     LagTwQuad tw;
-    tw.load(G.tw32, reinterpret_cast<float2 *>(smem), P, (p + P * G.m0) % G.ng, lane);
+    tw.load(G.tw32, reinterpret_cast<float2 *>(smem), P, (p + P * G.m0) % G.ng, lane, G.scale);
     char *ex = smem + lag_tw_lds(256, false) + wv * 4 * kLagQuadSlot;
     const float2 *step = G.step32 + (size_t)p * 16;
 

@@ -4,7 +4,9 @@
   parts, each with every other segment's weights set to zero, to FP64 rounding; so a template's rho
   (FP32 output) has the same bits alone and in a list, whatever chunks of segments the list gives.
 - 256-point bands, Gamma^ave: a pair's weight enters rounded to FP32 once (2^-24), not as products of
-  rounded factors."""
+  rounded factors.
+- Data scaled by a power of two with its noise variance gives the same bits: no weight or product of
+  spectra leaves the range of FP32 before rho itself would."""
 
 import numpy as np
 import pytest
@@ -145,3 +147,26 @@ def test_pair_weight_rounded_once(ccr, case):
     ratio = float((s_bad * s_ref).sum() / (s_ref * s_ref).sum()) / (bad[0] * bad[1] / n_k * 256.0) - 1.0
     print(f"  pair weight off by {ratio:.2e}, products of rounded factors by {off:.2e}", flush=True)
     assert abs(ratio) <= 2.0**-24 + 2e-9
+
+
+SCALED = {"lag0_circ": (0, 1), "lag0_ave": (0, 0), "lag1_ave": (1, 0), "lag1_circ": (1, 1)}
+
+
+@pytest.mark.parametrize("case", sorted(SCALED))
+@pytest.mark.parametrize("q", [2, 3, 5])
+def test_power_of_two_scaled_data(ccr, case, q):
+    R, weight = SCALED[case]
+    ds = dataset(179, weight=weight, q=q, n_seg=20, max_lag=R, gap_fraction=0.2)
+    with ccr.Context(ds.sky, device=0) as ctx:
+        out = []
+        for e in (0, -40, 40):
+            print(case, q, e, flush=True)
+            bid = ctx.load(ds)
+            for X in range(q):
+                ctx.set_data(bid, X, ds.sites[X], ds.t0, ds.dt, ds.x[X] * np.float32(2.0**e), ds.f_het, ds.valid[X])
+                ctx.set_weights(bid, X, ds.a[X], ds.b[X], ds.noise_var[X] * 2.0**(2 * e))
+            ctx.set_templates(bid, ds.templates)
+            out.append(ctx.compute_rho(bid, prec=ccr.PREC_SPLIT))
+    assert np.abs(out[0]).max() > 1.0
+    differ = [int(np.count_nonzero(out[0] != o)) for o in out[1:]]
+    assert differ == [0, 0]
