@@ -986,7 +986,7 @@ ccr_status prepare(ccr_ctx *c, Band &B) {
                 if (seg_work[(size_t)X * M + K] >= 0) bits[(size_t)K] |= 1u << X;
         B.off_segwd = put(segwd);
         B.off_seg_bits = put(bits);
-        size_t off[2][8] = {};
+        size_t off[2][9] = {};
         for (int f = 0; f < 2; ++f) {
             LagGrid &L = B.lag[f];
             if (!lag_plan(pl, B.p, Q, per_sample, f == 1, L.d)) continue;
@@ -1023,6 +1023,9 @@ ccr_status prepare(ccr_ctx *c, Band &B) {
                 std::vector<float2> wf(wd.size());
                 for (size_t e = 0; e < wd.size(); ++e) wf[e] = make_float2((float)wd[e].x, (float)wd[e].y);
                 off[f][5] = put(wf);
+                for (size_t e = 0; e < wd.size(); ++e)
+                    wf[e] = make_float2((float)(wd[e].x - (double)wf[e].x), (float)(wd[e].y - (double)wf[e].y));
+                off[f][8] = put(wf);
             }
             if (same_time && Q >= 2 && Q <= 4) {
                 std::vector<float> pw;
@@ -1065,6 +1068,7 @@ ccr_status prepare(ccr_ctx *c, Band &B) {
                 d.segwf = reinterpret_cast<const float2 *>(base + off[f][5]);
                 d.tw32 = reinterpret_cast<const float2 *>(base + off[f][0]);
                 d.step32 = reinterpret_cast<const float2 *>(base + off[f][1]);
+                d.segwl = reinterpret_cast<const float2 *>(base + off[f][8]);
                 if (off[f][7]) d.pairw = reinterpret_cast<const float *>(base + off[f][7]);
             }
             d.g0 = reinterpret_cast<const int *>(base + off[f][2]);
@@ -1598,7 +1602,8 @@ Variant variant_of(const BandDev &bd, bool fp64, bool short_series, bool farrow,
     BandDev bw = bd;
     bw.ps2 = bd.pw != nullptr ? 1 : 0;
     const bool wide_ok = (bd.pw == nullptr || (streams && v.far && bd.pwf != nullptr)) && spectra_wide_ok(bw, fp64, kMaxLds);
-    v.sp = plain && spectra_pairs_ok(bd, fp64, kMaxLds) && !(prefer_wide && wide_ok);
+    const bool sp_ok = plain && spectra_pairs_ok(bd, fp64, kMaxLds);
+    v.sp = sp_ok && !(prefer_wide && wide_ok);
     v.timer = v.sp ? 6 : 7;
     // the grid is the faster one wherever it applies (lags up to 4): band after band 1.5 to 12 times,
     // and for same-time pairs of 256 points 7.2 -> 4.06 ms (120-day band, 512 templates); the kernels
@@ -1606,6 +1611,8 @@ Variant variant_of(const BandDev &bd, bool fp64, bool short_series, bool farrow,
     if (lag_fits(bd, fp64, v.lk)) {
         v.lag = true;
         v.sp = false;
+        // (the 256-point kernel's bands had their pair weights formed in FP64)
+        v.lk.rest = sp_ok && bd.R > 0 && v.lk.ns <= 512;
     }
     v.fold = fold && bd.allp && bd.n_s >= kFoldThreads;
     v.wide = !v.sp && !v.lag && !v.fold && wide_ok;

@@ -74,6 +74,7 @@ struct LagDev {
     // [Q][n_seg + 2 kLagSegs] pair weights (hat a scale, hat b scale), zero for absent segments
     const float2 *segwf;
     const double2 *segwd;
+    const float2 *segwl;  // what rounding segwf left of the FP64 weights, rounded itself
     // same-time pairs in FP32, 256 points: power of two that the spectra are multiplied with, about the
     // largest weight, and that segwf and pairw (by its square) are divided by
     float scale;
@@ -282,9 +283,10 @@ struct LagKey {
     // detectors (2, 3, 4, or 0: any number); same = 0: the other kernel
     int same = 0, rows = 0, dets = 0;
     bool cross = false, ps = false, circ = false;
+    bool rest = false;  // FP32 weights with the rests that rounding leaves
     bool operator==(const LagKey &o) const {
         return ns == o.ns && rm == o.rm && waves == o.waves && same == o.same && rows == o.rows && dets == o.dets &&
-               cross == o.cross && ps == o.ps && circ == o.circ;
+               cross == o.cross && ps == o.ps && circ == o.circ && rest == o.rest;
     }
 };
 // Most threads of a workgroup (a lane per kept column), and the LDS of its twiddle table.

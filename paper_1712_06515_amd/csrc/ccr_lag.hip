@@ -300,8 +300,10 @@ struct LagDets {
 // detectors, pairs across them only): {a_0, a_1, b_0, b_1}.  s0[t]: the same-time products of the
 // pairs X < Y, Re[conj(a_X) a_Y + conj(b_X) b_Y], or for Gamma^circ Im[conj(b_X) a_Y - conj(a_X) b_Y]
 // (a workgroup with more than one detector always sums pairs across them).  PS (per-sample
-// antenna functions): the two streams are transforms of their own.
-template <typename T, int ND, int NST, bool PS>
+// antenna functions): the two streams are transforms of their own.  WR: the weights with the part
+// that rounding them to FP32 leaves, for the bands whose pair weights were formed in FP64 before the
+// grid (four more instructions a spectrum: six bands of 3 detectors, three of them such, 8.00 -> 8.13 ms).
+template <typename T, int ND, int NST, bool PS, bool WR>
 __device__ __forceinline__ void lag_gather(const BandDev &B, const LagDets &D, const char *slots, int slot_bytes,
                                            int col, int Kb, int nd, bool circ, T (&s0)[kLagSegs], c2<T> (&n)[kLagSegs][NST]) {
     const int NDr = ND > 0 ? ND : nd;
@@ -320,9 +322,16 @@ __device__ __forceinline__ void lag_gather(const BandDev &B, const LagDets &D, c
                 a = f;
                 b = reinterpret_cast<const c2<T> *>(slots + (size_t)(u + 1) * slot_bytes)[col];
             } else {
-                const c2<T> w = ld_uniform_c2<T>(LagTab<T>::segw(B.lag), D.at(i) * (B.n_seg + 2 * kLagSegs) + kLagSegs + Kb + t);
-                a = cscale<T>(f, w.x);
-                b = cscale<T>(f, w.y);
+                const int e = D.at(i) * (B.n_seg + 2 * kLagSegs) + kLagSegs + Kb + t;
+                const c2<T> w = ld_uniform_c2<T>(LagTab<T>::segw(B.lag), e);
+                if constexpr (WR) {  // and what is left of the FP64 weights: one rounding, of the product
+                    const float2 r = ld_uniform_f2(B.lag.segwl, e);
+                    a = mk<T>(fma(f.x, w.x, f.x * r.x), fma(f.y, w.x, f.y * r.x));
+                    b = mk<T>(fma(f.x, w.y, f.x * r.y), fma(f.y, w.y, f.y * r.y));
+                } else {
+                    a = cscale<T>(f, w.x);
+                    b = cscale<T>(f, w.y);
+                }
             }
             if (i > 0) {
                 if (circ) {
@@ -385,7 +394,8 @@ __device__ __forceinline__ void lag_body(const BandDev &B, const c2<T> *__restri
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int W = blockDim.x >> 6;
     const int n_k = B.n_k, R = B.R, P = G.P, span = G.span, nf = G.nfold;
-    const bool circ = CM == 2 ? B.weight != 0 : CM == 1;
+    constexpr bool WR = (CM & 4) != 0;
+    const bool circ = (CM & 3) == 2 ? B.weight != 0 : (CM & 3) == 1;
     // the workgroup's detectors
     LagDets D{B.Q, 0, 1};
     if (G.n_sub > 1 || CR) {
@@ -607,13 +617,13 @@ __device__ __forceinline__ void lag_body(const BandDev &B, const c2<T> *__restri
             c2<T> n[kLagSegs][NST];
             T s0[kLagSegs];
             if constexpr (CR) {
-                lag_gather<T, 2, NST, PS>(B, D, slots, slot_bytes, col, Kb, nd, circ, s0, n);
+                lag_gather<T, 2, NST, PS, WR>(B, D, slots, slot_bytes, col, Kb, nd, circ, s0, n);
             } else {
                 switch (nd) {
-                    case 1: lag_gather<T, 1, NST, PS>(B, D, slots, slot_bytes, col, Kb, nd, circ, s0, n); break;
-                    case 2: lag_gather<T, 2, NST, PS>(B, D, slots, slot_bytes, col, Kb, nd, circ, s0, n); break;
-                    case 3: lag_gather<T, 3, NST, PS>(B, D, slots, slot_bytes, col, Kb, nd, circ, s0, n); break;
-                    default: lag_gather<T, 0, NST, PS>(B, D, slots, slot_bytes, col, Kb, nd, circ, s0, n); break;
+                    case 1: lag_gather<T, 1, NST, PS, WR>(B, D, slots, slot_bytes, col, Kb, nd, circ, s0, n); break;
+                    case 2: lag_gather<T, 2, NST, PS, WR>(B, D, slots, slot_bytes, col, Kb, nd, circ, s0, n); break;
+                    case 3: lag_gather<T, 3, NST, PS, WR>(B, D, slots, slot_bytes, col, Kb, nd, circ, s0, n); break;
+                    default: lag_gather<T, 0, NST, PS, WR>(B, D, slots, slot_bytes, col, Kb, nd, circ, s0, n); break;
                 }
             }
             if (Kb >= K0) {  // uniform; halo segments only enter the history
@@ -1009,12 +1019,15 @@ static void launch_lag_t(const LagKey &k, const BandDev *bands, const WorkItem *
 #define CCR_LAG(RM_, CR_, PS_, CM_)                                                                              \
     hipLaunchKernelGGL((k_lag<T, NS, RM_, CR_, PS_, CM_>), dim3(blocks), dim3(64 * k.waves), lds, stream, bands, \
                        items, n_items, (const c2<T> *)y, part)
-    // the weight is compiled in for pairs of both kinds with per-segment weights; the other forms
+    // CM: weight Gamma^ave (0) or Gamma^circ (1), or read at run time (2); 4: Gamma^ave with the weights'
+    // FP32 rests.  The weight is compiled in for pairs of both kinds with per-segment weights; the other forms
     // run transforms of up to 512 points (the planner's choice)
     if (k.cross || k.ps) {
         if constexpr (NS <= 512) {
             if (k.cross && k.ps) CCR_LAG(4, true, true, 2);
-            else if (k.cross) CCR_LAG(4, true, false, 2);
+            else if (k.cross && k.rest) {
+                if constexpr (sizeof(T) == 4) CCR_LAG(4, true, false, 4);
+            } else if (k.cross) CCR_LAG(4, true, false, 2);
             else if (k.rm == 0) CCR_LAG(0, false, true, 2);
             else CCR_LAG(4, false, true, 2);
         }
@@ -1022,6 +1035,12 @@ static void launch_lag_t(const LagKey &k, const BandDev *bands, const WorkItem *
         if (k.rm == 0) CCR_LAG(0, false, false, 1);
         else if (k.rm == 1) CCR_LAG(1, false, false, 1);
         else CCR_LAG(4, false, false, 1);
+    } else if (NS <= 512 && sizeof(T) == 4 && k.rest) {
+        if constexpr (NS <= 512 && sizeof(T) == 4) {
+            if (k.rm == 1) CCR_LAG(1, false, false, 4);
+            else if (k.rm == 2) CCR_LAG(2, false, false, 4);
+            else CCR_LAG(4, false, false, 4);
+        }
     } else {
         if (k.rm == 0) CCR_LAG(0, false, false, 0);
         else if (k.rm == 1) CCR_LAG(1, false, false, 0);

@@ -27,8 +27,8 @@ def ccr():
     return mod
 
 
-def dataset(n_k, ts=400.0, fb=0.1, weight=0, **kw):
-    cfg = small_config(t_short=ts, f_min=100.0, f_band=fb, a_p_max=2.0, **kw)
+def dataset(n_k, ts=400.0, fb=0.1, weight=0, f_min=100.0, **kw):
+    cfg = small_config(t_short=ts, f_min=f_min, f_band=fb, a_p_max=2.0, **kw)
     cfg["n_k"] = n_k
     cfg["band"]["weight"] = weight
     return synth.make_dataset(cfg, sigma_wander=0.2)
@@ -114,6 +114,11 @@ PAIR_WEIGHT = {
     "q2_lag0": (2, 0, (0, 4), (1, 4), 179),
     "q3_lag0_first_third": (3, 0, (0, 3), (2, 3), 256),
     "q4_lag0_second_fourth": (4, 0, (1, 4), (3, 4), 100),
+    # lags: N_K as planned at 400 Hz (distinct bins), 256- and 512-point classes
+    "q1_lag1": (1, 1, (0, 3), (0, 4), 0),
+    "q2_lag2": (2, 2, (0, 3), (1, 5), 0),
+    "q1_lag4_512_points": (1, 4, (0, 2), (0, 6), 0),
+    "q3_lag1_across_only": (3, 1, (0, 3), (2, 4), 0),
 }
 
 
@@ -125,8 +130,10 @@ def test_pair_weight_rounded_once(ccr, case):
     templates, 1e-9 of the products' own rounding."""
     q, R, (X, K), (Y, L), n_k = PAIR_WEIGHT[case]
     n_seg = 9
-    ds = dataset(n_k, fb=0.05 if n_k < 150 else 0.1, q=q, n_seg=n_seg, max_lag=R, pairs=2 if q == 1 else 3,
+    ds = dataset(n_k, fb=0.02 if "512" in case else (0.05 if n_k < 150 else 0.1), f_min=100.0 if n_k else 400.0, q=q, n_seg=n_seg, max_lag=R,
+                 pairs=2 if q == 1 else (1 if case.endswith("only") else 3),
                  templates=dict(a_p=(1.0, 2.0, 16), t_asc=(-900.0, 900.0, 16), period=[68023.70]))
+    n_k = ds.n_k
     bad, off = weights_rounded_badly(n_k)
     assert off > 1.1e-7
     with ccr.Context(ds.sky, device=0) as ctx:
@@ -143,7 +150,7 @@ def test_pair_weight_rounded_once(ccr, case):
         print(case, flush=True)
         s_ref = unnormalised(np.sqrt(n_k) / 16.0, np.sqrt(n_k) / 16.0)
         s_bad = unnormalised(bad[0], bad[1])
-        assert ctx.get_option("grid_ns") == 256
+        assert ctx.get_option("grid_ns") == (512 if "512" in case else 256)
     ratio = float((s_bad * s_ref).sum() / (s_ref * s_ref).sum()) / (bad[0] * bad[1] / n_k * 256.0) - 1.0
     print(f"  pair weight off by {ratio:.2e}, products of rounded factors by {off:.2e}", flush=True)
     assert abs(ratio) <= 2.0**-24 + 2e-9
