@@ -300,12 +300,14 @@ struct LagDets {
 // detectors, pairs across them only): {a_0, a_1, b_0, b_1}.  s0[t]: the same-time products of the
 // pairs X < Y, Re[conj(a_X) a_Y + conj(b_X) b_Y], or for Gamma^circ Im[conj(b_X) a_Y - conj(a_X) b_Y]
 // (a workgroup with more than one detector always sums pairs across them).  PS (per-sample
-// antenna functions): the two streams are transforms of their own.  WR: the weights with the part
+// antenna functions): the two streams are transforms of their own.  DET64 (lag 0 in FP32, no halo): each
+// detector's product goes to acc0 in FP64 by itself, as in the path these bands had before the grid.  WR: the weights with the part
 // that rounding them to FP32 leaves, for the bands whose pair weights were formed in FP64 before the
 // grid (four more instructions a spectrum: six bands of 3 detectors, three of them such, 8.00 -> 8.13 ms).
-template <typename T, int ND, int NST, bool PS, bool WR>
+template <typename T, int ND, int NST, bool PS, bool WR, bool DET64>
 __device__ __forceinline__ void lag_gather(const BandDev &B, const LagDets &D, const char *slots, int slot_bytes,
-                                           int col, int Kb, int nd, bool circ, T (&s0)[kLagSegs], c2<T> (&n)[kLagSegs][NST]) {
+                                           int col, int Kb, int nd, bool circ, T (&s0)[kLagSegs], c2<T> (&n)[kLagSegs][NST],
+                                           double &acc0) {
     const int NDr = ND > 0 ? ND : nd;
     constexpr int NM = ND > 0 ? ND : CCR_MAX_DET_K;
 #pragma unroll
@@ -334,6 +336,7 @@ __device__ __forceinline__ void lag_gather(const BandDev &B, const LagDets &D, c
                 }
             }
             if (i > 0) {
+                if constexpr (DET64) z = (T)0;
                 if (circ) {
                     z = fma(Bs.x, a.y, fma(-Bs.y, a.x, z));
                     z = fma(-A.x, b.y, fma(A.y, b.x, z));
@@ -341,6 +344,7 @@ __device__ __forceinline__ void lag_gather(const BandDev &B, const LagDets &D, c
                     z = fma(A.x, a.x, fma(A.y, a.y, z));
                     z = fma(Bs.x, b.x, fma(Bs.y, b.y, z));
                 }
+                if constexpr (DET64) acc0 += (double)z;
             }
             if constexpr (NST == 4) {
                 n[t][i & 1] = a;
@@ -367,7 +371,8 @@ __device__ __forceinline__ void lag_gather(const BandDev &B, const LagDets &D, c
 //   buffer.  Units of absent segments write zeros.  The next unit's input is loaded meanwhile.
 //   Pair sums.  Lane j of the workgroup owns column j: it forms the step's streams, multiplies each segment's with those of the RM segments before it -- the step's own
 //   or the last step's, kept in registers -- and adds them to S_1 .. S_RM (lags above R are
-//   computed and dropped).  FP32 products of a segment are summed in FP32, segments in FP64.
+//   computed and dropped).  FP32 products of a segment and lag are summed in FP32 (at lag 0 alone: of
+//   a segment and detector), the sums in FP64.
 // Two barriers a step.  Partials: [comp][P][span], comp 0: S_0 (same-time pairs across
 // detectors), 2 d - 1 and 2 d: Re and Im of S_d.
 //
@@ -390,6 +395,7 @@ __device__ __forceinline__ void lag_body(const BandDev &B, const c2<T> *__restri
     constexpr int NST = CR ? 4 : 2;
     constexpr bool LTW = lag_tw_lds(NS, sizeof(T) == 8) > 0;
     constexpr bool ALL64 = sizeof(T) == 8;  // a step's products have one sum
+    constexpr bool DET64 = RM == 0 && !ALL64;
     const LagDev &G = B.lag;
     const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     const int W = blockDim.x >> 6;
@@ -617,18 +623,18 @@ __device__ __forceinline__ void lag_body(const BandDev &B, const c2<T> *__restri
             c2<T> n[kLagSegs][NST];
             T s0[kLagSegs];
             if constexpr (CR) {
-                lag_gather<T, 2, NST, PS, WR>(B, D, slots, slot_bytes, col, Kb, nd, circ, s0, n);
+                lag_gather<T, 2, NST, PS, WR, DET64>(B, D, slots, slot_bytes, col, Kb, nd, circ, s0, n, acc0);
             } else {
                 switch (nd) {
-                    case 1: lag_gather<T, 1, NST, PS, WR>(B, D, slots, slot_bytes, col, Kb, nd, circ, s0, n); break;
-                    case 2: lag_gather<T, 2, NST, PS, WR>(B, D, slots, slot_bytes, col, Kb, nd, circ, s0, n); break;
-                    case 3: lag_gather<T, 3, NST, PS, WR>(B, D, slots, slot_bytes, col, Kb, nd, circ, s0, n); break;
-                    default: lag_gather<T, 0, NST, PS, WR>(B, D, slots, slot_bytes, col, Kb, nd, circ, s0, n); break;
+                    case 1: lag_gather<T, 1, NST, PS, WR, DET64>(B, D, slots, slot_bytes, col, Kb, nd, circ, s0, n, acc0); break;
+                    case 2: lag_gather<T, 2, NST, PS, WR, DET64>(B, D, slots, slot_bytes, col, Kb, nd, circ, s0, n, acc0); break;
+                    case 3: lag_gather<T, 3, NST, PS, WR, DET64>(B, D, slots, slot_bytes, col, Kb, nd, circ, s0, n, acc0); break;
+                    default: lag_gather<T, 0, NST, PS, WR, DET64>(B, D, slots, slot_bytes, col, Kb, nd, circ, s0, n, acc0); break;
                 }
             }
             if (Kb >= K0) {  // uniform; halo segments only enter the history
 #pragma unroll
-                for (int t = ALL64 ? kLagSegs - 1 : 0; t < kLagSegs; ++t) acc0 += (double)s0[t];
+                for (int t = ALL64 ? kLagSegs - 1 : 0; t < kLagSegs && !DET64; ++t) acc0 += (double)s0[t];
                 if constexpr (RM > 0) {
                     T st[2 * RM];
 #pragma unroll

@@ -177,3 +177,24 @@ def test_power_of_two_scaled_data(ccr, case, q):
     assert np.abs(out[0]).max() > 1.0
     differ = [int(np.count_nonzero(out[0] != o)) for o in out[1:]]
     assert differ == [0, 0]
+
+
+@pytest.mark.parametrize("weight", [0, 1])
+def test_detectors_add_in_fp64_at_lag_0(ccr, weight):
+    """One segment's weight, output bins that are grid points, pairs at lag 0 only: the unnormalised sum is
+    the FP64 sum of the FP32 products of detectors 1 and 2 with those before them, so most values need
+    more than 24 bits (a sum in FP32 would need 24 in every bin)."""
+    q, n_k, n_seg = 3, 500, 7
+    ds = dataset(n_k, ts=900.0, fb=0.1, weight=weight, q=q, n_seg=n_seg, max_lag=0, mu_f=0.02, n_fft_override=512)
+    with ccr.Context(ds.sky, device=0) as ctx:
+        bid = ctx.load(ds)
+        for X in range(q):
+            only = np.arange(n_seg) == 3
+            ctx.set_weights(bid, X, np.where(only, ds.a[X], 0.0), np.where(only, ds.b[X], 0.0), ds.noise_var[X])
+        ctx.set_templates(bid, ds.templates)
+        s = ctx.compute_rho(bid, prec=ccr.PREC_SPLIT) * (ctx.band_info(bid)["norm"] / np.sqrt(2.0))
+        assert (ctx.get_option("grid_ns"), ctx.get_option("grid_taps")) == (512, 1)
+    # within FP64 rounding of the normalisation of a 24-bit number
+    short = np.abs(s.astype(np.float32).astype(np.float64) / s - 1.0) < 1e-14
+    print(f"weight {weight}: {short.mean():.2f} of {s.size} sums have 24 bits", flush=True)
+    assert short.mean() < 0.5
