@@ -2817,8 +2817,10 @@ ccr_status ccr_sft_series(ccr_ctx *c, int64_t n_sft, double t_sft, double t0, in
             if (!std::isfinite(z[i])) return fail(c, CCR_EINVAL, "non-finite SFT bin at %lld", (long long)(i / 2));
     }
     HIP_OK(c, hipSetDevice(c->device));
-    // per SFT: the stitching phase (cycles, reduced in long double) and the presence flag, one copy
-    const size_t pb = (size_t)n_sft * (sizeof(double) + 1);
+    // per SFT: the stitching phase (cycles, reduced in long double; its FP64 value and the rest) and the
+    // presence flag, one copy
+    const size_t pb = (size_t)n_sft * (sizeof(double2) + 1);
+    auto with_rest = [](long double v) { return make_double2((double)v, (double)(v - (long double)(double)v)); };
     std::vector<char> small;
     try {
         small.resize(pb);
@@ -2828,9 +2830,9 @@ ccr_status ccr_sft_series(ccr_ctx *c, int64_t n_sft, double t_sft, double t0, in
     for (int64_t K = 0; K < n_sft; ++K) {
         long double ph = fh * ((long double)t0 + (long double)K * ts);
         ph -= floorl(ph);
-        const double p = (double)ph;
-        std::memcpy(small.data() + K * sizeof(double), &p, sizeof p);
-        small[(size_t)n_sft * sizeof(double) + K] = sft_valid ? (sft_valid[K] ? 1 : 0) : 1;
+        const double2 p = with_rest(ph);
+        std::memcpy(small.data() + K * sizeof p, &p, sizeof p);
+        small[(size_t)n_sft * sizeof p + K] = sft_valid ? (sft_valid[K] ? 1 : 0) : 1;
     }
     // device buffers in one allocation, kept by the context up to kSftKeepBytes
     const size_t zb = (size_t)n_sft * n_bins * sizeof(float2), xb = (size_t)n_sft * n_out * sizeof(float2);
@@ -2844,9 +2846,9 @@ ccr_status ccr_sft_series(ccr_ctx *c, int64_t n_sft, double t_sft, double t0, in
         HIP_OK(c, hipMemcpyAsync(dz, z, zb, hipMemcpyHostToDevice, s));
         {
             LaunchTimer lt(c, 8, s);
-            HIP_OK(c, launch_sft_series(reinterpret_cast<float2 *>(dz), n_sft, n_bins, off, (int)n_out, (int)h, (double)nu,
-                                        (double)(1.0L / ts), reinterpret_cast<double *>(dp),
-                                        reinterpret_cast<uint8_t *>(dp + n_sft * sizeof(double)),
+            HIP_OK(c, launch_sft_series(reinterpret_cast<float2 *>(dz), n_sft, n_bins, off, (int)n_out, (int)h, with_rest(nu),
+                                        (double)ts, reinterpret_cast<double2 *>(dp),
+                                        reinterpret_cast<uint8_t *>(dp + n_sft * sizeof(double2)),
                                         reinterpret_cast<float2 *>(dx), s));
         }
         return copy_out(c, x_out, dx, xb, s);

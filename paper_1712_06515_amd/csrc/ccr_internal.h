@@ -321,11 +321,11 @@ hipError_t launch_finish_m(const BandDev *bands, const WorkItem *items, int n_it
 hipError_t launch_zero(void *p, size_t bytes, hipStream_t stream);
 // SFT front end: the heterodyned series of n_sft SFTs (complex64 bins, n_bins per SFT; the band of
 // n_out bins starts `off` bins in, h of them below the heterodyne bin); nu: remainder of f_h T_sft off
-// the bin grid, inv_ts = 1 / T_sft, phase[K] = frac(f_h t_K) (cycles), present[K] (null: all); x:
-// n_sft x n_out complex64.
+// the bin grid, ts = T_sft, phase[K] = frac(f_h t_K) (cycles), both as an FP64 value and the rest that
+// rounding to it leaves, present[K] (null: all); x: n_sft x n_out complex64.
 constexpr int kSftMaxOut = 4096;
-hipError_t launch_sft_series(const float2 *z, int64_t n_sft, int64_t n_bins, int64_t off, int n_out, int h, double nu,
-                             double inv_ts, const double *phase, const uint8_t *present, float2 *x,
+hipError_t launch_sft_series(const float2 *z, int64_t n_sft, int64_t n_bins, int64_t off, int n_out, int h, double2 nu,
+                             double ts, const double2 *phase, const uint8_t *present, float2 *x,
                              hipStream_t stream);
 
 // Fixed device scratch of the no-allocation entry point (a file-scope device array of

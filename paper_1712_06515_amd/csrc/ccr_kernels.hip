@@ -3144,7 +3144,8 @@ hipError_t launch_finish_m(const BandDev *bands, const WorkItem *items, int n_it
 // outputs, a wavefront 16 outputs of them.  The bins go through LDS in runs of kSftRun (FP32 as
 // given, widened on use), the N' roots sit in LDS, and each lane steps its root's index (l j) mod N'
 // exactly in integers, so a root fetched once serves 4 RT matrix instructions.  Sums in FP64, output
-// complex64.  Bound: FP64 matrix rate (64 cycles an instruction).  RT = 4 for calls that fill the
+// complex64.  Roots and phases are as good as ones taken on the host in long double: an angle is its FP64
+// value and the rest that rounding it leaves.  Bound: FP64 matrix rate (64 cycles an instruction).  RT = 4 for calls that fill the
 // GPU with 64-SFT tiles, 1 for shorter ones, whose time is one wavefront's chain.  1800 SFTs of 870
 // outputs: 0.72 ms with one thread per output and vector arithmetic, 0.33 ms here.
 namespace {
@@ -3152,10 +3153,18 @@ constexpr int kSftThreads = 256;
 constexpr int kSftRun = 32;
 typedef double f64x4 __attribute__((ext_vector_type(4)));
 
+// cos and sin of pi (a + rest), rest below half an ulp of a.
+__device__ __forceinline__ double2 cis_pi(double a, double rest) {
+    double s, c;
+    sincospi(a, &s, &c);
+    const double d = 3.14159265358979323846 * rest;
+    return make_double2(fma(-s, d, c), fma(c, d, s));
+}
+
 template <int RT>
 __global__ void __launch_bounds__(kSftThreads)
-k_sft_series(const float2 *__restrict__ z, int64_t n_sft, int64_t n_bins, int64_t off, int n_out, int h, double nu,
-             double inv_ts, const double *__restrict__ phase, const uint8_t *__restrict__ present,
+k_sft_series(const float2 *__restrict__ z, int64_t n_sft, int64_t n_bins, int64_t off, int n_out, int h, double2 nu,
+             double ts, const double2 *__restrict__ phase, const uint8_t *__restrict__ present,
              float2 *__restrict__ x) {
     extern __shared__ __align__(16) unsigned char smem[];
     constexpr int ROWS = 16 * RT, LD = kSftRun + 1;
@@ -3166,9 +3175,8 @@ k_sft_series(const float2 *__restrict__ z, int64_t n_sft, int64_t n_bins, int64_
     const int g = lane >> 4, c = lane & 15;
     const int j = blockIdx.y * 64 + wave * 16 + c;  // this lane's output column
     for (int m = threadIdx.x; m < n_out; m += kSftThreads) {
-        double sn, cs;
-        sincospi(2.0 * (double)m / (double)n_out, &sn, &cs);
-        tw[m] = make_double2(cs, sn);
+        const double a = 2.0 * (double)m / (double)n_out;
+        tw[m] = cis_pi(a, fma(-a, (double)n_out, 2.0 * (double)m) / (double)n_out);
     }
     // index of l = g - h: ((g - h) j) mod N', advanced by (4 j) mod N'
     const int jm = j < n_out ? j : 0;
@@ -3203,10 +3211,12 @@ k_sft_series(const float2 *__restrict__ z, int64_t n_sft, int64_t n_bins, int64_
         }
     }
     if (j >= n_out) return;
-    double es, ec;
-    sincospi(-2.0 * (nu * (double)j / (double)n_out), &es, &ec);
-    ec *= inv_ts;
-    es *= inv_ts;
+    // -2 nu j / N': the product's and the quotient's rests, and that of nu
+    const double nj = -2.0 * nu.x * (double)j, a = nj / (double)n_out;
+    const double rest = fma(-2.0 * nu.x, (double)j, -nj) - 2.0 * nu.y * (double)j + fma(-a, (double)n_out, nj);
+    double2 e = cis_pi(a, rest / (double)n_out);
+    e.x /= ts;
+    e.y /= ts;
 #pragma unroll
     for (int q = 0; q < RT; ++q)
 #pragma unroll
@@ -3215,10 +3225,9 @@ k_sft_series(const float2 *__restrict__ z, int64_t n_sft, int64_t n_bins, int64_
             if (K >= n_sft) continue;
             float2 o = make_float2(0.f, 0.f);
             if (!present || present[K]) {
-                double ss, sc;
-                sincospi(-2.0 * phase[K], &ss, &sc);
-                const double er = re[q][r] * ec - im[q][r] * es, ei = re[q][r] * es + im[q][r] * ec;
-                o = make_float2((float)(er * sc - ei * ss), (float)(er * ss + ei * sc));
+                const double2 ph = phase[K], s = cis_pi(-2.0 * ph.x, -2.0 * ph.y);
+                const double er = re[q][r] * e.x - im[q][r] * e.y, ei = re[q][r] * e.y + im[q][r] * e.x;
+                o = make_float2((float)(er * s.x - ei * s.y), (float)(er * s.y + ei * s.x));
             }
             x[(size_t)K * n_out + j] = o;
         }
@@ -3226,19 +3235,19 @@ k_sft_series(const float2 *__restrict__ z, int64_t n_sft, int64_t n_bins, int64_
 
 }  // namespace
 
-hipError_t launch_sft_series(const float2 *z, int64_t n_sft, int64_t n_bins, int64_t off, int n_out, int h, double nu,
-                             double inv_ts, const double *phase, const uint8_t *present, float2 *x,
+hipError_t launch_sft_series(const float2 *z, int64_t n_sft, int64_t n_bins, int64_t off, int n_out, int h, double2 nu,
+                             double ts, const double2 *phase, const uint8_t *present, float2 *x,
                              hipStream_t stream) {
     const unsigned bx = (unsigned)((n_out + 63) / 64);
     const size_t tab = (size_t)n_out * sizeof(double2);
     if ((int64_t)bx * ((n_sft + 63) / 64) >= 256)
         hipLaunchKernelGGL(k_sft_series<4>, dim3((unsigned)((n_sft + 63) / 64), bx), dim3(kSftThreads),
                            tab + 64 * (kSftRun + 1) * sizeof(float2), stream, z, n_sft, n_bins, off, n_out, h, nu,
-                           inv_ts, phase, present, x);
+                           ts, phase, present, x);
     else
         hipLaunchKernelGGL(k_sft_series<1>, dim3((unsigned)((n_sft + 15) / 16), bx), dim3(kSftThreads),
                            tab + 16 * (kSftRun + 1) * sizeof(float2), stream, z, n_sft, n_bins, off, n_out, h, nu,
-                           inv_ts, phase, present, x);
+                           ts, phase, present, x);
     return hipGetLastError();
 }
 
