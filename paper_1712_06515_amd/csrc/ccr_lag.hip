@@ -161,32 +161,26 @@ __device__ __forceinline__ void lag_fft_quad(float2 *v, float *ex, const LagTwQu
 }
 
 // NS-point forward FFT of one wavefront (V = NS / 64 values a lane, x[l + 64 r] in v[r] on
-// entry, X[l + 64 J] in v[J] on return), self-sorting passes of radix 16, 16, 4 (1024), 8, 8, 8
-// (512) or 4, 4, 4, 4 (256): a pass of radix V with stride Ns has butterfly l read a[l + 64 r],
+// entry, X[l + 64 J] in v[J] on return), self-sorting passes of radix 16, 16, 4 (1024, FP32), 8, 8, 8
+// (512) or 4, 4, 4, 4 (256, FP64): a pass of radix V with stride Ns has butterfly l read a[l + 64 r],
 // twiddle input r and write output r to (l / Ns) V Ns + l % Ns + r Ns.  Between passes the values
 // go through `ex` (at most NS + 64 entries), padded so that the lanes served together -- 32 for
 // 4-byte values, 16 for 8-byte ones -- fall on distinct banks on both sides: 4-byte values at
-// i + i / 32 in the first exchange and with 16 (8, 4, 16) entries after each 256 (64, 32, 64)
-// in the later ones, 8-byte values at i + i / V.
+// i + i / 32 in the first exchange and with 16 (8) entries after each 256 (64) in the second,
+// 8-byte values at i + i / V.
 template <typename T, bool L>
 __device__ __forceinline__ void lag_fft(c2<T> *v, T *ex, const LagTw<T, 1024, L> &t, int lane) {
     const int g = lane >> 4, k = lane & 15;
     auto perm = [](int i) { return 4 * (i & 3) + (i >> 2); };
     dft16<T>(v);
-    if constexpr (sizeof(T) == 4)
-        exchange<T, 16>(v, ex, perm, [&](int i) { return 16 * lane + (lane >> 1) + i; },
-                        [&](int r) { return lane + (lane >> 5) + 66 * r; });
-    else
-        exchange<T, 16>(v, ex, perm, [&](int i) { return 17 * lane + i; }, [&](int r) { return lane + g + 68 * r; });
+    static_assert(sizeof(T) == 4, "1024 points: FP32 only");
+    exchange<T, 16>(v, ex, perm, [&](int i) { return 16 * lane + (lane >> 1) + i; },
+                    [&](int r) { return lane + (lane >> 5) + 66 * r; });
 #pragma unroll
     for (int r = 0; r < 16; ++r) v[r] = cmul<T>(v[r], t.a(r));
     dft16<T>(v);
-    if constexpr (sizeof(T) == 4)
-        exchange<T, 16>(v, ex, perm, [&](int i) { return 272 * g + k + 16 * i; },
-                        [&](int r) { return lane + 64 * (r & 3) + 272 * (r >> 2); });
-    else
-        exchange<T, 16>(v, ex, perm, [&](int i) { return 272 * g + k + 17 * i; },
-                        [&](int r) { return lane + g + 68 * (r & 3) + 272 * (r >> 2); });
+    exchange<T, 16>(v, ex, perm, [&](int i) { return 272 * g + k + 16 * i; },
+                    [&](int r) { return lane + 64 * (r & 3) + 272 * (r >> 2); });
 #pragma unroll
     for (int j = 0; j < 4; ++j) {  // v[j + 4 r] = a[l + 64 j + 256 r]
 #pragma unroll
@@ -222,27 +216,17 @@ __device__ __forceinline__ void lag_fft(c2<T> *v, T *ex, const LagTw<T, 256, L> 
     const int g4 = lane >> 2, k4 = lane & 3, g16 = lane >> 4, k16 = lane & 15;
     auto id = [](int i) { return i; };
     auto rd = [&](int r) { return lane + g4 + 80 * r; };
+    static_assert(sizeof(T) == 8, "256 points in FP32 run four to a wavefront");
     dft4<T>(v[0], v[1], v[2], v[3]);
-    if constexpr (sizeof(T) == 4)
-        exchange<T, 4>(v, ex, id, [&](int i) { return 4 * lane + (lane >> 3) + i; },
-                       [&](int r) { return lane + (lane >> 5) + 66 * r; });
-    else
-        exchange<T, 4>(v, ex, id, [&](int i) { return 5 * lane + i; }, rd);
+    exchange<T, 4>(v, ex, id, [&](int i) { return 5 * lane + i; }, rd);
 #pragma unroll
     for (int r = 0; r < 4; ++r) v[r] = cmul<T>(v[r], t.a(r));
     dft4<T>(v[0], v[1], v[2], v[3]);
-    if constexpr (sizeof(T) == 4)
-        exchange<T, 4>(v, ex, id, [&](int i) { return 16 * g4 + 4 * (g4 >> 1) + k4 + 4 * i; },
-                       [&](int r) { return lane + 4 * (lane >> 5) + 72 * r; });
-    else
-        exchange<T, 4>(v, ex, id, [&](int i) { return 20 * g4 + k4 + 5 * i; }, rd);
+    exchange<T, 4>(v, ex, id, [&](int i) { return 20 * g4 + k4 + 5 * i; }, rd);
 #pragma unroll
     for (int r = 1; r < 4; ++r) v[r] = cmul<T>(v[r], t.b(r));
     dft4<T>(v[0], v[1], v[2], v[3]);
-    if constexpr (sizeof(T) == 4)
-        exchange<T, 4>(v, ex, id, [&](int i) { return 80 * g16 + k16 + 16 * i; }, [&](int r) { return lane + 80 * r; });
-    else
-        exchange<T, 4>(v, ex, id, [&](int i) { return 80 * g16 + k16 + (k16 >> 2) + 20 * i; }, rd);
+    exchange<T, 4>(v, ex, id, [&](int i) { return 80 * g16 + k16 + (k16 >> 2) + 20 * i; }, rd);
 #pragma unroll
     for (int r = 1; r < 4; ++r) v[r] = cmul<T>(v[r], t.c(r));
     dft4<T>(v[0], v[1], v[2], v[3]);
