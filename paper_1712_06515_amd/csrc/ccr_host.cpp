@@ -1830,7 +1830,7 @@ ccr_status build_plan(ccr_ctx *c, bool fp64, int n_bands, const int *band_ids, v
                                : v.sp ? nch
                                       : (v.reg16 ? (B.n_work + kSpec16Groups - 1) / kSpec16Groups : B.n_work);
         proto.gx[kStPairs] = v.fold  ? 2 * (int)pl.P
-                             : v.lag ? (int)((lag1 / sizeof(double) / bd.lag.n_sub + kLagFinThreads - 1) / kLagFinThreads)
+                             : v.lag ? (nch * bd.lag.n_sub == 1 ? 0 : (int)((lag1 / sizeof(double) / bd.lag.n_sub + kLagFinThreads - 1) / kLagFinThreads))
                              : (v.sp || v.wide) ? 0 : (int)((pl.n_f + kPairsThreads - 1) / kPairsThreads);
         const int fin = v.lag ? kLagFinThreads : kFinishThreads;
         proto.gx[kStFinish] = (int)((pl.n_f + fin - 1) / fin);

@@ -62,3 +62,21 @@ def test_planned_form(ccr, case):
             print(f"  grid {grid}, error {err:.2e}, max|rho| {np.abs(ref).max():.2f}", flush=True)
             assert err < (1e-10 if prec == ccr.PREC_FP64 else 1e-4)
             assert all(e is None or g == e for g, e in zip(grid, expect)), (grid, expect)
+
+
+def test_single_partials_beside_chunks(ccr):
+    """Bands of one kernel in one call, the first, the middle and the last with a single chunk (nothing to
+    add up) and others with several, give what each gives alone."""
+    kw = dict(t_short=400.0, f_min=100.0, f_band=0.1, max_lag=1, a_p_max=2.0)
+    dss = [synth.make_dataset(small_config(n_seg=n, seed=n, **kw)) for n in (6, 31, 5, 4, 17, 3)]
+    with ccr.Context(dss[0].sky, device=0) as ctx:
+        ctx.set_option("k_chunk", 6)
+        ids = [ctx.load(ds) for ds in dss]
+        for prec in (ccr.PREC_FP64, ccr.PREC_SPLIT):
+            print(f"precision {prec}", flush=True)
+            together = ctx.compute_rho(ids, prec=prec)
+            for i, r, ds in zip(ids, together, dss):
+                assert np.array_equal(r, ctx.compute_rho(i, prec=prec))
+                if prec == ccr.PREC_FP64:
+                    ref = oracle.Oracle(ds).rho(ds.templates)
+                    assert float(np.max(np.abs(r - ref) / np.maximum(np.abs(ref), 1.0))) < 1e-10
