@@ -1011,12 +1011,15 @@ ccr_status prepare(ccr_ctx *c, Band &B) {
                 if (most > 0.0) e2 = std::min(126, std::max(-126, std::ilogb(most)));
             }
             L.d.scale = (float)std::ldexp(1.0, e2);
+            const double down = std::ldexp(1.0, -e2);
             // per-detector weights and per-problem activity with a step of zeros at either end
             const size_t row = (size_t)M + 2 * kLagSegs;
             std::vector<double2> wd((size_t)Q * row, make_double2(0.0, 0.0));
             for (int X = 0; X < Q; ++X)
-                for (int64_t K = 0; K < M; ++K) wd[X * row + kLagSegs + K] = segwd[(size_t)X * M + K];
-            for (double2 &w : wd) w = make_double2(std::ldexp(w.x, -e2), std::ldexp(w.y, -e2));
+                for (int64_t K = 0; K < M; ++K) {
+                    const double2 w = segwd[(size_t)X * M + K];
+                    wd[X * row + kLagSegs + K] = make_double2(w.x * down, w.y * down);
+                }
             if (f == 1) {
                 off[f][5] = put(wd);
             } else {
