@@ -335,7 +335,8 @@ def main():
     log(f"split path {ms_per_step:.2f} ms/step ({value:.3e} rho/s)")
     rho = out.cpu().numpy()
     err = golden_error(ds, rho, n_t) if args.workload == "large" else None
-    tuned = {"k_chunk": ctx.get_option("tuned_k_chunk"), "template_batch": ctx.get_option("tuned_template_batch"),
+    tuned = {"k_chunk": ctx.get_option("tuned_k_chunk"), "own_chunks": ctx.get_option("tuned_own_chunks"),
+             "template_batch": ctx.get_option("tuned_template_batch"),
              "round_templates": ctx.get_option("tuned_round_templates"),
              "spectra_kernel": ctx.get_option("tuned_spectra_kernel")}
 
@@ -530,6 +531,7 @@ def extra_lines(args):
         out["band"] = {"workload": WORKLOADS["band"], "value": info["n_templates"] * info["n_f"] / sec,
                        "unit": "rho-evals/s", "ms_per_step": 1e3 * sec,
                        "tuned": {"k_chunk": ctx.get_option("tuned_k_chunk"),
+                                 "own_chunks": ctx.get_option("tuned_own_chunks"),
                                  "template_batch": ctx.get_option("tuned_template_batch"),
                                  "round_templates": ctx.get_option("tuned_round_templates"),
                                  "spectra_kernel": ctx.get_option("tuned_spectra_kernel")}}
@@ -549,6 +551,7 @@ def extra_lines(args):
         out["multiband"] = {"workload": WORKLOADS["multiband"], "value": n_eval / sec, "unit": "rho-evals/s",
                             "ms_per_step": 1e3 * sec, "bands": len(ids), "rho_evals_per_step": n_eval,
                             "tuned": {"k_chunk": ctx.get_option("tuned_k_chunk"),
+                                      "own_chunks": ctx.get_option("tuned_own_chunks"),
                                       "template_batch": ctx.get_option("tuned_template_batch"),
                                       "round_templates": ctx.get_option("tuned_round_templates"),
                                       "spectra_kernel": ctx.get_option("tuned_spectra_kernel")}}

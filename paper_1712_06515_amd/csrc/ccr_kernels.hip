@@ -599,10 +599,11 @@ __device__ __forceinline__ double2 interpolate64_d8(const double *cw, const floa
 // segment, kResTemplates templates).  The segment's input, over the range of j* of its templates
 // (their delays differ by a few samples), and its gap mask are staged in LDS once; the wavefronts
 // then share the (template, 64-sample pass) pairs with no global reads but the coefficients.
-// Bound: VALU issue (FP64 arithmetic, ~250 instructions a pass).  Against one wavefront per segment
-// that loads each pass's window and divides per tap: 5 templates of 120 days at T_short 1440 s 1.61
-// -> 0.94 ms, 12 of the 120-day band at 200 Hz 0.79 -> 0.51 ms.  A range wider than the LDS window reads
-// each sample's taps from global memory.
+// Bound: VALU issue where the GPU is full (12 templates of the 120-day band at 200 Hz: 86 % busy, 15
+// wavefronts a CU, ~250 FP64 instructions a pass); 60 % at 10 a CU for 5 templates of 870-sample
+// segments (a tile of four templates and one of one).  Against one wavefront per segment that loads
+// each pass's window and divides per tap: the latter 1.61 -> 0.93 ms, the former 0.79 -> 0.51 ms.  A range
+// wider than the LDS window reads each sample's taps from global memory.
 template <int NC>
 __device__ __forceinline__ void resample64_body(const BandDev &B, const double *coef, double2 *y, int w, int t0,
                                                 int t1) {

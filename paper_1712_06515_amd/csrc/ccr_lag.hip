@@ -15,6 +15,15 @@
 //                 interpolation margin, per (template, chunk of segments, residue class)
 //   k_lag_reduce  chunk sums
 //   k_lag_finish  interpolation to the output bins, lag phases, sqrt(2) / N
+//
+// Accuracy.  Errors of S_d at one grid point reach the bins within half the taps of it, so they are
+// relative to the largest S_d there, where a transform at the bin itself rounds relative to the bin's own
+// value.  Against the FP64 path on noise and signals up to rho ~ 1e3 the error is smaller than that of the
+// kernels before the grid at every lag (rms 2.1 - 2.8e-7 in place of 2.5 - 7.8e-7).  Beside a signal of
+// rho = 1e4, 1e6 and 1e7 and up the worst bin at lags above 0 is off by 3e-5, 1 to 3e-4 and 1e-3 of max(|rho|, 1)
+// (before: 3e-6, 2e-5, 6e-5), from the FP32 rounding of the products at the peak (6e-8 of it, over the
+// root of the segments) and the taps' stop band (3e-10 of it); at lag 0 less than before at any strength.
+// FP64: the same as before below 1e6, up to 3.4 times at 2e7 (1.2e-10 -> 4.2e-10).
 #include <type_traits>
 
 #include "ccr_device.h"
@@ -167,7 +176,8 @@ __device__ __forceinline__ void lag_fft_quad(float2 *v, float *ex, const LagTwQu
 // go through `ex` (at most NS + 64 entries), padded so that the lanes served together -- 32 for
 // 4-byte values, 16 for 8-byte ones -- fall on distinct banks on both sides: 4-byte values at
 // i + i / 32 in the first exchange and with 16 (8) entries after each 256 (64) in the second,
-// 8-byte values at i + i / V.
+// 8-byte values at i + i / V.  By the counters that holds for 4-byte values (no conflict cycles); in
+// FP64 0.30 (512 points) to 0.37 (256) of the LDS cycles are still conflicts.
 template <typename T, bool L>
 __device__ __forceinline__ void lag_fft(c2<T> *v, T *ex, const LagTw<T, 1024, L> &t, int lane) {
     const int g = lane >> 4, k = lane & 15;
@@ -283,11 +293,12 @@ struct LagDets {
 // the sums over the detectors of hat a_X F_X and hat b_X F_X (n[t] = {A, B}); NST = 4 (two
 // detectors, pairs across them only): {a_0, a_1, b_0, b_1}.  s0[t]: the same-time products of the
 // pairs X < Y, Re[conj(a_X) a_Y + conj(b_X) b_Y], or for Gamma^circ Im[conj(b_X) a_Y - conj(a_X) b_Y]
-// (a workgroup with more than one detector always sums pairs across them).  PS (per-sample
-// antenna functions): the two streams are transforms of their own.  DET64 (lag 0 in FP32, no halo): each
-// detector's product goes to acc0 in FP64 by itself, as in the path these bands had before the grid.  WR: the weights with the part
-// that rounding them to FP32 leaves, for the bands whose pair weights were formed in FP64 before the
-// grid (four more instructions a spectrum: six bands of 3 detectors, three of them such, 8.00 -> 8.13 ms).
+// (a workgroup with more than one detector always sums pairs across them; in FP64 s0[t] adds up
+// over the step).  PS (per-sample antenna functions): the two streams are transforms of their own.
+// DET64 (lag 0 in FP32, no halo): each detector's product goes to acc0 in FP64 by itself, as in the
+// path these bands had before the grid.  WR: the weights with the part that rounding them to FP32
+// leaves, for the bands whose pair weights were formed in FP64 before the grid (four more
+// instructions a spectrum: six bands of 3 detectors, three of them such, 8.00 -> 8.13 ms).
 template <typename T, int ND, int NST, bool PS, bool WR, bool DET64>
 __device__ __forceinline__ void lag_gather(const BandDev &B, const LagDets &D, const char *slots, int slot_bytes,
                                            int col, int Kb, int nd, bool circ, T (&s0)[kLagSegs], c2<T> (&n)[kLagSegs][NST],
@@ -353,20 +364,28 @@ __device__ __forceinline__ void lag_gather(const BandDev &B, const LagDets &D, c
 //   mod N_S only), applies the class's input twiddle, transforms them and writes the class's
 //   bins inside the band to the unit's LDS slot, which also serves as the transform's exchange
 //   buffer.  Units of absent segments write zeros.  The next unit's input is loaded meanwhile.
-//   Pair sums.  Lane j of the workgroup owns column j: it forms the step's streams, multiplies each segment's with those of the RM segments before it -- the step's own
-//   or the last step's, kept in registers -- and adds them to S_1 .. S_RM (lags above R are
-//   computed and dropped).  FP32 products of a segment and lag are summed in FP32 (at lag 0 alone: of
-//   a segment and detector), the sums in FP64.
+//   Pair sums.  Lane j of the workgroup owns column j: it forms the step's streams, multiplies each
+//   segment's with those of the RM segments before it -- the step's own or the last step's, kept in
+//   registers -- and adds them to S_1 .. S_RM (lags above R are computed and dropped).  FP32 products
+//   of a segment and lag are summed in FP32 (at lag 0 alone: of a segment and detector), the sums in
+//   FP64.
 // Two barriers a step.  Partials: [comp][P][span], comp 0: S_0 (same-time pairs across
 // detectors), 2 d - 1 and 2 d: Re and Im of S_d.
 //
-// Bound: VALU issue (71 % busy at 1024 points, lag 4; transforms ~70 % of the instructions).
+// Bound at 1024 points, lag 4: VALU issue (83 % busy; transforms ~70 % of the instructions).  FP64: not
+// the arithmetic (22 % busy) but latency at two wavefronts a SIMD (6.6 - 7 a CU): 226 registers, of
+// which the twiddles take 64, ~75 spilled scalars, and the exchanges' bank conflicts.
+// Registers: the 1024-point lag-4 form holds its 128 with 20 vector and 73 scalar registers spilled (40
+// bytes a lane), the 512-point FP64 forms for pairs across detectors only spill 82 and 91 vector
+// registers (about 300 bytes a lane: streams of both detectors are kept; 256 points would hold them, which
+// the planner's instruction counts do not see), the quad forms ~94 scalars.
 // 60 templates of the 240-day, lag-4 band: transforms at every output bin with window sums over
 // an LDS ring of spectra 80.4 ms; this kernel with two columns a lane, twiddles in registers (256,
 // two wavefronts a SIMD), per-unit scalar searches and one bank conflict a read 10.9 ms; one
 // column a lane and twiddles in LDS (four wavefronts a SIMD), halo as whole steps, fused
 // multiply-adds in the products 8.4 ms; conflict-free padding and table lookups for the activity
-// masks and weights 7.25 ms.  FP64, 5 templates of 120 days: 23.4 ms (spectra through memory) -> 0.94 ms.
+// masks and weights 7.25 ms; segments added in FP64 one by one (fewer sums held) 6.87 ms.  FP64, 5
+// templates of 120 days: 23.4 ms (spectra through memory) -> 0.95 ms.
 template <typename T, int NS, int RM, bool CR, bool PS, int CM>
 __device__ __forceinline__ void lag_body(const BandDev &B, const c2<T> *__restrict__ y, double *__restrict__ part,
                                          int k_chunk, int n_chunks, int c, int sub, int p, int tb) {
@@ -718,12 +737,13 @@ __device__ __forceinline__ int lower_wave(const int *x, int n, int key, int lane
 //
 // (One workgroup for both classes, in step so that they read the segments together: 4.33 ms instead
 // of 4.06, though the two read the series 1.9 times over: that traffic does not set the time.)
-// Bound: VALU issue (busy in every cycle, ~112 instructions a transform of which ~95 are its passes
-// and twiddles; four wavefronts a SIMD).  512 templates of the 120-day band (2 detectors, 30 % gaps,
+// Bound: VALU issue, one instruction in 3.6 cycles of a SIMD (the derived share of profiles, which takes
+// every instruction for four cycles, reads 1.1), ~112 instructions a transform of which ~95 are its
+// passes and twiddles; four wavefronts a SIMD.  512 templates of the 120-day band (2 detectors, 30 % gaps,
 // two classes of 179-sample segments, 137 bins): the 256-point spectra + pairs kernel, which runs
 // every step through an LDS ring, 7.2 ms; k_lag with four transforms a wavefront 6.5 ms; this kernel
 // 4.8 ms, with chunks of up to 1024 segments (a wavefront gets ~35 steps, not 9) 4.25 ms, with one
-// weight a pair in place of the two sums for 2 and 3 detectors 4.06 ms.
+// weight a pair in place of the two sums for 2 and 3 detectors 4.06 ms; 4.1 with the weights from the table.
 template <int NO, int NR, int QK>
 __device__ __forceinline__ void lag_same_body(const BandDev &B, const float2 *__restrict__ y, double *__restrict__ part,
                                               int k_chunk, int n_chunks, int c, int sub, int p, int tb) {

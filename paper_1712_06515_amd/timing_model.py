@@ -16,10 +16,13 @@ is 2 N_K (N_K = ceil(T_short Delta f_load) complex samples per segment), N_FFT t
 length and N_f its output bins; N_orb is the number of orbital templates of the call.  The fit is
 a nonnegative least-squares fit of the relative residuals.  The paper fits its constants
 separately below and above N_FFT = 2^18, where its CPU FFT slows down; on this GPU the cost per
-unit changes with the kernel that computes the segment spectra and pair sums (one fused kernel
-for 256-point segments, one for 256- to 1024-point segments, the general staged kernels otherwise), so
-the constants are fitted per kernel path (a path with fewer than 4 measurements takes the fit
-over all of them).
+unit changes with the kernel that computes the segment spectra and pair sums, so the constants are
+fitted per kernel path: same-time pairs of 256-point segments (same256), the lag-resolved grid's
+other forms up to lag 4 (grid), and above that the fused kernel for 256-point segments (fused256),
+the one for 256- to 1024-point segments (wide) and the general staged kernels (general).  A path with
+fewer than 4 measurements takes the fit over all of them.  On the grid a segment's transforms do not
+grow with N_FFT (its interpolation to the output bins, once per template, does), so tau_FFT there is
+what is left of that dependence.
 
 This module measures and fits; it computes nothing of the statistic itself.  `python -m
 paper_1712_06515_amd.timing_model --out FILE` runs the sweep on the GPU and writes the
@@ -76,7 +79,7 @@ def _fit_one(X, t):
     }
 
 
-PATHS = ("fused256", "wide", "general")
+PATHS = ("same256", "grid", "fused256", "wide", "general")
 
 
 def fit(rows):
@@ -169,7 +172,11 @@ def run_sweep(n_orb=2048, repeats=3, prec=1, progress=print):
             ctx.set_option("timing", 1)
             ctx.compute_rho(bid, prec=prec, out_fp64=False, outputs=[out.data_ptr()])
             kt = ctx.kernel_times(reset=True)
-            path = ("fused256" if kt["spectra_pairs"][1] else "wide" if kt["spectra_wide"][1] else "general")
+            if ctx.get_option("grid_ns"):
+                same = ctx.get_option("grid_ns") == 256 and ds.band["max_lag"] == 0 and info["n_k"] <= 256
+                path = "same256" if same else "grid"
+            else:
+                path = "fused256" if kt["spectra_pairs"][1] else "wide" if kt["spectra_wide"][1] else "general"
         row = dict(config=c, n_orb=len(tm), n_fft=int(info["n_fft"]), n_f=int(info["n_f"]), n_k=int(info["n_k"]),
                    n_seg=int(info["n_seg"]), seconds=best, path=path,
                    features=[float(v) for v in features(info, len(tm), c["D"])])
