@@ -185,6 +185,13 @@ const char *ccr_last_error(const ccr_ctx *ctx);
  *                     pair-sum kernel; 1: they run the kernel of the other bands.  (With lags up
  *                     to 4 both values run the lag-resolved grid; the value then only says which
  *                     slot of ccr_kernel_time, 6 or 7, counts it.);
+ *   "grid"            1 (default): lags up to 4 run on the lag-resolved frequency grid and every
+ *                     ordered pair as a folded series; 0: the kernels for any lag, which transform
+ *                     every segment at the output bins (calls 1.3 to 13 times slower).  On the grid a bin's
+ *                     error is relative to the largest |rho| within the reach of its
+ *                     interpolation: beside a signal of rho above about 1e5 (split precision, lags
+ *                     above 0) single bins are off by more than 1e-4 of max(|rho|, 1), up to 1e-3
+ *                     from 1e7 on, where 0 keeps them below 1e-4;
  *   "autotune"        1: on the first call for a given band list and precision, time the
  *                     first launch round of each candidate launch shape and keep the fastest
  *                     per template: the spectra kernel (where a band can take either) and

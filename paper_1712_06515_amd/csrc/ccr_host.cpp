@@ -127,6 +127,7 @@ struct ccr_ctx {
     size_t auto_budget = 0;         // automatic workspace budget, fixed at the first compute call
     int64_t opt_k_chunk = 0;
     int64_t opt_spectra_kernel = 0;  // 1: the 256- to 1024-point spectra + pair-sum kernel wherever it applies
+    int64_t opt_grid = 1;  // 0: neither the lag-resolved grid nor the folded series
     int64_t opt_round_templates = 0;  // at most this many templates in one launch round (0: no limit)
     int64_t opt_fused = 0;
     int64_t opt_timing = 0;
@@ -1608,9 +1609,9 @@ Variant variant_of(const BandDev &bd, bool fp64, bool short_series, bool farrow,
     const bool sp_ok = plain && spectra_pairs_ok(bd, fp64, kMaxLds);
     v.sp = sp_ok && !(prefer_wide && wide_ok);
     v.timer = v.sp ? 6 : 7;
-    // the grid is the faster one wherever it applies (lags up to 4): band after band 1.5 to 12 times,
-    // and for same-time pairs of 256 points 7.2 -> 4.06 ms (120-day band, 512 templates); the kernels
-    // below take the rest
+    // the grid is the faster one wherever it applies (lags up to 4: its kernel's step, history and halo
+    // are four segments): whole calls 1.3 (512 templates of 120 days, lag 0: 12.19 -> 9.07 ms) to 13 times
+    // (24 of 20 days, lag 3: 6.41 -> 0.48 ms); the kernels below take the rest
     if (lag_fits(bd, fp64, v.lk)) {
         v.lag = true;
         v.sp = false;
@@ -1761,6 +1762,7 @@ ccr_status build_plan(ccr_ctx *c, bool fp64, int n_bands, const int *band_ids, v
         const Plan &pl = B.plan;
         BandDev bd = band_dev(B, fp64);
         bd.far_stage = (int)c->opt_farrow_stage;
+        if (!c->opt_grid) bd.lag.on = 0;
         cp.bands.push_back(bd);
         // folded series: the samples m + j N_FFT of one output sample in runs of fold_kc values of j,
         // so that a template gives at least 128 workgroups
@@ -1785,7 +1787,7 @@ ccr_status build_plan(ccr_ctx *c, bool fp64, int n_bands, const int *band_ids, v
         const size_t F0 = v0.sp || v0.wide ? 0 : (size_t)B.Q * pl.n_seg * pl.n_f * cs * (bd.pw ? 2 : 1);
         const size_t part0 = (size_t)((pl.n_seg + kc0 - 1) / kc0) * pl.n_f * sizeof(double) * (bd.allp ? 4 : 1);
         const bool fixed0 = arena_bytes_of(coef1, y0, F0, part0) <= kNoAllocArena;
-        Variant v = variant(bd, !fixed0 || arena_bytes_of(coef1, ser1, fold1, fold_part) <= kNoAllocArena);
+        Variant v = variant(bd, c->opt_grid && (!fixed0 || arena_bytes_of(coef1, ser1, fold1, fold_part) <= kNoAllocArena));
         const size_t lag1 = (size_t)bd.lag.n_sub * (2 * bd.R + 1) * bd.lag.P * bd.lag.span * sizeof(double);
         int64_t kc = bp.k_chunk > 0 ? bp.k_chunk : default_chunk(B, v, bd, fp64);
         kc = std::max<int64_t>(1, std::min<int64_t>(kc, pl.n_seg));
@@ -2077,9 +2079,10 @@ ccr_status choose_params(ccr_ctx *c, ccr_precision prec, int n_bands, const int 
     for (int bi = 0; bi < n_bands; ++bi) {
         const Band &B = *get_band(c, band_ids[bi]);
         max_seg = std::max<int64_t>(max_seg, B.plan.n_seg);
-        const BandDev bd = band_dev(B, fp64);
-        const Variant v0 = variant_of(bd, fp64, B.short_series, c->opt_farrow != 0, false);
-        Variant v1 = variant_of(bd, fp64, B.short_series, c->opt_farrow != 0, true);
+        BandDev bd = band_dev(B, fp64);
+        if (!c->opt_grid) bd.lag.on = 0;
+        const Variant v0 = variant_of(bd, fp64, B.short_series, c->opt_farrow != 0, false, true, c->opt_grid != 0);
+        Variant v1 = variant_of(bd, fp64, B.short_series, c->opt_farrow != 0, true, true, c->opt_grid != 0);
         v1.timer = v0.timer;  // (the same kernel in another time slot is no choice)
         both = both || !(v0 == v1);
     }
@@ -2386,6 +2389,7 @@ ccr_status ccr_set_option(ccr_ctx *c, const char *name, int64_t value) {
     else if (k == "workspace_mb") c->opt_workspace_mb = value == 0 ? 0 : std::max<int64_t>(value, 64);
     else if (k == "k_chunk") c->opt_k_chunk = value;
     else if (k == "spectra_kernel") c->opt_spectra_kernel = value ? 1 : 0;
+    else if (k == "grid") c->opt_grid = value ? 1 : 0;
     else if (k == "round_templates") c->opt_round_templates = value;
     else if (k == "fused") c->opt_fused = value;
     else if (k == "timing") c->opt_timing = value;
@@ -2396,8 +2400,9 @@ ccr_status ccr_set_option(ccr_ctx *c, const char *name, int64_t value) {
     else if (k == "farrow_stage") c->opt_farrow_stage = value ? 1 : 0;
     else return fail(c, CCR_EUNSUP, "unknown option '%s'", name);
     if (k == "template_batch" || k == "workspace_mb" || k == "k_chunk" || k == "items_per_launch" || k == "farrow" ||
-        k == "farrow_stage" || k == "fused" || k == "spectra_kernel" || k == "round_templates")
+        k == "farrow_stage" || k == "fused" || k == "spectra_kernel" || k == "round_templates" || k == "grid")
         c->gen++;
+    if (k == "grid") c->tuned.clear();  // (shapes tuned on other kernels)
     return CCR_OK;
 }
 
@@ -2417,6 +2422,7 @@ ccr_status ccr_get_option(ccr_ctx *c, const char *name, int64_t *value) {
     else if (k == "tuned_template_batch") *value = c->last_tuned_template_batch;
     else if (k == "tuned_spectra_kernel") *value = c->last_tuned_spectra;
     else if (k == "spectra_kernel") *value = c->opt_spectra_kernel;
+    else if (k == "grid") *value = c->opt_grid;
     else if (k == "round_templates") *value = c->opt_round_templates;
     else if (k == "tuned_round_templates") *value = c->last_tuned_round_templates;
     else if (k == "tuned_own_chunks") *value = c->last_tuned_own;
